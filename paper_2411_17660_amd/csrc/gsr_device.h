@@ -36,7 +36,8 @@ struct alignas(16) Record {
   float a1, a2, a3, opacity;
   float c0, c1, c2, z;
   uint32_t sqx, sqy;      // lo | hi << 16
-  uint32_t reserved0, reserved1;
+  float cull_r;           // sqrt(q) where alpha reaches 1/255, plus a margin of 1e-3
+  uint32_t reserved;
 };
 static_assert(sizeof(Record) == 64, "record layout");
 

@@ -87,7 +87,7 @@ void launch_ranges(hipStream_t st, const void* keys, int bits, const uint64_t* k
 // (`xcd_groups`, else one group), longest expected work first by
 // `prev_nproc` (processed entries of a previous forward over the same
 // tiles) when given, else in spatial order.  order [n_tiles] is scratch.
-void launch_composite_fwd(hipStream_t st, int tw, int th, int batch, int n_tiles, int F,
+void launch_composite_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
                           const Record* rec, const float* bg, float* rgb, float* depth,
                           float* alpha, float* t_final, int32_t* n_last, uint32_t* nproc,

@@ -89,6 +89,7 @@ struct Proj {
   int clamp_x, clamp_y;
   int32_t x_lo, x_hi, y_lo, y_hi;      // 3-sigma pixel square
   int32_t bx_lo, bx_hi, by_lo, by_hi;  // its part that can reach alpha >= 1/255
+  double Qa;                           // q where alpha reaches 1/255
 };
 
 __device__ __forceinline__ void project(const FrameDesc& fr, const double W[9],
@@ -165,6 +166,7 @@ __device__ __forceinline__ void project(const FrameDesc& fr, const double W[9],
   // sqrt(Qa s_xx), sqrt(Qa s_yy).  Outside it alpha < 1/255, so dropping
   // those tiles leaves the images unchanged.
   const double Qa = 2.0 * log(G.opacity / (double)kAlphaMin) * (1.0 + 1e-9);
+  p.Qa = Qa;
   if (!(Qa > 0.0)) return;
   const double hx = sqrt(Qa * p.cov[0]), hy = sqrt(Qa * p.cov[2]);
   const double ba = ceil(p.u - hx), bb = floor(p.u + hx);
@@ -249,8 +251,8 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(
     // (outside it alpha < 1/255, so the contribution rule is unchanged)
     o.sqx = (uint32_t)p.bx_lo | ((uint32_t)p.bx_hi << 16);
     o.sqy = (uint32_t)p.by_lo | ((uint32_t)p.by_hi << 16);
-    o.reserved0 = 0;
-    o.reserved1 = 0;
+    o.cull_r = (float)sqrt(p.Qa) + 1e-3f;
+    o.reserved = 0;
     rec[r] = o;
   }
 }

@@ -1,5 +1,5 @@
 // raster.hip -- front-to-back compositing (forward) and its reverse-order
-// backward, one wavefront per tile.
+// backward.
 //
 // Forward, per pixel, over its tile's list in (depth, index) order
 // (DROID-Splat eqn:rendering, C = sum_i c_i a_i prod_{j<i}(1 - a_j), with
@@ -8,13 +8,17 @@
 // stops before an entry that would drop T below 1e-4.  Outputs RGB + T bg,
 // the alpha-blended depth sum z_i a_i T_i and accumulated alpha 1 - T.
 //
-// Layout on CDNA4: a tile of TW x TH pixels is one 64-lane wave; lane l owns
-// column l % TW and PIX = TW*TH/64 pixels in row strips of 64/TW rows, so a
-// whole strip is skipped (wave-uniform branch) when an entry's square misses
-// its rows.  64 records at a time are staged in LDS by the wave itself and
-// read back as broadcasts; per-entry values stay wave-uniform.
+// Layout on CDNA4: a wave composites one 8 x 8 block, a pixel per lane.  For
+// every 64 list entries each lane tests its own entry against the block
+// (exact ellipse against rectangle), so the wave visits only entries that
+// reach it (on 500k Gaussians over 8 x 1200x680, 98 % of the visits blend at
+// least one pixel; with 16 x 4 strips and the entries' boxes 46 % did).  What
+// bounds the forward is VALU issue, ~26 instructions a visit; it took 1081 us
+// there with one wave per 16 x 16 tile, 738 us with one per block, and on one
+// 640x480 frame, whose 1,200 tiles left one wave to a SIMD, 509 and 65 us.
 //
-// Backward: the wave walks the tile's processed prefix from the back.  Each
+// Backward: one wave per tile (PIX pixels per lane in row strips of 64 / TW
+// rows) walks the tile's processed prefix from the back.  Each
 // lane recomputes alpha bit-identically (same helpers, explicit fma),
 // rebuilds T_i = T_{i+1} / (1 - a_i) (reciprocal plus one Newton step) and
 // carries what is seen behind each entry through the convex recurrence
@@ -59,8 +63,9 @@ __device__ __forceinline__ uint32_t work_bucket(uint32_t w) {
 // depend on it).  Work = processed entries of a previous forward over the
 // same tiles (`nproc`); without it the tiles keep their spatial order.
 __global__ void __launch_bounds__(1024) tile_order_kernel(int n_tiles, int groups,
-                                                          const uint32_t* __restrict__ nproc,
-                                                          uint32_t* __restrict__ order) {
+                                                          const uint32_t* nproc,
+                                                          uint32_t* __restrict__ order,
+                                                          uint32_t* clear) {
   static_assert(kOrderBins == 1024, "one thread per bin in the offsets scan");
   __shared__ uint32_t bins[kOrderBins];
   const int q = blockIdx.x;
@@ -69,7 +74,10 @@ __global__ void __launch_bounds__(1024) tile_order_kernel(int n_tiles, int group
   for (int i = threadIdx.x; i < kOrderBins; i += blockDim.x) bins[i] = 0;
   __syncthreads();
   if (!nproc) {
-    for (int t = t0 + (int)threadIdx.x; t < t1; t += blockDim.x) order[t] = (uint32_t)t;
+    for (int t = t0 + (int)threadIdx.x; t < t1; t += blockDim.x) {
+      order[t] = (uint32_t)t;
+      if (clear) clear[t] = 0u;
+    }
     return;
   }
   for (int t = t0 + (int)threadIdx.x; t < t1; t += blockDim.x)
@@ -95,140 +103,190 @@ __global__ void __launch_bounds__(1024) tile_order_kernel(int n_tiles, int group
   for (int t = t0 + (int)threadIdx.x; t < t1; t += blockDim.x) {
     const uint32_t pos = atomicAdd(&bins[work_bucket(nproc[t])], 1u);
     order[t0 + pos] = (uint32_t)t;
+    if (clear) clear[t] = 0u;  // (may be nproc: this thread has read its tiles' counts)
   }
 }
 
-// The tile of workgroup `bid`, or -1 past the end of its group.
+// Pixel blocks.  A tile of TW x TH pixels is cut into 8 x 8 blocks, one pixel
+// per lane (lane l owns pixel (l % 8, l / 8) of a block).  A square block has
+// the smallest perimeter of 64 pixels, so the fewest Gaussians touch it.
+constexpr int kBlk = 8;
 
-template <int TW, int TH, bool COUNT, bool MEDIAN, int BATCH>
-__device__ __forceinline__ void composite_fwd_tile(
-    int tile, Record* sm, int n_frames, const FrameDesc* __restrict__ frames,
-    const uint2* __restrict__ ranges, const uint32_t* __restrict__ vals,
-    const Record* __restrict__ rec, float bg0, float bg1, float bg2, float* __restrict__ rgb,
-    float* __restrict__ depth, float* __restrict__ alpha, float* __restrict__ t_final,
-    int32_t* __restrict__ n_last, uint32_t* __restrict__ tile_nproc,
-    unsigned long long* __restrict__ pair_count, int32_t* __restrict__ med_pos) {
-  constexpr int PIX = TW * TH / kWave;
-  constexpr int RPP = kWave / TW;  // rows per strip
-  const int f = frame_of_tile(frames, n_frames, tile);
-  const FrameDesc fr = frames[f];
-  const int lt = tile - fr.tile_offset;
-  const int x0 = (lt % fr.grid_x) * TW, y0 = (lt / fr.grid_x) * TH;
-  const int lane = threadIdx.x;
-  const int px = x0 + lane % TW;
-  const int ly = lane / TW;
-  const uint2 rg = ranges[tile];
+template <int TW, int TH>
+struct TileBlocks {
+  static constexpr int kX = TW / kBlk, kY = TH / kBlk, kN = kX * kY;
+};
 
-  // D: alpha-blended depth, or (MEDIAN) the depth of the entry after which
-  // T first falls below 1/2, at list position mpos (-1: none yet)
-  float T[PIX], C0[PIX], C1[PIX], C2[PIX], D[PIX];
-  int last[PIX], mpos[PIX];
-  bool done[PIX];
-  uint32_t hits = 0;  // (pixel, entry) pairs whose square test passed (COUNT only)
-#pragma unroll
-  for (int k = 0; k < PIX; ++k) {
-    T[k] = 1.0f; C0[k] = C1[k] = C2[k] = D[k] = 0.0f; last[k] = 0; mpos[k] = -1;
-    const int py = y0 + k * RPP + ly;
-    done[k] = !(px < fr.width && py < fr.height);
-  }
-  for (uint32_t b = rg.x; b < rg.y; b += BATCH) {
-    bool live = false;
-#pragma unroll
-    for (int k = 0; k < PIX; ++k) live |= !done[k];
-    if (__ballot(live) == 0) break;
-#pragma unroll
-    for (int i = lane; i < BATCH; i += kWave) {
-      const uint32_t e = b + (uint32_t)i;
-      if (e < rg.y) sm[i] = rec[vals[e]];
-    }
-    __syncthreads();
-    const int cnt = (int)min((uint32_t)BATCH, rg.y - b);
-    for (int j = 0; j < cnt; ++j) {
-      const Record& R = sm[j];
-      // The fields every pixel strip reads up to the alpha test, loaded from
-      // LDS once per entry (read in each strip, they would be reloaded there
-      // with the address rebuilt each time).
-      float e_vhi = R.v_hi, e_vlo = R.v_lo, e_a1 = R.a1, e_a2 = R.a2, e_a3 = R.a3, e_op = R.opacity;
-      asm volatile("" : "+v"(e_vhi), "+v"(e_vlo), "+v"(e_a1), "+v"(e_a2), "+v"(e_a3), "+v"(e_op));
-      const int xlo = R.sqx & 0xffff, xhi = R.sqx >> 16;
-      const int ylo = R.sqy & 0xffff, yhi = R.sqy >> 16;
-      const bool xin = (unsigned)(px - xlo) <= (unsigned)(xhi - xlo);
-      const float dx = dx_of(R.u_hi, R.u_lo, px);
-#pragma unroll
-      for (int k = 0; k < PIX; ++k) {
-        const int row0 = y0 + k * RPP;
-        if (ylo > row0 + RPP - 1 || yhi < row0) continue;  // strip missed (uniform)
-        const int py = row0 + ly;
-        if (done[k] || !xin || (unsigned)(py - ylo) > (unsigned)(yhi - ylo)) continue;
-        if (COUNT) ++hits;
-        const float dy = dx_of(e_vhi, e_vlo, py);
-        const float q = q_of(e_a1, e_a2, e_a3, dx, dy);
-        const float g = gauss_of(q);
-        const float a = fminf(kAlphaMax, e_op * g);
-        if (a < kAlphaMin) continue;
-        const float Tn = T[k] * (1.0f - a);
-        if (Tn < kTMin) { done[k] = true; continue; }
-        const float w = a * T[k];
-        C0[k] += R.c0 * w;
-        C1[k] += R.c1 * w;
-        C2[k] += R.c2 * w;
-        if (MEDIAN) {
-          if (mpos[k] < 0 && Tn < 0.5f) {
-            mpos[k] = (int)(b + j - rg.x);
-            D[k] = R.z;
-          }
-        } else {
-          D[k] += R.z * w;
-        }
-        T[k] = Tn;
-        last[k] = (int)(b + j + 1 - rg.x);
-      }
-    }
-    __syncthreads();
-  }
-  int mx = 0;
-  const int64_t plane = (int64_t)fr.width * fr.height;
-#pragma unroll
-  for (int k = 0; k < PIX; ++k) {
-    const int py = y0 + k * RPP + ly;
-    if (px < fr.width && py < fr.height) {
-      const int64_t p = (int64_t)py * fr.width + px;
-      float* img = rgb + 3 * fr.pixel_offset;
-      img[p] = C0[k] + T[k] * bg0;
-      img[plane + p] = C1[k] + T[k] * bg1;
-      img[2 * plane + p] = C2[k] + T[k] * bg2;
-      depth[fr.pixel_offset + p] = D[k];
-      alpha[fr.pixel_offset + p] = 1.0f - T[k];
-      t_final[fr.pixel_offset + p] = T[k];
-      n_last[fr.pixel_offset + p] = last[k];
-      if (MEDIAN) med_pos[fr.pixel_offset + p] = mpos[k];
-      mx = max(mx, last[k]);
-    }
-  }
-  for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
-  if (lane == 0) tile_nproc[tile] = (uint32_t)mx;
-  if (COUNT) {
-    unsigned long long h = hits;
-    for (int o = 32; o > 0; o >>= 1) h += __shfl_xor(h, o, 64);
-    if (lane == 0) atomicAdd(pair_count, h);
-  }
+// The pixels of the 8 x 8 block at (bx, by) inside an entry's pixel bounds, one
+// bit per lane: 0 where the block's part inside the bounds cannot reach
+// alpha >= 1/255, by the least q = (a1 dx + a2 dy)^2 + (a3 dy)^2 over it
+// against cull_r^2 (q where alpha reaches 1/255, and a margin).  Each lane
+// asks this of its own record, so 64 entries cost one evaluation.  q is
+// convex with its minimum at d = 0: over the half-plane beyond the block side
+// nearest to 0 it is least at dy = -a1 a2 x / (a2^2 + a3^2), so over the block
+// it is least in the row nearest to that dy, where m = a1 dx + a2 dy runs over
+// an interval.  Conservative: cull_r holds a margin of 1e-3 and the threshold
+// grows by 4e-6 (64 FP32 ulps) of the largest terms that can cancel in m, far
+// above the rounding of this test and of q_of, so a pixel of a part that
+// fails it has a computed alpha < 1/255 and the images do not change.  NaN
+// keeps the block.  ALL: the bounds alone.
+template <bool ALL>
+__device__ __forceinline__ uint64_t block_pixels(const Record& R, int bx, int by) {
+  const int xlo = max(bx, (int)(R.sqx & 0xffff)), xhi = min(bx + kBlk - 1, (int)(R.sqx >> 16));
+  const int ylo = max(by, (int)(R.sqy & 0xffff)), yhi = min(by + kBlk - 1, (int)(R.sqy >> 16));
+  if (xlo > xhi || ylo > yhi) return 0;
+  const float dxl = dx_of(R.u_hi, R.u_lo, xhi), dxh = dx_of(R.u_hi, R.u_lo, xlo);
+  const float dyl = dx_of(R.v_hi, R.v_lo, yhi), dyh = dx_of(R.v_hi, R.v_lo, ylo);
+  const float xn = __builtin_amdgcn_fmed3f(0.0f, dxl, dxh);
+  const float ys = -(R.a1 * R.a2 * xn) * __builtin_amdgcn_rcpf(R.a2 * R.a2 + R.a3 * R.a3);
+  const float yc = __builtin_amdgcn_fmed3f(ys, dyl, dyh);
+  const float m = __builtin_amdgcn_fmed3f(0.0f, R.a1 * dxl + R.a2 * yc, R.a1 * dxh + R.a2 * yc);
+  const float b = R.a3 * yc;
+  const float big = R.a1 * fmaxf(fabsf(dxl), fabsf(dxh)) +
+                    (fabsf(R.a2) + R.a3) * fmaxf(fabsf(dyl), fabsf(dyh));
+  const float r = R.cull_r + 4e-6f * big;
+  if (!ALL && m * m + b * b > r * r) return 0;
+  const uint32_t cols = (0xffu >> (kBlk - 1 - (xhi - xlo))) << (xlo - bx);
+  const uint64_t rows = (~0ull >> (kBlk * (kBlk - 1 - (yhi - ylo)))) << (kBlk * (ylo - by));
+  const uint32_t c4 = cols * 0x01010101u;
+  return (((uint64_t)c4 << 32) | c4) & rows;
 }
 
+// The entry fields that the compositing reads per pixel, staged in LDS.
+struct alignas(16) Entry {
+  float4 c;    // u_hi, u_lo, v_hi, v_lo
+  float4 q;    // a1, a2, a3, opacity
+  float4 col;  // c0, c1, c2, z
+};
 
-template <int TW, int TH, bool COUNT, bool MEDIAN, int BATCH>
-__global__ void __launch_bounds__(64) composite_fwd_kernel(
+__device__ __forceinline__ Entry entry_of(const Record& R) {
+  return {make_float4(R.u_hi, R.u_lo, R.v_hi, R.v_lo), make_float4(R.a1, R.a2, R.a3, R.opacity),
+          make_float4(R.c0, R.c1, R.c2, R.z)};
+}
+
+// The forward's LDS entry: also the block's pixels inside the entry's bounds
+// and one past its list position.
+struct alignas(16) FwdEntry {
+  Entry e;
+  uint32_t px_lo, px_hi, pos, pad;
+};
+
+// One wave composites one 8 x 8 block, a pixel per lane.  Records of 64
+// entries at a time wait in registers (their loads are issued while the batch
+// before them is composited), each lane culls its record against the block,
+// and the ones that reach it are packed into LDS in list order, where the wave
+// reads them back as broadcasts one entry ahead of their use.  Which lanes
+// take part is kept as wave-uniform lane masks.
+template <int TW, int TH, bool COUNT, bool MEDIAN>
+__global__ void __launch_bounds__(kWave) composite_fwd_kernel(
     int n_tiles, int groups, const uint32_t* __restrict__ order, int n_frames,
     const FrameDesc* __restrict__ frames, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ vals, const Record* __restrict__ rec, float bg0, float bg1,
     float bg2, float* __restrict__ rgb, float* __restrict__ depth, float* __restrict__ alpha,
     float* __restrict__ t_final, int32_t* __restrict__ n_last, uint32_t* __restrict__ tile_nproc,
     unsigned long long* __restrict__ pair_count, int32_t* __restrict__ med_pos) {
-  __shared__ Record sm[BATCH];
-  const int tile = tile_of_block(blockIdx.x, n_tiles, groups, order);
+  using TB = TileBlocks<TW, TH>;
+  __shared__ FwdEntry sm[kWave + 2];
+  // workgroup i of a group takes block i % kN of its (i / kN)-th tile, so that
+  // a tile's blocks share the XCD of its group (and the records in its L2)
+  const int group = blockIdx.x % groups, i_wg = blockIdx.x / groups;
+  const int tile = tile_of_block((i_wg / TB::kN) * groups + group, n_tiles, groups, order);
   if (tile < 0) return;
-  composite_fwd_tile<TW, TH, COUNT, MEDIAN, BATCH>(tile, sm, n_frames, frames, ranges, vals, rec, bg0,
-                                             bg1, bg2, rgb, depth, alpha, t_final, n_last,
-                                             tile_nproc, pair_count, med_pos);
+  const int blk = i_wg % TB::kN;
+  const int f = frame_of_tile(frames, n_frames, tile);
+  const FrameDesc fr = frames[f];
+  const int lt = tile - fr.tile_offset;
+  const int bx = (lt % fr.grid_x) * TW + (blk % TB::kX) * kBlk;
+  const int by = (lt / fr.grid_x) * TH + (blk / TB::kX) * kBlk;
+  const int lane = threadIdx.x;
+  const int px = bx + (lane & 7), py = by + (lane >> 3);
+  const uint2 rg = ranges[tile];
+
+  // D: alpha-blended depth, or (MEDIAN) the depth of the entry after which
+  // T first falls below 1/2, one past list position mpos (0: none yet)
+  float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, D = 0.0f;
+  uint32_t last = 0, mpos = 0;
+  uint64_t open = __ballot(px < fr.width && py < fr.height);  // pixels that have not stopped
+  uint64_t hits = 0;  // (pixel, entry) pairs whose square test passed (COUNT only)
+  const auto blend = [&](const FwdEntry& E) {
+    const uint64_t in = (((uint64_t)__builtin_amdgcn_readfirstlane(E.px_hi) << 32) |
+                         (uint32_t)__builtin_amdgcn_readfirstlane(E.px_lo)) & open;
+    if (COUNT) hits += __popcll(in);
+    const float dx = dx_of(E.e.c.x, E.e.c.y, px), dy = dx_of(E.e.c.z, E.e.c.w, py);
+    const float q = q_of(E.e.q.x, E.e.q.y, E.e.q.z, dx, dy);
+    const float a = fminf(kAlphaMax, E.e.q.w * gauss_of(q));
+    const float Tn = T * (1.0f - a);
+    uint64_t act = __ballot(!(a < kAlphaMin)) & in;
+    const uint64_t stop = __ballot(Tn < kTMin) & act;
+    open &= ~stop;
+    act &= ~stop;
+    if (__builtin_amdgcn_inverse_ballot_w64(act)) {
+      const float w = a * T;
+      C0 += E.e.col.x * w;
+      C1 += E.e.col.y * w;
+      C2 += E.e.col.z * w;
+      if (MEDIAN) {
+        if (mpos == 0 && Tn < 0.5f) {
+          mpos = E.pos;
+          D = E.e.col.w;
+        }
+      } else {
+        D += E.e.col.w * w;
+      }
+      T = Tn;
+      last = E.pos;
+    }
+  };
+  // the batch's record in registers, and the next batch's list entry
+  Record R{};
+  uint32_t v_next = 0;
+  if (rg.x + lane < rg.y) R = rec[vals[rg.x + lane]];
+  if (rg.x + kWave + lane < rg.y) v_next = vals[rg.x + kWave + lane];
+  for (uint32_t b = rg.x; b < rg.y && open; b += kWave) {
+    uint64_t in = 0;
+    asm volatile("" ::"v"(R.reserved));  // (below)
+    if (b + lane < rg.y) in = block_pixels<COUNT>(R, bx, by);
+    const uint64_t mk = __ballot(in != 0);
+    const int n = __popcll(mk);
+    const int at = __builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0u));
+    if (in) sm[at] = {entry_of(R), (uint32_t)in, (uint32_t)(in >> 32), b + lane + 1 - rg.x, 0u};
+    if (lane < 2) sm[n + lane].px_lo = sm[n + lane].px_hi = 0u;  // (entries are taken in pairs)
+    // Every register the record's loads write has a reader, at the latest the
+    // empty asm above: the register of a word that nothing reads would go to
+    // another value, whose first write then waits for the load.
+    if (b + kWave + lane < rg.y) R = rec[v_next];
+    if (b + 2 * kWave + lane < rg.y) v_next = vals[b + 2 * kWave + lane];
+    __syncthreads();
+    FwdEntry E0 = sm[0];
+    for (int i = 0; i < n && open; i += 2) {
+      const FwdEntry E1 = sm[i + 1];
+      blend(E0);
+      E0 = sm[i + 2];
+      blend(E1);
+    }
+    __syncthreads();
+  }
+  if (px < fr.width && py < fr.height) {
+    const int64_t plane = (int64_t)fr.width * fr.height;
+    const int64_t p = (int64_t)py * fr.width + px;
+    float* img = rgb + 3 * fr.pixel_offset;
+    img[p] = C0 + T * bg0;
+    img[plane + p] = C1 + T * bg1;
+    img[2 * plane + p] = C2 + T * bg2;
+    depth[fr.pixel_offset + p] = D;
+    alpha[fr.pixel_offset + p] = 1.0f - T;
+    t_final[fr.pixel_offset + p] = T;
+    n_last[fr.pixel_offset + p] = (int32_t)last;
+    if (MEDIAN) med_pos[fr.pixel_offset + p] = (int32_t)mpos - 1;
+  }
+  int mx = (int)last;
+  for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
+  if (lane == 0) {
+    if (TB::kN == 1) tile_nproc[tile] = (uint32_t)mx;
+    else if (mx > 0) atomicMax(&tile_nproc[tile], (uint32_t)mx);  // cleared by the order kernel
+  }
+  if (COUNT && lane == 0) atomicAdd(pair_count, (unsigned long long)hits);
 }
 
 template <int TW, int TH, bool MEDIAN, int BATCH>
@@ -440,9 +498,9 @@ __global__ void __launch_bounds__(64, (TW * TH <= 256) ? 4 : 1) composite_bwd_ke
 }
 
 static void launch_order(hipStream_t st, int n_tiles, int groups, const uint32_t* nproc,
-                         uint32_t* order) {
+                         uint32_t* order, uint32_t* clear = nullptr) {
   hipLaunchKernelGGL(tile_order_kernel, dim3((unsigned)groups), dim3(1024), 0, st, n_tiles,
-                     groups, nproc, order);
+                     groups, nproc, order, clear);
 }
 
 static unsigned grid_of(int n_tiles, int groups) {
@@ -457,50 +515,21 @@ void launch_tile_order(hipStream_t st, int n_tiles, int groups, const uint32_t* 
 unsigned tile_schedule_grid(int n_tiles, int groups) { return grid_of(n_tiles, groups); }
 int tile_schedule_groups(bool xcd_groups) { return xcd_groups ? kQueues : 1; }
 
-template <int TW, int TH, bool COUNT, bool MEDIAN, int BATCH>
-static void launch_fwd_v(hipStream_t st, int n_tiles, int groups, const uint32_t* order, int F,
-                         const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
-                         const Record* rec, const float* bg, float* rgb, float* depth,
-                         float* alpha, float* t_final, int32_t* n_last, uint32_t* nproc,
-                         unsigned long long* pairs, int32_t* med_pos) {
-  auto k = composite_fwd_kernel<TW, TH, COUNT, MEDIAN, BATCH>;
-  hipLaunchKernelGGL(k, dim3(grid_of(n_tiles, groups)), dim3(kWave), 0, st, n_tiles, groups,
-                     order, F, frames, ranges, vals, rec, bg[0], bg[1], bg[2], rgb, depth, alpha,
-                     t_final, n_last, nproc, pairs, med_pos);
-}
-
-template <int TW, int TH, int BATCH>
-static void launch_fwd_b(hipStream_t st, int n_tiles, int groups, const uint32_t* order, int F,
-                         const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
-                         const Record* rec, const float* bg, float* rgb, float* depth,
-                         float* alpha, float* t_final, int32_t* n_last, uint32_t* nproc,
-                         unsigned long long* pairs, int32_t* med_pos) {
-#define GSR_FWD_V(C, M)                                                                         \
-  launch_fwd_v<TW, TH, C, M, BATCH>(st, n_tiles, groups, order, F, frames, ranges, vals, rec,    \
-                                    bg, rgb, depth, alpha, t_final, n_last, nproc, pairs,        \
-                                    med_pos)
-  if (pairs) {
-    if (med_pos) GSR_FWD_V(true, true); else GSR_FWD_V(true, false);
-  } else {
-    if (med_pos) GSR_FWD_V(false, true); else GSR_FWD_V(false, false);
-  }
-#undef GSR_FWD_V
-}
-
 template <int TW, int TH>
-static void launch_fwd_t(hipStream_t st, int batch, int n_tiles, int groups,
-                         const uint32_t* order, int F, const FrameDesc* frames,
-                         const uint2* ranges, const uint32_t* vals, const Record* rec,
-                         const float* bg, float* rgb, float* depth, float* alpha, float* t_final,
-                         int32_t* n_last, uint32_t* nproc, unsigned long long* pairs,
-                         int32_t* med_pos) {
-#define GSR_FWD_B(B)                                                                           \
-  launch_fwd_b<TW, TH, B>(st, n_tiles, groups, order, F, frames, ranges, vals, rec, bg, rgb,     \
-                          depth, alpha, t_final, n_last, nproc, pairs, med_pos)
-  if (batch == 32) GSR_FWD_B(32);
-  else if (batch == 128) GSR_FWD_B(128);
-  else GSR_FWD_B(64);
-#undef GSR_FWD_B
+static void launch_fwd_t(hipStream_t st, int n_tiles, int groups, const uint32_t* order, int F,
+                         const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
+                         const Record* rec, const float* bg, float* rgb, float* depth,
+                         float* alpha, float* t_final, int32_t* n_last, uint32_t* nproc,
+                         unsigned long long* pairs, int32_t* med_pos) {
+  const auto go = [&](auto* k) {
+    hipLaunchKernelGGL(k, dim3(grid_of(n_tiles, groups) * TileBlocks<TW, TH>::kN), dim3(kWave), 0,
+                       st, n_tiles, groups, order, F, frames, ranges, vals, rec, bg[0], bg[1],
+                       bg[2], rgb, depth, alpha, t_final, n_last, nproc, pairs, med_pos);
+  };
+  if (pairs && med_pos) go(composite_fwd_kernel<TW, TH, true, true>);
+  else if (pairs) go(composite_fwd_kernel<TW, TH, true, false>);
+  else if (med_pos) go(composite_fwd_kernel<TW, TH, false, true>);
+  else go(composite_fwd_kernel<TW, TH, false, false>);
 }
 
 template <int TW, int TH, int BATCH>
@@ -545,7 +574,7 @@ static void launch_bwd_t(hipStream_t st, int batch, int n_tiles, int groups,
 #undef GSR_BWD_B
 }
 
-void launch_composite_fwd(hipStream_t st, int tw, int th, int batch, int n_tiles, int F,
+void launch_composite_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
                           const Record* rec, const float* bg, float* rgb, float* depth,
                           float* alpha, float* t_final, int32_t* n_last, uint32_t* nproc,
@@ -553,10 +582,10 @@ void launch_composite_fwd(hipStream_t st, int tw, int th, int batch, int n_tiles
                           unsigned long long* pairs, int32_t* med_pos) {
   if (n_tiles <= 0) return;
   const int groups = xcd_groups ? kQueues : 1;
-  launch_order(st, n_tiles, groups, prev_nproc, order);
-#define GSR_FWD(W, H)                                                                         \
-  launch_fwd_t<W, H>(st, batch, n_tiles, groups, order, F, frames, ranges, vals, rec, bg, rgb,  \
-                     depth, alpha, t_final, n_last, nproc, pairs, med_pos)
+  launch_order(st, n_tiles, groups, prev_nproc, order, nproc);
+#define GSR_FWD(W, H)                                                                        \
+  launch_fwd_t<W, H>(st, n_tiles, groups, order, F, frames, ranges, vals, rec, bg, rgb, depth,  \
+                     alpha, t_final, n_last, nproc, pairs, med_pos)
   if (tw == 16 && th == 16) GSR_FWD(16, 16);
   else if (tw == 8 && th == 8) GSR_FWD(8, 8);
   else if (tw == 32 && th == 8) GSR_FWD(32, 8);

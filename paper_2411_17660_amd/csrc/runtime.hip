@@ -430,7 +430,7 @@ gsr_status forward_impl(gsr_context* ctx, const gsr_settings* s, int64_t n, cons
                         P<uint32_t>(ctx->nproc), have_prev ? P<uint32_t>(ctx->nproc) : nullptr,
                         P<uint32_t>(ctx->order_f), remap, count ? d_pairs : nullptr);
     else
-      launch_composite_fwd(st, tw, th, s->lds_batch ? s->lds_batch : kWave, (int)T, F,
+      launch_composite_fwd(st, tw, th, (int)T, F,
                            P<FrameDesc>(ctx->frames),
                            P<uint2>(ctx->ranges), svals, P<Record>(ctx->rec), s->background,
                            rgb, depth, alpha, P<float>(ctx->t_final), P<int32_t>(ctx->n_last),

@@ -1,0 +1,43 @@
+"""Compositing over 8 x 8 pixel blocks against the oracle where it can go
+wrong: every number of blocks per backward wave (chosen by the tile count),
+images that end inside a block or a tile, entries that only graze a block
+(thin, rotated Gaussians), lists around the batch of 64 entries, and the
+median depth on each path.  Bars: those of the parity tests (lists and stop
+positions bit-exact, images 1e-4 absolute on unflagged pixels, gradients 1e-3
+relative with the oracle's noise term)."""
+import numpy as np
+import pytest
+
+from paper_2411_17660_amd import scenes
+from test_gpu_parity import check_backward, check_forward
+
+pytestmark = pytest.mark.gpu
+
+# (W, H), tile: a backward wave takes as many blocks (up to 4) as leave 4,096
+# waves, so 16x16 tiles take one block below 2,048 of them, two below 4,096
+# and four beyond
+SHAPES = [((33, 17), (16, 16)), ((8, 8), (8, 8)), ((785, 689), (16, 16)),
+          ((1030, 1025), (16, 16)), ((1025, 513), (32, 16)), ((1030, 530), (16, 8)),
+          ((1031, 1025), (32, 8)), ((523, 509), (8, 8))]
+
+
+@pytest.fixture(scope="module")
+def rast():
+    from paper_2411_17660_amd.raster import Rasterizer
+    return Rasterizer(0)
+
+
+@pytest.mark.parametrize("median", [False, True])
+@pytest.mark.parametrize("size,tile", SHAPES)
+def test_blocks_match_oracle(rast, size, tile, median):
+    W, H = size
+    for n, thin in ((63, True), (65, False), (200, True)):
+        label = f"blocks {W}x{H}/{tile[0]}x{tile[1]} n{n}"
+        sc = scenes.tiny_scene(seed=n, n=n, W=W, H=H, f=0.7 * max(W, H), sh_degree=1,
+                               ls_mean=-2.2, ls_sigma=0.5, opacity_sigma=1.5)
+        if thin:  # 20 : 1 needles at random angles: most of their box is empty
+            ls = np.array(sc.log_scales)
+            ls[:, 1:] = ls[:, :1] - 3.0
+            sc.log_scales = np.ascontiguousarray(ls, np.float32)
+        ref, _, flags = check_forward(rast, sc, tile=tile, label=label, median=median)
+        check_backward(rast, sc, ref, flags, n, label=label)
