@@ -82,8 +82,8 @@ typedef struct {
   int32_t sh_degree;      /* 0..3 */
   float background[3];
   int32_t tile_w, tile_h; /* 16x16, 8x8, 32x8, 16x8 or 32x16 */
-  int32_t lds_batch;      /* Gaussians staged per LDS round by the 3D compositing kernels:
-                             32, 64, 128; 0 = 64 (the surfel kernels always stage 64) */
+  int32_t lds_batch;      /* 0, 32, 64 or 128: accepted, without effect on results or
+                             speed (the compositing kernels stage 64 entries per round) */
   int64_t key_capacity;   /* 0: the library sizes the key buffers from the
                              exact count (one 8-byte device->host read per
                              forward); > 0: fixed capacity, no host read, and
@@ -329,18 +329,15 @@ gsr_status gsr_mcmc_relocate(gsr_context* ctx, int64_t n, int32_t sh_degree, flo
                              const int32_t* src, void* stream);
 
 /* Autotuner: runs gsr_step_l1 with every supported tile shape (16x16, 8x8,
- * 32x8, 16x8, 32x16) and every LDS batch (32, 64, 128 Gaussians staged per
- * round) on the given inputs: one untimed sizing run per tile shape, then
- * `reps` runs per (shape, batch) timed with HIP events on `stream`.  Writes
- * the fastest settings to *chosen (base settings with tile_w, tile_h and
- * lds_batch replaced and a fixed key_capacity 5% above the measured count);
- * on the fastest shape the default batch of 64 is kept when its time is
- * within 1% of the fastest batch's, so that run-to-run noise does not flip
- * between batches that differ by less than it.
- * ms[GSR_TUNE_BATCHES * i + j] receives the median step time of shape i with
- * batch j in the orders above (array of GSR_TUNE_TILES * GSR_TUNE_BATCHES;
- * NULL allowed).  Results do not depend on the choice: images are bitwise
- * the same for every shape and batch.  The choice is cached in the context
+ * 32x8, 16x8, 32x16) on the given inputs: one untimed sizing run per tile
+ * shape, then `reps` runs timed with HIP events on `stream`.  Writes the
+ * fastest settings to *chosen (base settings with tile_w and tile_h replaced,
+ * lds_batch 64 and a fixed key_capacity 5% above the measured count).
+ * ms[GSR_TUNE_BATCHES * i + j] receives the median step time of shape i in
+ * the order above (array of GSR_TUNE_TILES * GSR_TUNE_BATCHES; NULL allowed),
+ * the same for every lds_batch j (32, 64, 128), on which it does not depend.
+ * Results do not depend on the choice: images are bitwise the same for every
+ * shape.  The choice is cached in the context
  * per (multiset of frame sizes, n rounded up to a power of two, SH degree);
  * a cached choice is returned without measuring (ms all -1) unless `force`.
  * The library owns the scratch outputs it renders into. */

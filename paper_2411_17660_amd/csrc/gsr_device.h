@@ -46,8 +46,11 @@ static_assert(sizeof(Record) == 64, "record layout");
 // is the first key slot of record r (written by keygen; all-ones if the record
 // overflowed a fixed key capacity).
 
-// Gradient of one (tile, entry) key: du, dv, dSigma'_xx, dSigma'_xy, dSigma'_yy
-// (symmetric-matrix gradient), dopacity, dc0..2, dz
+// Sums of one (tile, entry) key over its pixels, p = alpha dL/dalpha and
+// (m, b) = (a1 dx + a2 dy, a3 dy): p m, p b, p m^2, p m b, p b^2, dopacity,
+// dc0..2, dz.  Summed per record they become the screen-space gradient du,
+// dv, dSigma'_xx, dSigma'_xy, dSigma'_yy (symmetric-matrix gradient),
+// dopacity, dc0..2, dz.
 constexpr int kNG = 10;
 
 // The frame of a global tile id: the last frame whose first tile is <= tile

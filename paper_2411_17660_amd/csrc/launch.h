@@ -17,7 +17,7 @@ int64_t preprocess_bwd_waves(int64_t n);
 void launch_preprocess_bwd(hipStream_t st, int64_t n, int F, const FrameDesc* frames,
                            const float* poses, const float* means, const float* log_scales,
                            const float* quats, const float* opac, const float* sh, int deg,
-                           const uint32_t* order, const uint32_t* first_wide,
+                           const Record* rec, const uint32_t* order, const uint32_t* first_wide,
                            const uint32_t* keyoff, const uint32_t* ntiles, const float* partial,
                            const uint32_t* stamp, const uint32_t* epoch, uint64_t key_capacity,
                            double* grad2d, float* g_means, float* g_log_scales, float* g_quats,
@@ -93,12 +93,12 @@ void launch_composite_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           float* alpha, float* t_final, int32_t* n_last, uint32_t* nproc,
                           const uint32_t* prev_nproc, uint32_t* order, bool xcd_groups,
                           unsigned long long* pairs, int32_t* med_pos);
-void launch_composite_bwd(hipStream_t st, int tw, int th, int batch, int n_tiles, int F,
+void launch_composite_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
-                          const Record* rec, const uint2* trect, const uint32_t* keyoff,
-                          const uint32_t* nproc, const float* bg, const float* g_rgb,
-                          const float* g_depth, const float* g_alpha, const float* t_final,
-                          const int32_t* n_last, float* partial, uint32_t* stamp,
+                          const Record* rec, const uint32_t* keyoff, const uint32_t* nproc,
+                          const float* bg, const float* g_rgb, const float* g_depth,
+                          const float* g_alpha, const float* t_final, const int32_t* n_last,
+                          float* partial, uint32_t* stamp,
                           const uint32_t* epoch, uint32_t* order, bool xcd_groups,
                           const int32_t* med_pos);
 

@@ -306,6 +306,22 @@ constexpr int kSlotGroup = 4;
 constexpr int kSlotUnroll = 4;
 static_assert(kNG % 2 == 0, "partials are read as float pairs");
 
+// A record's key sums t become its screen-space gradient: with the conic's
+// factor L (Q = L L^T, L^T d = (a1 dx + a2 dy, a3 dy) = (m, b)), the centre's
+// gradient is -L sum p (m, b) and the 2D covariance's is
+// L (sum p (m, b)(m, b)^T) L^T / 2.  Applied here, once per record in FP64,
+// instead of per pixel and entry.
+__device__ __forceinline__ void screen_gradient(const Record& R, double (&t)[kNG]) {
+  const double a1 = R.a1, a2 = R.a2, a3 = R.a3;
+  const double pm = t[0], pb = t[1], pmm = t[2], pmb = t[3], pbb = t[4];
+  const double ym = a2 * pmm + a3 * pmb, yb = a2 * pmb + a3 * pbb;
+  t[0] = -(a1 * pm);
+  t[1] = -(a2 * pm + a3 * pb);
+  t[2] = 0.5 * (a1 * (a1 * pmm));
+  t[3] = 0.5 * (a1 * ym);
+  t[4] = 0.5 * (a2 * ym + a3 * yb);
+}
+
 // The wide pass takes the w-th largest records, w < n_wide = m - *first_wide
 // (capped at wide_max), a wave each in turn (grid stride); 64 lanes stride
 // over a record's slots, kSlotUnroll per lane per round.
@@ -314,7 +330,9 @@ __device__ __forceinline__ void slot_reduce_wide(
     const uint32_t* __restrict__ keyoff, const uint32_t* __restrict__ ntiles,
     const float* __restrict__ partial, const uint32_t* __restrict__ stamp, uint32_t epoch,
     uint64_t key_capacity, const uint32_t* __restrict__ first_wide, uint64_t wide_max,
-    double* __restrict__ grad2d) {
+    const Record* __restrict__ rec, double* __restrict__ grad2d) {
+  __shared__ double tot[256 / kWave][kNG];
+  double* my = tot[threadIdx.x / kWave];
   const uint64_t n_wide = min(m - *first_wide, wide_max);
   const uint64_t stride = ((uint64_t)n_blocks * blockDim.x) / kWave;
   const int lane = threadIdx.x & (kWave - 1);
@@ -359,7 +377,14 @@ __device__ __forceinline__ void slot_reduce_wide(
   int idx;
   bool writer;
   const double v = wave_transpose_sum<kNG>(acc, lane, idx, writer);
-  if (writer) grad2d[r * kNG + idx] = v;
+  if (writer) my[idx] = v;
+  __builtin_amdgcn_wave_barrier();  // a wave's LDS operations complete in issue order
+  if (lane == 0) {
+    double t[kNG];
+    for (int j = 0; j < kNG; ++j) t[j] = my[j];
+    screen_gradient(rec[r], t);
+    for (int j = 0; j < kNG; ++j) grad2d[r * kNG + j] = t[j];
+  }
   }
 }
 
@@ -370,7 +395,7 @@ __device__ __forceinline__ void slot_reduce_groups(
     const uint32_t* __restrict__ keyoff, const uint32_t* __restrict__ ntiles,
     const float* __restrict__ partial, const uint32_t* __restrict__ stamp, uint32_t epoch,
     uint64_t key_capacity, const uint32_t* __restrict__ first_wide, uint64_t wide_max,
-    double* __restrict__ grad2d /* [m][kNG] */) {
+    const Record* __restrict__ rec, double* __restrict__ grad2d /* [m][kNG] */) {
   const uint64_t gid = (uint64_t)block * blockDim.x + threadIdx.x;
   const uint64_t k = gid / kSlotGroup + min(m - *first_wide, wide_max);
   const int sub = threadIdx.x & (kSlotGroup - 1);
@@ -429,6 +454,7 @@ __device__ __forceinline__ void slot_reduce_groups(
     for (int j = sub; j < kNG; j += kSlotGroup) grad2d[r * kNG + j] = 0.0;
     return;
   }
+  screen_gradient(rec[r], acc);
   // lane sub writes values sub, sub + kSlotGroup, ...
 #pragma unroll
   for (int j0 = 0; j0 < kNG; j0 += kSlotGroup) {
@@ -449,14 +475,14 @@ __global__ void __launch_bounds__(256) slot_reduce_kernel(
     const uint32_t* __restrict__ ntiles, const float* __restrict__ partial,
     const uint32_t* __restrict__ stamp, const uint32_t* __restrict__ epoch_dev,
     uint64_t key_capacity, const uint32_t* __restrict__ first_wide, uint64_t wide_max,
-    unsigned wide_blocks, double* __restrict__ grad2d) {
+    unsigned wide_blocks, const Record* __restrict__ rec, double* __restrict__ grad2d) {
   const uint32_t epoch = *epoch_dev;
   if (blockIdx.x < wide_blocks)
     slot_reduce_wide(blockIdx.x, wide_blocks, m, order, keyoff, ntiles, partial, stamp, epoch,
-                     key_capacity, first_wide, wide_max, grad2d);
+                     key_capacity, first_wide, wide_max, rec, grad2d);
   else
     slot_reduce_groups(blockIdx.x - wide_blocks, m, order, keyoff, ntiles, partial, stamp,
-                       epoch, key_capacity, first_wide, wide_max, grad2d);
+                       epoch, key_capacity, first_wide, wide_max, rec, grad2d);
 }
 
 // --------------------------------------------------------------------------
@@ -511,7 +537,7 @@ __global__ void __launch_bounds__(256) preprocess_bwd_kernel(
       dt[1] = gr[1] * fy / tz;
       dt[2] = -gr[0] * fx * tx / tz2 - gr[1] * fy * ty / tz2 + gr[9];
       dsig += gr[5];
-      // the key partials carry dL/dSigma' (symmetric: xx, xy, yy) directly
+      // dL/dSigma' (symmetric: xx, xy, yy)
       const double GS[4] = {gr[2], gr[3], gr[3], gr[4]};
       // Sigma' = J Sc J^T + lowpass: G_J = 2 GS J Sc, G_Sc = J^T GS J
       double JSc[6];
@@ -772,7 +798,7 @@ int64_t preprocess_bwd_waves(int64_t n) { return ((n + 255) / 256) * 4; }
 void launch_preprocess_bwd(hipStream_t st, int64_t n, int F, const FrameDesc* frames,
                            const float* poses, const float* means, const float* log_scales,
                            const float* quats, const float* opac, const float* sh, int deg,
-                           const uint32_t* order, const uint32_t* first_wide,
+                           const Record* rec, const uint32_t* order, const uint32_t* first_wide,
                            const uint32_t* keyoff, const uint32_t* ntiles, const float* partial,
                            const uint32_t* stamp, const uint32_t* epoch, uint64_t key_capacity,
                            double* grad2d, float* g_means, float* g_log_scales, float* g_quats,
@@ -795,7 +821,7 @@ void launch_preprocess_bwd(hipStream_t st, int64_t n, int F, const FrameDesc* fr
     const uint64_t threads = m * kSlotGroup;
     hipLaunchKernelGGL(slot_reduce_kernel, dim3(wide_blocks + (unsigned)((threads + 255) / 256)),
                        dim3(256), 0, st, m, order, keyoff, ntiles, partial, stamp, epoch,
-                       key_capacity, first_wide, wide_max, wide_blocks, grad2d);
+                       key_capacity, first_wide, wide_max, wide_blocks, rec, grad2d);
     switch (deg) {
       case 0: GSR_PRE_BWD(0); break;
       case 1: GSR_PRE_BWD(1); break;

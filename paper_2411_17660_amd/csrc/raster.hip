@@ -1,5 +1,5 @@
 // raster.hip -- front-to-back compositing (forward) and its reverse-order
-// backward.
+// backward, over 8 x 8 pixel blocks of the tiles.
 //
 // Forward, per pixel, over its tile's list in (depth, index) order
 // (DROID-Splat eqn:rendering, C = sum_i c_i a_i prod_{j<i}(1 - a_j), with
@@ -17,11 +17,10 @@
 // there with one wave per 16 x 16 tile, 738 us with one per block, and on one
 // 640x480 frame, whose 1,200 tiles left one wave to a SIMD, 509 and 65 us.
 //
-// Backward: one wave per tile (PIX pixels per lane in row strips of 64 / TW
-// rows) walks the tile's processed prefix from the back.  Each
-// lane recomputes alpha bit-identically (same helpers, explicit fma),
-// rebuilds T_i = T_{i+1} / (1 - a_i) (reciprocal plus one Newton step) and
-// carries what is seen behind each entry through the convex recurrence
+// Backward: the waves of a tile walk the tile's processed prefix from the
+// back.  Each lane recomputes alpha bit-identically (same helpers, explicit
+// fma), rebuilds T_i = T_{i+1} / (1 - a_i) (reciprocal plus one Newton step)
+// and carries what is seen behind each entry through the convex recurrence
 // B_{i-1} = a_i c_i + (1 - a_i) B_i from B = background (depth from 0, the
 // transmittance behind from 1), so that dC/da_i = T_i (c_i - B_i): T_i only
 // scales the result and the recurrence damps rounding instead of
@@ -31,13 +30,17 @@
 // with Q = Sigma'^-1 = L L^T (L the factor the forward already uses) and d
 // the offset, dq/dd = 2 Q d and dq/dSigma' = -(Q d)(Q d)^T,
 // Q d = L (L^T d); this avoids the ill-conditioned -Q dQ Q step from conic
-// gradients for elongated Gaussians.  The 10 per-entry values are summed
-// over the lane's pixels and then across the wave in FP64 through LDS
-// (fixed order); the result for this (tile, entry) key goes to its own slot
-// (no atomics), stamped with the backward's epoch so the per-record
-// reduction can skip slots of keys that no pixel reached.
+// gradients for elongated Gaussians.  What an entry receives from its pixels
+// are moments, summed across the wave in FP64 by matrix products (below); the
+// result for this (tile, entry) key goes to its own slot (no atomics),
+// stamped with the backward's epoch so the per-record reduction can skip
+// slots of keys that no pixel reached.  It took 2531 us on the 8 x 1200x680
+// batch and 708 us on the 640x480 frame with one wave per tile and a
+// reduction through LDS (an LDS pipe shared by four SIMDs, which that
+// reduction held for ~104 clocks a key), 1806 and 233 us as it is now.
 #include "launch.h"
 #include "wave_util.h"
+#include <algorithm>
 
 namespace gsr {
 
@@ -150,6 +153,13 @@ __device__ __forceinline__ uint64_t block_pixels(const Record& R, int bx, int by
   const uint64_t rows = (~0ull >> (kBlk * (kBlk - 1 - (yhi - ylo)))) << (kBlk * (ylo - by));
   const uint32_t c4 = cols * 0x01010101u;
   return (((uint64_t)c4 << 32) | c4) & rows;
+}
+
+// lane j's value of v (j wave-uniform)
+__device__ __forceinline__ uint64_t readlane64(uint64_t v, int j) {
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), j);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, j);
+  return ((uint64_t)hi << 32) | lo;
 }
 
 // The entry fields that the compositing reads per pixel, staged in LDS.
@@ -289,212 +299,298 @@ __global__ void __launch_bounds__(kWave) composite_fwd_kernel(
   if (COUNT && lane == 0) atomicAdd(pair_count, (unsigned long long)hits);
 }
 
-template <int TW, int TH, bool MEDIAN, int BATCH>
-__device__ __forceinline__ void composite_bwd_tile(
-    int tile, Record* sm, uint32_t* slot, double* red, uint32_t epoch, int n_frames,
-    const FrameDesc* __restrict__ frames,
-    const uint2* __restrict__ ranges, const uint32_t* __restrict__ vals,
-    const Record* __restrict__ rec, const uint2* __restrict__ trect,
+// Backward.  A workgroup takes a tile with WAVES waves of PIX blocks each (one
+// pixel of a block per lane); the waves walk the same batches of list entries
+// from the back, each visiting the entries that reach one of its blocks.  Per
+// pixel and visit a lane forms p = a dL/da and w = a T; an entry receives the
+// sums over pixels of w times the upstream colour and depth gradient and of p
+// times 1, X, Y, X^2, X Y, Y^2 (X, Y the pixel's position in the tile).  Sums
+// over the lanes of a wave are products with constant matrices, taken in FP64
+// by v_mfma_f64_4x4x4, whose lane 16 k + 4 b + i holds element (i, k) of the
+// left and (k, i) of the right operand and whose lane 16 i + 4 b + j holds
+// (i, j) of the result, for four independent products b.  With the pixels as
+// they lie in the lanes (i = x % 4, b = x / 4 + 2 (y % 2), k = y / 2) a first
+// product with (1, Y, Y^2) sums over k; its result is laid out as the left
+// operand of a second one with (1, X, X^2) that sums over i; two row rotations
+// add the four b.  The colour and depth sums take the same way with unit
+// matrices and land in the fourth column.  No data goes through LDS and no
+// lane selects anything; a transposing reduction took 62 VALU instructions
+// and 14 more per visit for the products.  One lane per entry then adds the
+// waves' totals in wave order, moves the moments from the tile's origin to the
+// entry's centre, whitens them (all FP64) and stores the key's slot as FP32.
+// What bounds it: VALU issue.
+constexpr int kBatchB = 64;          // list entries per batch
+constexpr int kBwdMinWaves = 4096;  // four waves on each of the 1,024 SIMDs
+static_assert(kNG == 10, "4 colour and depth sums and 6 moments");
+
+struct alignas(16) BwdEntry {  // as Entry, the colour and depth already FP64
+  float4 c, q;
+  double c0, c1, c2, z;
+};
+
+template <int WAVES, bool MEDIAN>
+struct BwdLds {
+  BwdEntry sm[WAVES > 1 ? 2 : 1][kBatchB];
+  uint32_t slot[WAVES > 1 ? 2 : 1][kBatchB];
+  alignas(16) double tot[WAVES][kBatchB][kNG];  // 4 colour / depth sums, 6 moments
+  uint64_t summed[WAVES];                       // the batch's entries the wave has sums for
+};
+
+template <int TW, int TH, int PIX, bool MEDIAN>
+__global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_kernel(
+    int n_tiles, int groups, const uint32_t* __restrict__ order, int n_frames,
+    const FrameDesc* __restrict__ frames, const uint2* __restrict__ ranges,
+    const uint32_t* __restrict__ vals, const Record* __restrict__ rec,
     const uint32_t* __restrict__ keyoff, const uint32_t* __restrict__ tile_nproc, float bg0,
     float bg1, float bg2, const float* __restrict__ g_rgb, const float* __restrict__ g_depth,
     const float* __restrict__ g_alpha, const float* __restrict__ t_final,
     const int32_t* __restrict__ n_last, float* __restrict__ partial,
-    uint32_t* __restrict__ stamp, const int32_t* __restrict__ med_pos) {
-  constexpr int PIX = TW * TH / kWave;
-  constexpr int RPP = kWave / TW;
+    uint32_t* __restrict__ stamp, const uint32_t* __restrict__ epoch_dev,
+    const int32_t* __restrict__ med_pos) {
+  using TB = TileBlocks<TW, TH>;
+  constexpr int WAVES = TB::kN / PIX;
+  // a wave's blocks: kCols x kRows neighbouring ones (whole rows of the tile,
+  // or a part of one row)
+  constexpr int kCols = PIX < TB::kX ? PIX : TB::kX, kRows = PIX / kCols;
+  static_assert(TB::kX % kCols == 0, "blocks of a wave form a rectangle");
+  __shared__ BwdLds<WAVES, MEDIAN> L;
+  const int tile = tile_of_block(blockIdx.x, n_tiles, groups, order);
+  if (tile < 0) return;
   const uint32_t nproc = tile_nproc[tile];
-  if (nproc == 0) return;
+  if (nproc == 0) return;  // uniform over the workgroup
+  const uint32_t epoch = *epoch_dev;
   const int f = frame_of_tile(frames, n_frames, tile);
   const FrameDesc fr = frames[f];
   const int lt = tile - fr.tile_offset;
   const int tx = lt % fr.grid_x, ty = lt / fr.grid_x;
-  const int x0 = tx * TW, y0 = ty * TH;
-  const int lane = threadIdx.x;
-  const int px = x0 + lane % TW;
-  const int ly = lane / TW;
-  // the key reduction leaves value min(lane >> 2, 9) on each quad (lanes
-  // 40..63 repeat value 9 and write nothing); the covariance sums carry
-  // twice the gradient (the 1/2 is a power of two: exact)
-  const int red_v = min(lane >> 2, kNG - 1);
-  const bool red_writer = (lane & 3) == 0 && (lane >> 2) < kNG;
-  const double red_scale = (red_v >= 2 && red_v <= 4) ? 0.5 : 1.0;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int blk0 = wave * PIX;
+  const int bx0 = tx * TW + (blk0 % TB::kX) * kBlk, by0 = ty * TH + (blk0 / TB::kX) * kBlk;
+  const int px0 = bx0 + (lane & 7), py0 = by0 + (lane >> 3);
   const uint2 rg = ranges[tile];
   const int64_t plane = (int64_t)fr.width * fr.height;
 
-  // per pixel: T_{i+1}; the transmittance seen behind the current entry
-  // (normalised by T_{i+1}); upstream gradients.  dL/da_i needs the upstream-
-  // weighted difference G . (c_i - B_i) between the entry's colour (and
-  // depth) and what is seen behind it, B_i.  That difference cancels on
-  // surfaces of uniform colour, and the gradient of a large Gaussian sums it
-  // over up to 10^5 pixels, so it is formed in FP64.  G is fixed per pixel,
-  // so the recursion B_i = B_{i+1} + a_i (c_i - B_{i+1}) carries over to the
-  // scalar E = G . B, which is what the pixel keeps (in FP64), together with
-  // G itself in FP64.
-  float T[PIX], BT[PIX];
+  // per pixel: T_{i+1} and the upstream gradients G.  dL/da_i = T_i G . (c_i -
+  // B_i), the upstream-weighted difference between the entry's colour, depth
+  // and alpha (which is 1) and what is seen behind it, B_i.  That difference
+  // cancels on surfaces of uniform colour, and the gradient of a large
+  // Gaussian sums it over up to 10^5 pixels, so it is formed in FP64.  G is
+  // fixed per pixel, so the recursion B_i = B_{i+1} + a_i (c_i - B_{i+1})
+  // carries over to the scalar E = G . B - G_A, which is what the pixel keeps
+  // (in FP64), together with G itself in FP64.
+  float T[PIX];
   double E[PIX], H0[PIX], H1[PIX], H2[PIX], HZ[PIX];
-  float G0[PIX], G1[PIX], G2[PIX], GD[PIX], GA[PIX];
-  int last[PIX];
-  // MEDIAN: the depth is the z of the entry at list position mp, so G_D
-  // reaches that entry's z only and no alpha
-  int mp[PIX];
+  int last[PIX], mp[PIX];  // mp: MEDIAN, the list position of the pixel's depth
+  uint32_t most[PIX];      // the block's longest walk (wave-uniform)
 #pragma unroll
   for (int k = 0; k < PIX; ++k) {
-    const int py = y0 + k * RPP + ly;
-    const bool valid = px < fr.width && py < fr.height;
-    const int64_t p = (int64_t)py * fr.width + px;
-    last[k] = valid ? n_last[fr.pixel_offset + p] : 0;
-    mp[k] = (MEDIAN && valid) ? med_pos[fr.pixel_offset + p] : -1;
-    T[k] = valid ? t_final[fr.pixel_offset + p] : 1.0f;
-    BT[k] = 1.0f;
-    const float* gi = g_rgb + 3 * fr.pixel_offset;
-    G0[k] = valid ? gi[p] : 0.0f;
-    G1[k] = valid ? gi[plane + p] : 0.0f;
-    G2[k] = valid ? gi[2 * plane + p] : 0.0f;
-    GD[k] = valid ? g_depth[fr.pixel_offset + p] : 0.0f;
-    GA[k] = valid ? g_alpha[fr.pixel_offset + p] : 0.0f;
-    H0[k] = G0[k]; H1[k] = G1[k]; H2[k] = G2[k];
-    HZ[k] = MEDIAN ? 0.0 : (double)GD[k];
-    // behind the last entry: the background colour at depth 0
-    E[k] = __builtin_fma(H2[k], (double)bg2, __builtin_fma(H1[k], (double)bg1, H0[k] * (double)bg0));
-  }
-  // Per-entry sums.  With p = a dL/da, dL/dq = -p/2: gu, gv carry
-  // sum(-p Q d), the gradient of the centre, and gS* carry
-  // sum(p (Q d)(Q d)^T), twice the gradient of the 2D covariance; the 1/2 is
-  // applied once per key (a power of two: exact).  A lane adds to them only
-  // past the alpha test, so they are still zero after an entry no lane
-  // blended, and are reset only after an entry that was reduced.  The empty
-  // asm hides the zeros from constant folding, so that they are set in place
-  // rather than rewritten on every branch of the first strip.
-  float gu = 0.f, gv = 0.f, gs = 0.f;
-  double gSxx = 0.0, gSxy = 0.0, gSyy = 0.0;
-  float gc0 = 0.f, gc1 = 0.f, gc2 = 0.f, gz = 0.f;
-  asm volatile("" : "+v"(gu), "+v"(gv), "+v"(gs), "+v"(gSxx), "+v"(gSxy), "+v"(gSyy),
-               "+v"(gc0), "+v"(gc1), "+v"(gc2), "+v"(gz));
-  for (int hi = (int)nproc; hi > 0; hi -= BATCH) {
-    const int lo = max(0, hi - BATCH);
-#pragma unroll
-    for (int i = lane; i < BATCH; i += kWave) {
-      if (lo + i < hi) {
-        const uint32_t r = vals[rg.x + lo + i];
-        const Record R = rec[r];
-        sm[i] = R;
-        const uint2 tr = trect[r];
-        const int rx0 = tr.x & 0xffff, rx1 = tr.x >> 16, ry0 = tr.y & 0xffff;
-        slot[i] = keyoff[r] + (uint32_t)((ty - ry0) * (rx1 - rx0 + 1) + (tx - rx0));
-      }
+    const int px = px0 + (k % kCols) * kBlk, py = py0 + (k / kCols) * kBlk;
+    T[k] = 1.0f;
+    E[k] = H0[k] = H1[k] = H2[k] = HZ[k] = 0.0;
+    last[k] = 0;
+    mp[k] = -1;
+    if (px < fr.width && py < fr.height) {
+      const int64_t p = (int64_t)py * fr.width + px, q = fr.pixel_offset + p;
+      const float* gi = g_rgb + 3 * fr.pixel_offset;
+      last[k] = n_last[q];
+      if (MEDIAN) mp[k] = med_pos[q];
+      T[k] = t_final[q];
+      H0[k] = gi[p];
+      H1[k] = gi[plane + p];
+      H2[k] = gi[2 * plane + p];
+      HZ[k] = g_depth[q];
+      // behind the last entry: the background colour at depth 0 and alpha 0
+      E[k] = __builtin_fma(H2[k], (double)bg2,
+                           __builtin_fma(H1[k], (double)bg1, H0[k] * (double)bg0)) -
+             (double)g_alpha[q];
     }
-    __syncthreads();
-    for (int j = hi - lo - 1; j >= 0; --j) {
+    int mx = last[k];
+    for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, kWave));
+    most[k] = __builtin_amdgcn_readfirstlane((uint32_t)mx);
+  }
+  // right operands: powers of Y by block row (k the row pair) and of X by
+  // block column, unit columns for the colours
+  double wy[kRows], wx[kCols], unit[4];
+  {
+    const int j = lane & 3, k = lane >> 4, b = (lane >> 2) & 3;
+    const auto power = [&](double v) {
+      return j == 0 ? 1.0 : j == 1 ? v : j == 2 ? v * v : 0.0;
+    };
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) wy[r] = power(by0 - ty * TH + r * kBlk + 2 * k + (b >> 1));
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) wx[c] = power(bx0 - tx * TW + c * kBlk + k + 4 * (b & 1));
+#pragma unroll
+    for (int c = 0; c < 4; ++c) unit[c] = j == c ? 1.0 : 0.0;
+  }
+  // lane 16 a + c of the result: moment Y^a X^c (c < 3), colour / depth sum a
+  // (c = 3); its place in a row of totals (negative: not used)
+  int out_v = -1;
+  {
+    const int c = lane & 3, a = lane >> 4;
+    if (!(lane & 12)) {
+      if (c == 3) out_v = a;
+      else if (a + c <= 2) out_v = 4 + (a == 0 ? c : a == 1 ? 3 + c : 5);
+    }
+  }
+  // colour / depth sums of the lane's pixels; reset after each entry that was
+  // reduced (a lane adds only past the alpha test)
+  double gc0 = 0.0, gc1 = 0.0, gc2 = 0.0, gz = 0.0;
+  asm volatile("" : "+v"(gc0), "+v"(gc1), "+v"(gc2), "+v"(gz));
+  // Batches of list entries from the back: [hi - kBatchB, hi).  The batch's
+  // record waits in registers, the next batch's list entry is loaded ahead.
+  int hi = (int)nproc, buf = 0;
+  Record R{};
+  uint32_t r_cur = 0, r_next = 0;
+  if (lane < hi) r_cur = vals[rg.x + max(0, hi - kBatchB) + lane];
+  if (lane < hi) R = rec[r_cur];
+  if (lane < hi - kBatchB) r_next = vals[rg.x + max(0, hi - 2 * kBatchB) + lane];
+  for (; hi > 0; hi -= kBatchB, buf ^= WAVES > 1) {
+    const int lo = max(0, hi - kBatchB);
+    const bool has = lane < hi - lo;
+    asm volatile("" ::"v"(R.reserved));  // as in the forward
+    uint64_t mk[PIX], in[PIX], any = 0;
+#pragma unroll
+    for (int k = 0; k < PIX; ++k) {
+      in[k] = 0;
+      if (has && (uint32_t)(lo + lane) < most[k])
+        in[k] = block_pixels<false>(R, bx0 + (k % kCols) * kBlk, by0 + (k / kCols) * kBlk);
+      mk[k] = __ballot(in[k] != 0);
+      any |= mk[k];
+    }
+    if (WAVES == 1 ? (any >> lane) & 1 : has && (lane & (WAVES - 1)) == wave) {
+      const Entry e = entry_of(R);
+      L.sm[buf][lane] = {e.c, e.q, R.c0, R.c1, R.c2, R.z};
+      // the record's tile rect, from its pixel bounds
+      const int rx0 = (int)(R.sqx & 0xffff) / TW, rx1 = (int)(R.sqx >> 16) / TW;
+      const int ry0 = (int)(R.sqy & 0xffff) / TH;
+      L.slot[buf][lane] = keyoff[r_cur] + (uint32_t)((ty - ry0) * (rx1 - rx0 + 1) + (tx - rx0));
+    }
+    r_cur = r_next;
+    if (lane < lo) R = rec[r_cur];
+    if (lane < lo - kBatchB) r_next = vals[rg.x + max(0, lo - 2 * kBatchB) + lane];
+    __syncthreads();  // (also: the previous batch's sums have been read)
+    uint64_t summed = 0;
+    while (any) {
+      const int j = 63 - __builtin_clzll(any);
+      any &= ~(1ull << j);
       const int pos = lo + j;
-      const Record& R = sm[j];
-      // The fields every pixel strip reads, loaded from LDS once per entry
-      // (read in each strip, they would be reloaded there with the address
-      // rebuilt each time).
-      float e_vhi = R.v_hi, e_vlo = R.v_lo, e_a1 = R.a1, e_a2 = R.a2, e_a3 = R.a3, e_op = R.opacity;
-      asm volatile("" : "+v"(e_vhi), "+v"(e_vlo), "+v"(e_a1), "+v"(e_a2), "+v"(e_a3), "+v"(e_op));
-      const int xlo = R.sqx & 0xffff, xhi = R.sqx >> 16;
-      const int ylo = R.sqy & 0xffff, yhi = R.sqy >> 16;
-      const bool xin = (unsigned)(px - xlo) <= (unsigned)(xhi - xlo);
-      const float dx = dx_of(R.u_hi, R.u_lo, px);
-      const float a1dx = e_a1 * dx;
-      const double c0 = R.c0, c1 = R.c1, c2 = R.c2, cz = R.z;
-      bool any = false;
+      const BwdEntry En = L.sm[buf][j];
+      // the block columns' a1 dx, the block rows' dy and (a3 dy)^2
+      float ax[kCols], dy[kRows], bb[kRows];
+#pragma unroll
+      for (int c = 0; c < kCols; ++c) ax[c] = En.q.x * dx_of(En.c.x, En.c.y, px0 + c * kBlk);
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) {
+        dy[r] = dx_of(En.c.z, En.c.w, py0 + r * kBlk);
+        const float b = En.q.z * dy[r];
+        bb[r] = b * b;
+      }
+      double my[kCols];  // sums over k of p Y^j, by block column
+#pragma unroll
+      for (int c = 0; c < kCols; ++c) {
+        my[c] = 0.0;
+        asm volatile("" : "+v"(my[c]));
+      }
+      uint64_t hit = 0;
 #pragma unroll
       for (int k = 0; k < PIX; ++k) {
-        const int row0 = y0 + k * RPP;
-        if (ylo > row0 + RPP - 1 || yhi < row0) continue;
-        const int py = row0 + ly;
-        if (pos >= last[k] || !xin || (unsigned)(py - ylo) > (unsigned)(yhi - ylo)) continue;
-        const float dy = dx_of(e_vhi, e_vlo, py);
-        const float q = q_of(e_a1, e_a2, e_a3, dx, dy);
-        const float g = gauss_of(q);
-        const float sg = e_op * g;
+        if (PIX > 1 && !((mk[k] >> j) & 1)) continue;  // block missed (uniform)
+        const float m = __builtin_fmaf(En.q.y, dy[k / kCols], ax[k % kCols]);
+        const float g = gauss_of(__builtin_fmaf(m, m, bb[k / kCols]));  // q_of
+        const float sg = En.q.w * g;
         const float a = fminf(kAlphaMax, sg);
-        if (a < kAlphaMin) continue;
-        const float om = 1.0f - a;
-        const float inv = __builtin_amdgcn_rcpf(om);
-        float Ti = T[k] * inv;
-        Ti = __builtin_fmaf(__builtin_fmaf(-Ti, om, T[k]), inv, Ti);  // Newton step
-        const float w = a * Ti;
-        // G . (c_i - B_i) = G . c_i - E
-        double gc = __builtin_fma(H2[k], c2, __builtin_fma(H1[k], c1, H0[k] * c0));
-        if (!MEDIAN) gc = __builtin_fma(HZ[k], cz, gc);
-        const double diff = gc - E[k];
-        // dL/da_i = T_i [G . (c_i - B_i) + G_A BT_i]
-        const float dLda = Ti * __builtin_fmaf(GA[k], BT[k], (float)diff);
-        gc0 += G0[k] * w;
-        gc1 += G1[k] * w;
-        gc2 += G2[k] * w;
-        if (MEDIAN)
-          gz += pos == mp[k] ? GD[k] : 0.0f;
-        else
-          gz += GD[k] * w;
-        // step the 'behind' state in front of entry i
-        E[k] = __builtin_fma((double)a, diff, E[k]);
-        BT[k] = BT[k] * om;
-        T[k] = Ti;
-        any = true;
-        if (sg > kAlphaMax) continue;  // clamped: alpha does not move
-        gs += dLda * g;
-        const float pa = a * dLda;
-        // Q d = L (L^T d), L^T d = (a1 dx + a2 dy, a3 dy)
-        const float m = __builtin_fmaf(e_a2, dy, a1dx);
-        const float b = e_a3 * dy;
-        const float qx = e_a1 * m;
-        const float qy = __builtin_fmaf(e_a2, m, e_a3 * b);
-        gu = __builtin_fmaf(-pa, qx, gu);
-        gv = __builtin_fmaf(-pa, qy, gv);
-        // Each pixel adds the rank-1 matrix p (Q d)(Q d)^T.  Formed in FP64
-        // its three entries stay exactly rank-1; rounded one by one in FP32
-        // they would not, and a Gaussian at the near plane has scale
-        // gradients that read the near-null direction of the summed matrix.
-        {
-          const double pd = pa, qxd = qx, qyd = qy;
-          const double t = pd * qxd;
-          gSxx = __builtin_fma(t, qxd, gSxx);
-          gSxy = __builtin_fma(t, qyd, gSxy);
-          gSyy = __builtin_fma(pd * qyd, qyd, gSyy);
+        const uint64_t act = __ballot(!(a < kAlphaMin)) & __ballot(pos < last[k]) &
+                             readlane64(in[k], j);
+        hit |= act;
+        float p = 0.0f;
+        if (__builtin_amdgcn_inverse_ballot_w64(act)) {
+          const float om = 1.0f - a;
+          const float inv = __builtin_amdgcn_rcpf(om);
+          float Ti = T[k] * inv;
+          Ti = __builtin_fmaf(__builtin_fmaf(-Ti, om, T[k]), inv, Ti);  // Newton step
+          const float w = a * Ti;
+          T[k] = Ti;
+          // G . (c_i - B_i) = G . c_i - E
+          double diff = __builtin_fma(H0[k], En.c0, -E[k]);
+          diff = __builtin_fma(H1[k], En.c1, diff);
+          diff = __builtin_fma(H2[k], En.c2, diff);
+          if (!MEDIAN) diff = __builtin_fma(HZ[k], En.z, diff);
+          // step the 'behind' state in front of entry i
+          E[k] = __builtin_fma((double)a, diff, E[k]);
+          const double wd = w;
+          gc0 = __builtin_fma(H0[k], wd, gc0);
+          gc1 = __builtin_fma(H1[k], wd, gc1);
+          gc2 = __builtin_fma(H2[k], wd, gc2);
+          if (MEDIAN)
+            gz += pos == mp[k] ? HZ[k] : 0.0;
+          else
+            gz = __builtin_fma(HZ[k], wd, gz);
+          // p = a dL/da; clamped: alpha does not move
+          p = sg > kAlphaMax ? 0.0f : w * (float)diff;
+        }
+        my[k % kCols] =
+            __builtin_amdgcn_mfma_f64_4x4x4f64((double)p, wy[k / kCols], my[k % kCols], 0, 0, 0);
+      }
+      if (hit == 0) continue;
+      double cs = __builtin_amdgcn_mfma_f64_4x4x4f64(gc0, unit[0], 0.0, 0, 0, 0);
+      cs = __builtin_amdgcn_mfma_f64_4x4x4f64(gc1, unit[1], cs, 0, 0, 0);
+      cs = __builtin_amdgcn_mfma_f64_4x4x4f64(gc2, unit[2], cs, 0, 0, 0);
+      cs = __builtin_amdgcn_mfma_f64_4x4x4f64(gz, unit[3], cs, 0, 0, 0);
+      double tot = __builtin_amdgcn_mfma_f64_4x4x4f64(my[0], wx[0], 0.0, 0, 0, 0);
+#pragma unroll
+      for (int c = 1; c < kCols; ++c)
+        tot = __builtin_amdgcn_mfma_f64_4x4x4f64(my[c], wx[c], tot, 0, 0, 0);
+      tot = __builtin_amdgcn_mfma_f64_4x4x4f64(cs, unit[3], tot, 0, 0, 0);
+      gc0 = gc1 = gc2 = gz = 0.0;
+      asm volatile("" : "+v"(gc0), "+v"(gc1), "+v"(gc2), "+v"(gz));
+      tot += dpp<kDppRowRor8>(tot);
+      tot += dpp<kDppRowRor4>(tot);
+      if (out_v >= 0) L.tot[wave][j][out_v] = tot;
+      summed |= 1ull << j;
+    }
+    if (lane == 0) L.summed[wave] = summed;
+    __syncthreads();
+    // one wave (in turn) finishes the batch's entries while the others go on
+    if (((nproc - hi) / kBatchB) % WAVES == (uint32_t)wave) {
+      double t[kNG];
+#pragma unroll
+      for (int v = 0; v < kNG; ++v) t[v] = 0.0;
+      bool any_sum = false;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) {
+        if (!((L.summed[w] >> lane) & 1)) continue;
+        any_sum = true;
+        const double2* src = reinterpret_cast<const double2*>(L.tot[w][lane]);
+#pragma unroll
+        for (int v = 0; v < kNG / 2; ++v) {
+          t[2 * v] += src[v].x;
+          t[2 * v + 1] += src[v].y;
         }
       }
-      if (__ballot(any) == 0) continue;
-      // The lanes' values of one key cancel against each other: sum them in
-      // FP64 (the key's total is stored as FP32; the per-record sum over its
-      // keys is FP64 again)
-      const double vals10[kNG] = {gu, gv, gSxx, gSxy, gSyy, gs, gc0, gc1, gc2, gz};
-      const double tot = lds_wave_sum<kNG>(red, vals10, lane);
-      gu = gv = gs = gc0 = gc1 = gc2 = gz = 0.f;
-      gSxx = gSxy = gSyy = 0.0;
-      asm volatile("" : "+v"(gu), "+v"(gv), "+v"(gs), "+v"(gSxx), "+v"(gSxy), "+v"(gSyy),
-                   "+v"(gc0), "+v"(gc1), "+v"(gc2), "+v"(gz));
-      const uint32_t sl = slot[j];
-      if (red_writer) partial[(size_t)sl * kNG + red_v] = (float)(tot * red_scale);
-      if (lane == 1) stamp[sl] = epoch;
+      if (any_sum) {
+        const BwdEntry& En = L.sm[buf][lane];
+        const double ux = ((double)En.c.x + En.c.y) - tx * TW;
+        const double uy = ((double)En.c.z + En.c.w) - ty * TH;
+        const double a1 = En.q.x, a2 = En.q.y, a3 = En.q.z;
+        const double P = t[4], Px = t[5], Pxx = t[6], Py = t[7], Pxy = t[8], Pyy = t[9];
+        const double sx = ux * P - Px, sy = uy * P - Py;  // sums of p dx, p dy
+        const double sxx = ux * (sx - Px) + Pxx, syy = uy * (sy - Py) + Pyy;
+        const double sxy = uy * sx - ux * Py + Pxy;
+        const double ym = a1 * sxy + a2 * syy;
+        const uint32_t sl = L.slot[buf][lane];
+        float2* out = reinterpret_cast<float2*>(partial + (size_t)sl * kNG);
+        out[0] = make_float2((float)(a1 * sx + a2 * sy), (float)(a3 * sy));
+        out[1] = make_float2((float)(a1 * (a1 * sxx + a2 * sxy) + a2 * ym), (float)(a3 * ym));
+        out[2] = make_float2((float)(a3 * a3 * syy), (float)(P / En.q.w));
+        out[3] = make_float2((float)t[0], (float)t[1]);
+        out[4] = make_float2((float)t[2], (float)t[3]);
+        stamp[sl] = epoch;
+      }
     }
-    __syncthreads();
+    if (WAVES == 1) __syncthreads();
   }
-}
-
-template <int TW, int TH, bool MEDIAN, int BATCH>
-__global__ void __launch_bounds__(64, (TW * TH <= 256) ? 4 : 1) composite_bwd_kernel(
-    int n_tiles, int groups, const uint32_t* __restrict__ order, int n_frames,
-    const FrameDesc* __restrict__ frames, const uint2* __restrict__ ranges,
-    const uint32_t* __restrict__ vals, const Record* __restrict__ rec,
-    const uint2* __restrict__ trect, const uint32_t* __restrict__ keyoff,
-    const uint32_t* __restrict__ tile_nproc, float bg0, float bg1, float bg2,
-    const float* __restrict__ g_rgb, const float* __restrict__ g_depth,
-    const float* __restrict__ g_alpha, const float* __restrict__ t_final,
-    const int32_t* __restrict__ n_last, float* __restrict__ partial,
-    uint32_t* __restrict__ stamp, const uint32_t* __restrict__ epoch_dev,
-    const int32_t* __restrict__ med_pos) {
-  __shared__ Record sm[BATCH];
-  __shared__ uint32_t slot[BATCH];
-  __shared__ double red[kNG * kRedValue];
-  const int tile = tile_of_block(blockIdx.x, n_tiles, groups, order);
-  if (tile < 0) return;
-  const uint32_t epoch = *epoch_dev;
-  composite_bwd_tile<TW, TH, MEDIAN, BATCH>(tile, sm, slot, red, epoch, n_frames, frames, ranges, vals, rec,
-                                     trect, keyoff, tile_nproc, bg0, bg1, bg2, g_rgb, g_depth,
-                                     g_alpha, t_final, n_last, partial, stamp, med_pos);
 }
 
 static void launch_order(hipStream_t st, int n_tiles, int groups, const uint32_t* nproc,
@@ -532,46 +628,30 @@ static void launch_fwd_t(hipStream_t st, int n_tiles, int groups, const uint32_t
   else go(composite_fwd_kernel<TW, TH, false, false>);
 }
 
-template <int TW, int TH, int BATCH>
-static void launch_bwd_b(hipStream_t st, int n_tiles, int groups, const uint32_t* order, int F,
-                         const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
-                         const Record* rec, const uint2* trect, const uint32_t* keyoff,
+template <int TW, int TH, int PIX>
+static void launch_bwd_t(hipStream_t st, int pix, int n_tiles, int groups, const uint32_t* order,
+                         int F, const FrameDesc* frames, const uint2* ranges,
+                         const uint32_t* vals, const Record* rec, const uint32_t* keyoff,
                          const uint32_t* nproc, const float* bg, const float* g_rgb,
                          const float* g_depth, const float* g_alpha, const float* t_final,
                          const int32_t* n_last, float* partial, uint32_t* stamp,
                          const uint32_t* epoch, const int32_t* med_pos) {
-  if (med_pos) {
-    auto k = composite_bwd_kernel<TW, TH, true, BATCH>;
-    hipLaunchKernelGGL(k, dim3(grid_of(n_tiles, groups)), dim3(kWave), 0, st, n_tiles,
-                       groups, order, F, frames, ranges, vals, rec, trect, keyoff, nproc,
-                       bg[0], bg[1], bg[2], g_rgb, g_depth, g_alpha, t_final, n_last, partial,
-                       stamp, epoch, med_pos);
-  } else {
-    auto k = composite_bwd_kernel<TW, TH, false, BATCH>;
-    hipLaunchKernelGGL(k, dim3(grid_of(n_tiles, groups)), dim3(kWave), 0, st, n_tiles,
-                       groups, order, F, frames, ranges, vals, rec, trect, keyoff, nproc,
-                       bg[0], bg[1], bg[2], g_rgb, g_depth, g_alpha, t_final, n_last, partial,
-                       stamp, epoch, med_pos);
+  if constexpr (PIX > 1) {
+    if (pix < PIX) {
+      launch_bwd_t<TW, TH, PIX / 2>(st, pix, n_tiles, groups, order, F, frames, ranges, vals, rec,
+                                    keyoff, nproc, bg, g_rgb, g_depth, g_alpha, t_final, n_last,
+                                    partial, stamp, epoch, med_pos);
+      return;
+    }
   }
-}
-
-template <int TW, int TH>
-static void launch_bwd_t(hipStream_t st, int batch, int n_tiles, int groups,
-                         const uint32_t* order, int F, const FrameDesc* frames,
-                         const uint2* ranges, const uint32_t* vals, const Record* rec,
-                         const uint2* trect, const uint32_t* keyoff, const uint32_t* nproc,
-                         const float* bg, const float* g_rgb, const float* g_depth,
-                         const float* g_alpha, const float* t_final, const int32_t* n_last,
-                         float* partial, uint32_t* stamp, const uint32_t* epoch,
-                         const int32_t* med_pos) {
-#define GSR_BWD_B(B)                                                                           \
-  launch_bwd_b<TW, TH, B>(st, n_tiles, groups, order, F, frames, ranges, vals, rec, trect,     \
-                          keyoff, nproc, bg, g_rgb, g_depth, g_alpha, t_final, n_last,         \
-                          partial, stamp, epoch, med_pos)
-  if (batch == 32) GSR_BWD_B(32);
-  else if (batch == 128) GSR_BWD_B(128);
-  else GSR_BWD_B(64);
-#undef GSR_BWD_B
+  const auto go = [&](auto* k) {
+    hipLaunchKernelGGL(k, dim3(grid_of(n_tiles, groups)), dim3(TW * TH / PIX), 0, st, n_tiles,
+                       groups, order, F, frames, ranges, vals, rec, keyoff, nproc, bg[0], bg[1],
+                       bg[2], g_rgb, g_depth, g_alpha, t_final, n_last, partial, stamp, epoch,
+                       med_pos);
+  };
+  if (med_pos) go(composite_bwd_kernel<TW, TH, PIX, true>);
+  else go(composite_bwd_kernel<TW, TH, PIX, false>);
 }
 
 void launch_composite_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
@@ -594,10 +674,10 @@ void launch_composite_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
 #undef GSR_FWD
 }
 
-void launch_composite_bwd(hipStream_t st, int tw, int th, int batch, int n_tiles, int F,
+void launch_composite_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
-                          const Record* rec, const uint2* trect, const uint32_t* keyoff,
-                          const uint32_t* nproc, const float* bg, const float* g_rgb,
+                          const Record* rec, const uint32_t* keyoff, const uint32_t* nproc,
+                          const float* bg, const float* g_rgb,
                           const float* g_depth, const float* g_alpha, const float* t_final,
                           const int32_t* n_last, float* partial, uint32_t* stamp,
                           const uint32_t* epoch, uint32_t* order, bool xcd_groups,
@@ -605,10 +685,19 @@ void launch_composite_bwd(hipStream_t st, int tw, int th, int batch, int n_tiles
   if (n_tiles <= 0) return;
   const int groups = xcd_groups ? kQueues : 1;
   launch_order(st, n_tiles, groups, nproc, order);
-#define GSR_BWD(W, H)                                                                          \
-  launch_bwd_t<W, H>(st, batch, n_tiles, groups, order, F, frames, ranges, vals, rec, trect,   \
-                     keyoff, nproc, bg, g_rgb, g_depth, g_alpha, t_final, n_last, partial,     \
-                     stamp, epoch, med_pos)
+  // Blocks per wave: as many as leave kBwdMinWaves waves (four per SIMD).  More
+  // blocks per wave share an entry's overhead and its reduction, fewer keep the
+  // SIMDs busy when there are few tiles.  Measured with 1 / 2 / 4 blocks (us):
+  // 8 x 1200x680 (25,800 tiles of 16x16) 2802 / 2148 / 1806; 4 x 640x480
+  // (4,800) 610 / 487 / 440; 1 x 640x480 (1,200) 233 / 244 / 314; 2 x 131x97
+  // (126) 83 / 110 / 155; 7,800 tiles of 32x16 1522 / 1036 / 923.
+  const int blocks = tw * th / kWave;
+  int pix = 4;
+  while (pix > 1 && (int64_t)n_tiles * blocks / pix < kBwdMinWaves) pix /= 2;
+#define GSR_BWD(W, H)                                                                            \
+  launch_bwd_t<W, H, std::min(4, TileBlocks<W, H>::kN)>(                                         \
+      st, pix, n_tiles, groups, order, F, frames, ranges, vals, rec, keyoff, nproc, bg, g_rgb,    \
+      g_depth, g_alpha, t_final, n_last, partial, stamp, epoch, med_pos)
   if (tw == 16 && th == 16) GSR_BWD(16, 16);
   else if (tw == 8 && th == 8) GSR_BWD(8, 8);
   else if (tw == 32 && th == 8) GSR_BWD(32, 8);

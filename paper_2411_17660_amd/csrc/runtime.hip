@@ -618,11 +618,10 @@ gsr_status gsr_backward(gsr_context* ctx, const float* g_rgb, const float* g_dep
   // A8 reverse compositing -> per-key partials
   {
     StageTimer t(ctx, st, timing, GSR_STAGE_COMPOSITE_BWD);
-    launch_composite_bwd(st, s.tile_w, s.tile_h, s.lds_batch ? s.lds_batch : kWave, (int)sv.T,
-                         sv.F, P<FrameDesc>(ctx->frames),
+    launch_composite_bwd(st, s.tile_w, s.tile_h, (int)sv.T, sv.F,
+                         P<FrameDesc>(ctx->frames),
                          P<uint2>(ctx->ranges), svals, P<Record>(ctx->rec),
-                         P<uint2>(ctx->trect), P<uint32_t>(ctx->keyoff),
-                         P<uint32_t>(ctx->nproc), s.background, g_rgb,
+                         P<uint32_t>(ctx->keyoff), P<uint32_t>(ctx->nproc), s.background, g_rgb,
                          g_depth, g_alpha,
                          P<float>(ctx->t_final), P<int32_t>(ctx->n_last),
                          P<float>(ctx->partial), P<uint32_t>(ctx->stamp), d_epoch,
@@ -653,6 +652,7 @@ gsr_status gsr_backward(gsr_context* ctx, const float* g_rgb, const float* g_dep
     launch_wide_boundary(st, M, P<uint32_t>(cls_in_b ? ctx->cls_b : ctx->cls_a), first_wide);
     launch_preprocess_bwd(st, sv.n, sv.F, P<FrameDesc>(ctx->frames), sv.poses, sv.means,
                           sv.log_scales, sv.quats, sv.opac, sv.sh, s.sh_degree,
+                          P<Record>(ctx->rec),
                           P<uint32_t>(cls_in_b ? ctx->clsv_b : ctx->clsv_a), first_wide,
                           P<uint32_t>(ctx->keyoff), P<uint32_t>(ctx->ntiles), P<float>(ctx->partial),
                           P<uint32_t>(ctx->stamp), d_epoch, ctx->key_cap,
@@ -864,7 +864,6 @@ gsr_status gsr_autotune(gsr_context* ctx, const gsr_settings* base, int64_t n, c
                         int32_t reps, int32_t force, gsr_settings* chosen, float* ms_out,
                         void* stream) {
   static const int kShapes[GSR_TUNE_TILES][2] = {{16, 16}, {8, 8}, {32, 8}, {16, 8}, {32, 16}};
-  static const int kBatches[GSR_TUNE_BATCHES] = {32, 64, 128};
   constexpr int kConfigs = GSR_TUNE_TILES * GSR_TUNE_BATCHES;
   if (!ctx || !base || !chosen || !cams || F < 1) return GSR_ERR_INVALID_ARGUMENT;
   if (reps < 1) reps = 1;
@@ -905,8 +904,6 @@ gsr_status gsr_autotune(gsr_context* ctx, const gsr_settings* base, int64_t n, c
   GSR_HIP(hipEventCreate(&e1));
   float best = 1e30f;
   gsr_settings best_s = *base;
-  float tuned[kConfigs];
-  for (int i = 0; i < kConfigs; ++i) tuned[i] = 1e30f;
   for (int i = 0; i < GSR_TUNE_TILES && !rc; ++i) {
     gsr_settings s = *base;
     s.tile_w = kShapes[i][0];
@@ -914,48 +911,36 @@ gsr_status gsr_autotune(gsr_context* ctx, const gsr_settings* base, int64_t n, c
     s.lds_batch = kWave;
     s.key_capacity = 0;
     s.flags &= ~(uint32_t)(GSR_FLAG_TIMING | GSR_FLAG_COUNT_PAIRS);
-    // one sizing run per tile shape (the keys do not depend on the batch)
+    // one sizing run per tile shape
     rc = gsr_step_l1(ctx, &s, n, means, log_scales, quats, opac, sh, F, cams, poses, target_rgb,
                      target_depth, depth_weight, rgb, depth, alpha, loss, gm, gl, gq, go, gsh, gt,
                      stream);
     if (rc) break;
     s.key_capacity = (int64_t)(ctx->s.K + ctx->s.K / 20 + 1024);
-    for (int j = 0; j < GSR_TUNE_BATCHES && !rc; ++j) {
-      s.lds_batch = kBatches[j];
-      std::vector<float> t(reps);
-      for (int r = 0; r < reps && !rc; ++r) {
-        GSR_HIP(hipEventRecord(e0, st));
-        rc = gsr_step_l1(ctx, &s, n, means, log_scales, quats, opac, sh, F, cams, poses,
-                         target_rgb, target_depth, depth_weight, rgb, depth, alpha, loss, gm, gl,
-                         gq, go, gsh, gt, stream);
-        GSR_HIP(hipEventRecord(e1, st));
-        GSR_HIP(hipEventSynchronize(e1));
-        GSR_HIP(hipEventElapsedTime(&t[r], e0, e1));
-      }
-      if (rc) break;
-      if ((rc = gsr_check_overflow(ctx, stream))) break;
-      std::sort(t.begin(), t.end());
-      const float med = t[reps / 2];
-      tuned[i * GSR_TUNE_BATCHES + j] = med;
-      if (ms_out) ms_out[i * GSR_TUNE_BATCHES + j] = med;
-      if (med < best) {
-        best = med;
-        best_s = s;
-      }
+    std::vector<float> t(reps);
+    for (int r = 0; r < reps && !rc; ++r) {
+      GSR_HIP(hipEventRecord(e0, st));
+      rc = gsr_step_l1(ctx, &s, n, means, log_scales, quats, opac, sh, F, cams, poses,
+                       target_rgb, target_depth, depth_weight, rgb, depth, alpha, loss, gm, gl,
+                       gq, go, gsh, gt, stream);
+      GSR_HIP(hipEventRecord(e1, st));
+      GSR_HIP(hipEventSynchronize(e1));
+      GSR_HIP(hipEventElapsedTime(&t[r], e0, e1));
+    }
+    if (rc) break;
+    if ((rc = gsr_check_overflow(ctx, stream))) break;
+    std::sort(t.begin(), t.end());
+    const float med = t[reps / 2];
+    // the time does not depend on lds_batch
+    for (int j = 0; ms_out && j < GSR_TUNE_BATCHES; ++j) ms_out[i * GSR_TUNE_BATCHES + j] = med;
+    if (med < best) {
+      best = med;
+      best_s = s;
     }
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc) return rc;
-  // within 1% of the fastest batch on the fastest shape, keep the default
-  // batch: the batches give bitwise-identical results, and differences that
-  // small are run-to-run noise
-  for (int i = 0; i < GSR_TUNE_TILES; ++i) {
-    if (kShapes[i][0] != best_s.tile_w || kShapes[i][1] != best_s.tile_h) continue;
-    for (int j = 0; j < GSR_TUNE_BATCHES; ++j)
-      if (kBatches[j] == kWave && tuned[i * GSR_TUNE_BATCHES + j] <= 1.01f * best)
-        best_s.lds_batch = kWave;
-  }
   ctx->s.valid = false;  // the scratch outputs are not the caller's
   *chosen = best_s;
   ctx->tune_cache[key] = best_s;

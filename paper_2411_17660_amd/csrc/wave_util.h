@@ -51,7 +51,8 @@ __device__ __forceinline__ double swap_sum(double a, double b) {
 
 // The value of v on a partner lane inside the lane's 16-lane row: DPP row
 // mirror (partner 15 - l) for lane bit 3, half-row mirror (7 - l) for bit 2,
-// quad permutes (l ^ 2, l ^ 1) for bits 1 and 0.  The mirrors also flip the
+// quad permutes (l ^ 2, l ^ 1) for bits 1 and 0.  A row rotation by 8 is
+// l ^ 8, and one by 4 after it completes the sum over lane bits 3 and 2.  The mirrors also flip the
 // lower lane bits; the rounds that follow sum over those anyway.
 template <int CTRL>
 __device__ __forceinline__ double dpp(double v) {
@@ -63,7 +64,7 @@ __device__ __forceinline__ double dpp(double v) {
                                                          true);
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
-constexpr int kDppRowMirror = 0x140, kDppHalfMirror = 0x141, kDppQuadXor2 = 0x4e,
+constexpr int kDppRowRor8 = 0x128, kDppRowRor4 = 0x124, kDppRowMirror = 0x140, kDppHalfMirror = 0x141, kDppQuadXor2 = 0x4e,
               kDppQuadXor1 = 0xb1;
 
 // Sum over the wave of N <= 16 FP64 values per lane through LDS: every

@@ -264,8 +264,9 @@ class Rasterizer:
     def autotune(self, means, log_scales, quats, opacity, sh, poses, cams, sh_degree,
                  target_rgb, target_depth, depth_weight, background=(0.0, 0.0, 0.0), reps=3,
                  force=False):
-        """Measure every tile shape with every LDS batch on these inputs;
-        returns (tile, lds_batch, key_capacity, {(tile, batch): median ms})."""
+        """Measure every tile shape on these inputs; returns (tile, lds_batch,
+        key_capacity, {(tile, batch): median ms}), the time of a tile shape
+        under each lds_batch, on which it does not depend."""
         base = native.make_settings(sh_degree, background)
         chosen = native.Settings()
         nt, nbt = len(native.TILE_SHAPES), len(native.LDS_BATCHES)
