@@ -41,3 +41,28 @@ def test_blocks_match_oracle(rast, size, tile, median):
             sc.log_scales = np.ascontiguousarray(ls, np.float32)
         ref, _, flags = check_forward(rast, sc, tile=tile, label=label, median=median)
         check_backward(rast, sc, ref, flags, n, label=label)
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("size", [(40, 30), (785, 689), (1030, 1025)])
+def test_nonfinite_upstream_stays_in_its_channel(rast, size, bad):
+    """A red upstream gradient that is not finite at some pixels leaves the
+    green and blue SH gradients and the gradients of Gaussians that reach none
+    of those pixels bitwise as they are without it (the sums over pixels are
+    matrix products, whose zeros must not meet it)."""
+    from gpu_util import gpu_backward, gpu_forward
+    W, H = size
+    sc = scenes.tiny_scene(seed=5, n=150, W=W, H=H, f=0.7 * max(W, H), sh_degree=1,
+                           ls_mean=-2.6, ls_sigma=0.5)
+    G = [np.array(x) for x in scenes.upstream(6, sc)]
+    gpu_forward(rast, sc)
+    good = gpu_backward(rast, G)
+    py, px = H // 2, W // 2
+    G[0][py * W + px:py * W + px + 3] = bad
+    gpu_forward(rast, sc)
+    got = gpu_backward(rast, G)
+    assert np.array_equal(good["sh"][:, :, 1:], got["sh"][:, :, 1:])
+    hit = ~np.isfinite(got["means"]).all(1)
+    assert hit.any() and not hit.all()
+    for k in ("means", "log_scales", "quats", "opacity", "sh"):
+        assert np.array_equal(good[k][~hit], got[k][~hit]), k
