@@ -139,8 +139,9 @@ void launch_mcmc_relocate(hipStream_t st, int64_t n, int ksh3, float* means, flo
 // The compositing tile schedule (raster.hip): `order` lists the tiles group
 // by group, longest first by `nproc` (entries a previous pass processed per
 // tile; spatial order if NULL); launch tile_schedule_grid() workgroups.
+// clear [n_tiles] (may be nproc; NULL: none) is zeroed.
 void launch_tile_order(hipStream_t st, int n_tiles, int groups, const uint32_t* nproc,
-                       uint32_t* order);
+                       uint32_t* order, uint32_t* clear = nullptr);
 unsigned tile_schedule_grid(int n_tiles, int groups);
 int tile_schedule_groups(bool xcd_groups);
 
@@ -171,7 +172,7 @@ void launch_surfel_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                        uint32_t* order, bool xcd_groups, unsigned long long* pairs);
 void launch_surfel_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                        const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
-                       const void* rec, const uint2* trect, const uint32_t* keyoff,
+                       const void* rec, const uint32_t* keyoff,
                        const float* bg, const float* g_rgb, const float* g_depth,
                        const float* g_alpha, const float* g_normal, const float* g_dist,
                        const float* t_final, const int32_t* n_last, const float* dist_aux,

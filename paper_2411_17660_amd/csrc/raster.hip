@@ -110,56 +110,18 @@ __global__ void __launch_bounds__(1024) tile_order_kernel(int n_tiles, int group
   }
 }
 
-// Pixel blocks.  A tile of TW x TH pixels is cut into 8 x 8 blocks, one pixel
-// per lane (lane l owns pixel (l % 8, l / 8) of a block).  A square block has
-// the smallest perimeter of 64 pixels, so the fewest Gaussians touch it.
-constexpr int kBlk = 8;
-
-template <int TW, int TH>
-struct TileBlocks {
-  static constexpr int kX = TW / kBlk, kY = TH / kBlk, kN = kX * kY;
-};
-
-// The pixels of the 8 x 8 block at (bx, by) inside an entry's pixel bounds, one
-// bit per lane: 0 where the block's part inside the bounds cannot reach
-// alpha >= 1/255, by the least q = (a1 dx + a2 dy)^2 + (a3 dy)^2 over it
-// against cull_r^2 (q where alpha reaches 1/255, and a margin).  Each lane
-// asks this of its own record, so 64 entries cost one evaluation.  q is
-// convex with its minimum at d = 0: over the half-plane beyond the block side
-// nearest to 0 it is least at dy = -a1 a2 x / (a2^2 + a3^2), so over the block
-// it is least in the row nearest to that dy, where m = a1 dx + a2 dy runs over
-// an interval.  Conservative: cull_r holds a margin of 1e-3 and the threshold
-// grows by 4e-6 (64 FP32 ulps) of the largest terms that can cancel in m, far
-// above the rounding of this test and of q_of, so a pixel of a part that
-// fails it has a computed alpha < 1/255 and the images do not change.  NaN
-// keeps the block.  ALL: the bounds alone.
+// block_lanes with the entry's ellipse: 0 where the block's part inside its
+// bounds cannot reach alpha >= 1/255 (least_q against cull_r^2, q where alpha
+// reaches 1/255, with a margin).  ALL: the bounds alone.
 template <bool ALL>
 __device__ __forceinline__ uint64_t block_pixels(const Record& R, int bx, int by) {
-  const int xlo = max(bx, (int)(R.sqx & 0xffff)), xhi = min(bx + kBlk - 1, (int)(R.sqx >> 16));
-  const int ylo = max(by, (int)(R.sqy & 0xffff)), yhi = min(by + kBlk - 1, (int)(R.sqy >> 16));
-  if (xlo > xhi || ylo > yhi) return 0;
-  const float dxl = dx_of(R.u_hi, R.u_lo, xhi), dxh = dx_of(R.u_hi, R.u_lo, xlo);
-  const float dyl = dx_of(R.v_hi, R.v_lo, yhi), dyh = dx_of(R.v_hi, R.v_lo, ylo);
-  const float xn = __builtin_amdgcn_fmed3f(0.0f, dxl, dxh);
-  const float ys = -(R.a1 * R.a2 * xn) * __builtin_amdgcn_rcpf(R.a2 * R.a2 + R.a3 * R.a3);
-  const float yc = __builtin_amdgcn_fmed3f(ys, dyl, dyh);
-  const float m = __builtin_amdgcn_fmed3f(0.0f, R.a1 * dxl + R.a2 * yc, R.a1 * dxh + R.a2 * yc);
-  const float b = R.a3 * yc;
-  const float big = R.a1 * fmaxf(fabsf(dxl), fabsf(dxh)) +
-                    (fabsf(R.a2) + R.a3) * fmaxf(fabsf(dyl), fabsf(dyh));
+  const BlockPart b = block_part(R.sqx, R.sqy, bx, by);
+  if (b.empty()) return 0;
+  float big;
+  const float q = least_q(R.a1, R.a2, R.a3, R.u_hi, R.u_lo, R.v_hi, R.v_lo, b, big);
   const float r = R.cull_r + 4e-6f * big;
-  if (!ALL && m * m + b * b > r * r) return 0;
-  const uint32_t cols = (0xffu >> (kBlk - 1 - (xhi - xlo))) << (xlo - bx);
-  const uint64_t rows = (~0ull >> (kBlk * (kBlk - 1 - (yhi - ylo)))) << (kBlk * (ylo - by));
-  const uint32_t c4 = cols * 0x01010101u;
-  return (((uint64_t)c4 << 32) | c4) & rows;
-}
-
-// lane j's value of v (j wave-uniform)
-__device__ __forceinline__ uint64_t readlane64(uint64_t v, int j) {
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), j);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, j);
-  return ((uint64_t)hi << 32) | lo;
+  if (!ALL && q > r * r) return 0;
+  return block_lanes(b, bx, by);
 }
 
 // The entry fields that the compositing reads per pixel, staged in LDS.
@@ -622,8 +584,8 @@ static unsigned grid_of(int n_tiles, int groups) {
 }
 
 void launch_tile_order(hipStream_t st, int n_tiles, int groups, const uint32_t* nproc,
-                       uint32_t* order) {
-  if (n_tiles > 0) launch_order(st, n_tiles, groups, nproc, order);
+                       uint32_t* order, uint32_t* clear) {
+  if (n_tiles > 0) launch_order(st, n_tiles, groups, nproc, order, clear);
 }
 
 unsigned tile_schedule_grid(int n_tiles, int groups) { return grid_of(n_tiles, groups); }

@@ -558,7 +558,7 @@ gsr_status gsr_backward_surfel(gsr_context* ctx, const float* g_rgb, const float
   {
     StageTimer t(ctx, st, timing, GSR_STAGE_COMPOSITE_BWD);
     launch_surfel_bwd(st, s.tile_w, s.tile_h, (int)sv.T, sv.F, P<FrameDesc>(ctx->frames),
-                      P<uint2>(ctx->ranges), svals, ctx->rec.p, P<uint2>(ctx->trect),
+                      P<uint2>(ctx->ranges), svals, ctx->rec.p,
                       P<uint32_t>(ctx->keyoff), s.background, g_rgb, g_depth, g_alpha, g_normal,
                       g_dist, P<float>(ctx->t_final), P<int32_t>(ctx->n_last),
                       P<float>(ctx->dist_aux), P<float>(ctx->spart), P<uint32_t>(ctx->stamp),

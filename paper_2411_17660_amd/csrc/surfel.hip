@@ -40,14 +40,17 @@ namespace gsr {
 
 namespace {
 
-struct Surfel {  // 96 bytes: six 16-byte loads
+struct alignas(16) Surfel {  // 96 bytes: six 16-byte loads
   float m2x, m2y, zc, kux;  // M2 = (m2x, m2y, zc); k_u = (kux, kuy, 0)
   float kuy, kvx, kvy, cxh;  // k_v = (kvx, kvy, 0); centre x hi
   float cxl, cyh, cyl, opacity;
   float c0, c1, c2, n0;      // colour, normal
   float n1, n2;
   uint32_t sqx, sqy;         // pixel box, lo | hi << 16
-  float reserved[4];
+  // where alpha can reach 1/255: |(e1 dx + e2 dy, e3 dy)| <= 1 (the disk's
+  // image, widened to be centred on c; zeros: the whole box) or within the
+  // low-pass radius, squared
+  float e1, e2, e3, low;
 };
 static_assert(sizeof(Surfel) == 96, "surfel record layout");
 
@@ -175,7 +178,42 @@ __global__ void __launch_bounds__(256) surfel_preprocess_kernel(
     s.n2 = (float)(sgn * tw[2]);
     s.sqx = (uint32_t)x_lo | ((uint32_t)x_hi << 16);
     s.sqy = (uint32_t)y_lo | ((uint32_t)y_hi << 16);
-    s.reserved[0] = s.reserved[1] = s.reserved[2] = s.reserved[3] = 0.0f;
+    s.e1 = s.e2 = s.e3 = 0.0f;
+    s.low = (float)(0.5 * r2) * 1.0001f + 1e-3f;
+    {
+      // The disk's image {x : (x - x_e)^T S^-1 (x - x_e) <= 1} from the dual
+      // conic, taken around c instead: |L^T (x - c)| <= 1 + |L^T (x_e - c)|
+      // holds inside it (S^-1 = L L^T).  Only where the per-pixel FP32
+      // intersection resolves the boundary to well under the 2 % the block
+      // test adds: the boundary maps to disk coordinates with a stretch of at
+      // most ((1 + h)/(1 - h))^2 for h = r_a |(M2_0, M2_1)| / M2_2 <= 1/2, and
+      // an error of ~16 ulps of the largest products over p2 (which is linear
+      // in the pixel) and r_a stays below 1e-4.
+      const double c01 = r2 * (M0[0] * M1[0] + M0[1] * M1[1]) - M0[2] * M1[2];
+      const double i22 = 1.0 / c22;
+      const double sxx = dx * i22 * i22, syy = dy * i22 * i22;
+      const double sxy = (c02 * c12 - c01 * c22) * i22 * i22;
+      const double det = sxx * syy - sxy * sxy;
+      const double kux = ccx * M2[0] - M0[0], kuy = ccx * M2[1] - M0[1];
+      const double kvx = ccy * M2[0] - M1[0], kvy = ccy * M2[1] - M1[1];
+      const double X = fmax(ccx - lox, hix - ccx) + 1.0, Y = fmax(ccy - loy, hiy - ccy) + 1.0;
+      const double hux = X * fabs(M2[0]) + fabs(kux), huy = X * fabs(M2[1]) + fabs(kuy);
+      const double hvx = Y * fabs(M2[0]) + fabs(kvx), hvy = Y * fabs(M2[1]) + fabs(kvy);
+      const double p2 = fabs(kux * kvy - kuy * kvx) - X * fabs(M2[0] * kvy - M2[1] * kvx) -
+                        Y * fabs(kux * M2[1] - kuy * M2[0]);
+      const double big = hux * hvy + huy * hvx +
+                         M2[2] * (huy * Y + X * hvy + hux * Y + X * hvx) / ra;
+      if (det > 1e-6 * sxx * syy && p2 > 0.0 && big < 100.0 * p2 &&
+          ra * sqrt(M2[0] * M2[0] + M2[1] * M2[1]) < 0.5 * M2[2]) {
+        const double a1 = sqrt(syy / det), a2 = -sxy / sqrt(syy * det), a3 = 1.0 / sqrt(syy);
+        const double ox = c02 * i22 - ccx, oy = c12 * i22 - ccy;
+        const double m = a1 * ox + a2 * oy, b = a3 * oy;
+        const double w = 1.0 / (1.0 + sqrt(m * m + b * b));
+        s.e1 = (float)(a1 * w);
+        s.e2 = (float)(a2 * w);
+        s.e3 = (float)(a3 * w);
+      }
+    }
     rec[r] = s;
   }
 }
@@ -184,7 +222,7 @@ __global__ void __launch_bounds__(256) surfel_preprocess_kernel(
 struct SurfelHit {
   float Gh, z;
   bool obj;       // the disk term (not the low-pass) is the larger
-  float u, v, ip2, hux, huy, huz, hvx, hvy, hvz, ex, ey;  // kept for the backward
+  float u, v, hux, huy, huz, hvx, hvy, hvz, ex, ey;  // kept for the backward
 };
 
 // ln 255 rounded up: beyond this squared distance from the centre the
@@ -231,18 +269,14 @@ __device__ __forceinline__ SurfelHit surfel_eval(const SurfelEntry& e, int py) {
   const float p0 = h.huy * h.hvz - h.huz * h.hvy;
   const float p1 = h.huz * h.hvx - h.hux * h.hvz;
   const float p2 = h.hux * h.hvy - h.huy * h.hvx;
-  float G = 0.0f;
-  h.u = 0.0f;
-  h.v = 0.0f;
-  h.ip2 = 0.0f;
-  if (p2 != 0.0f) {
-    // reciprocal with one Newton step (within an ulp or so of 1/p2)
-    const float r0 = __builtin_amdgcn_rcpf(p2);
-    h.ip2 = __builtin_fmaf(__builtin_fmaf(-p2, r0, 1.0f), r0, r0);
-    h.u = p0 * h.ip2;
-    h.v = p1 * h.ip2;
-    G = gauss_of(h.u * h.u + h.v * h.v);
-  }
+  // reciprocal with one Newton step (within an ulp or so of 1/p2); a ray in the
+  // disk's plane (p2 = 0) leaves the low-pass alone: with G = 0, alpha is set by
+  // the low-pass or is 0, and u, v are not used
+  const float r0 = __builtin_amdgcn_rcpf(p2);
+  const float ip2 = __builtin_fmaf(__builtin_fmaf(-p2, r0, 1.0f), r0, r0);
+  h.u = p0 * ip2;
+  h.v = p1 * ip2;
+  const float G = p2 != 0.0f ? gauss_of(h.u * h.u + h.v * h.v) : 0.0f;
   const float d2 = h.ex * h.ex + h.ey * h.ey;
   const float Glp = d2 < kLowpassReach ? gauss_of(2.0f * d2) : 0.0f;
   h.obj = G >= Glp;
@@ -251,10 +285,70 @@ __device__ __forceinline__ SurfelHit surfel_eval(const SurfelEntry& e, int py) {
   return h;
 }
 
-// COUNT: also count the evaluated (pixel, entry) pairs, those whose box
-// test passes before the pixel stops (one atomic add per tile).
+// The pixels of the 8 x 8 block at (bx, by) inside the surfel's box, one bit per
+// lane; 0 where the block's part of the box cannot reach alpha >= 1/255.  ALL:
+// the box alone.
+template <bool ALL>
+__device__ __forceinline__ uint64_t block_pixels(const Surfel& S, int bx, int by) {
+  const BlockPart b = block_part(S.sqx, S.sqy, bx, by);
+  if (b.empty()) return 0;
+  if (!ALL) {
+    float big;
+    const float q = least_q(S.e1, S.e2, S.e3, S.cxh, S.cxl, S.cyh, S.cyl, b, big);
+    const float r = 1.02f + 4e-6f * big;
+    const float nx = __builtin_amdgcn_fmed3f(0.0f, dx_of(S.cxh, S.cxl, b.xhi),
+                                             dx_of(S.cxh, S.cxl, b.xlo));
+    const float ny = __builtin_amdgcn_fmed3f(0.0f, dx_of(S.cyh, S.cyl, b.yhi),
+                                             dx_of(S.cyh, S.cyl, b.ylo));
+    if (q > r * r && nx * nx + ny * ny > S.low) return 0;
+  }
+  return block_lanes(b, bx, by);
+}
+
+// A surfel staged in LDS for the forward: the record's fields up to the normal,
+// then the block's pixels inside the box and one past the list position.
+// (Assigned field by field: a copy of the whole record would go through scratch
+// memory.)
+struct alignas(16) FwdSurfel {
+  float4 v0, v1, v2, v3;  // as Surfel
+  float n1, n2;
+  uint32_t px_lo, px_hi, pos;
+  __device__ __forceinline__ void set(const Surfel& S, uint64_t in, uint32_t at) {
+    v0 = make_float4(S.m2x, S.m2y, S.zc, S.kux);
+    v1 = make_float4(S.kuy, S.kvx, S.kvy, S.cxh);
+    v2 = make_float4(S.cxl, S.cyh, S.cyl, S.opacity);
+    v3 = make_float4(S.c0, S.c1, S.c2, S.n0);
+    n1 = S.n1;
+    n2 = S.n2;
+    px_lo = (uint32_t)in;
+    px_hi = (uint32_t)(in >> 32);
+    pos = at;
+  }
+  __device__ __forceinline__ uint64_t lanes() const {
+    return ((uint64_t)__builtin_amdgcn_readfirstlane(px_hi) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane(px_lo);
+  }
+  __device__ __forceinline__ Surfel record() const {
+    Surfel S;
+    S.m2x = v0.x; S.m2y = v0.y; S.zc = v0.z; S.kux = v0.w;
+    S.kuy = v1.x; S.kvx = v1.y; S.kvy = v1.z; S.cxh = v1.w;
+    S.cxl = v2.x; S.cyh = v2.y; S.cyl = v2.z; S.opacity = v2.w;
+    S.c0 = v3.x; S.c1 = v3.y; S.c2 = v3.z; S.n0 = v3.w;
+    S.n1 = n1; S.n2 = n2;
+    return S;
+  }
+};
+
+// One wave composites one 8 x 8 block, a pixel per lane, as the 3D forward
+// does: each lane culls its own record of a batch of 64 against the block
+// (records loaded while the batch before them is composited) and the ones that
+// reach it are packed into LDS in list order.  What bounds it: VALU issue; one
+// wave per 16 x 16 tile took 1383 us on 250k surfels over 4 x 1200x680 and 526
+// us on 20k over one 321x243 frame, this takes 976 and 87 us.  COUNT: also count the evaluated
+// (pixel, entry) pairs, those whose box test passes before the pixel stops
+// (one atomic add per block).
 template <int TW, int TH, bool COUNT>
-__global__ void __launch_bounds__(64) surfel_fwd_kernel(
+__global__ void __launch_bounds__(kWave) surfel_fwd_kernel(
     int n_tiles, int groups, const uint32_t* __restrict__ order, uint32_t* __restrict__ tile_nproc,
     unsigned long long* __restrict__ pair_count,
     int n_frames, const FrameDesc* __restrict__ frames, const uint2* __restrict__ ranges,
@@ -262,125 +356,117 @@ __global__ void __launch_bounds__(64) surfel_fwd_kernel(
     float bg2, float* __restrict__ rgb, float* __restrict__ depth, float* __restrict__ alpha,
     float* __restrict__ normal, float* __restrict__ dist, float* __restrict__ t_final,
     int32_t* __restrict__ n_last, float* __restrict__ dist_aux /* [P][4]: z_ref, A, D_1, D_2 */) {
-  constexpr int PIX = TW * TH / kWave;
-  constexpr int RPP = kWave / TW;
-  __shared__ Surfel sm[kWave];
-  const int tile = tile_of_block(blockIdx.x, n_tiles, groups, order);
+  using TB = TileBlocks<TW, TH>;
+  __shared__ FwdSurfel sm[kWave + 2];
+  const int group = blockIdx.x % groups, i_wg = blockIdx.x / groups;
+  const int tile = tile_of_block((i_wg / TB::kN) * groups + group, n_tiles, groups, order);
   if (tile < 0) return;
+  const int blk = i_wg % TB::kN;
   const int f = frame_of_tile(frames, n_frames, tile);
   const FrameDesc fr = frames[f];
   const int lt = tile - fr.tile_offset;
-  const int x0 = (lt % fr.grid_x) * TW, y0 = (lt / fr.grid_x) * TH;
+  const int bx = (lt % fr.grid_x) * TW + (blk % TB::kX) * kBlk;
+  const int by = (lt / fr.grid_x) * TH + (blk / TB::kX) * kBlk;
   const int lane = threadIdx.x;
-  const int px = x0 + lane % TW;
-  const int ly = lane / TW;
+  const int px = bx + (lane & 7), py = by + (lane >> 3);
   const uint2 rg = ranges[tile];
-  float T[PIX], C0[PIX], C1[PIX], C2[PIX], D[PIX], N0[PIX], N1[PIX], N2[PIX];
+  float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, D = 0.0f, N0 = 0.0f, N1 = 0.0f, N2 = 0.0f;
   // distortion sums in FP64: the backward's weights e_i = A z_i^2 -
   // 2 z_i D_1 + D_2 and z_i A - D_1 cancel where the entries lie at one
   // depth, which FP32 sums over hundreds of entries cannot resolve
-  float ZR[PIX];
-  double SA[PIX], S1[PIX], S2[PIX], DS[PIX];
-  int last[PIX];
-  bool done[PIX];
-  uint32_t hits = 0;
-#pragma unroll
-  for (int k = 0; k < PIX; ++k) {
-    T[k] = 1.0f;
-    C0[k] = C1[k] = C2[k] = D[k] = N0[k] = N1[k] = N2[k] = 0.0f;
-    ZR[k] = 0.0f;
-    SA[k] = S1[k] = S2[k] = DS[k] = 0.0;
-    last[k] = 0;
-    const int py = y0 + k * RPP + ly;
-    done[k] = !(px < fr.width && py < fr.height);
+  float ZR = 0.0f;
+  double SA = 0.0, S1 = 0.0, S2 = 0.0, DS = 0.0;
+  uint32_t last = 0;
+  uint64_t open = __ballot(px < fr.width && py < fr.height);  // pixels that have not stopped
+  uint64_t hits = 0;
+  const auto blend = [&](const FwdSurfel& F) {
+    const Surfel S = F.record();
+    const uint64_t lanes = F.lanes() & open;
+    if (COUNT) hits += __popcll(lanes);
+    const SurfelEntry en = surfel_entry(S, px);
+    const SurfelHit h = surfel_eval(en, py);
+    const float a = fminf(kAlphaMax, en.opacity * h.Gh);
+    const float Tn = T * (1.0f - a);
+    uint64_t act = __ballot(!(a < kAlphaMin)) & lanes;
+    const uint64_t stop = __ballot(Tn < kTMin) & act;
+    open &= ~stop;
+    act &= ~stop;
+    if (__builtin_amdgcn_inverse_ballot_w64(act)) {
+      const float w = a * T;
+      C0 += S.c0 * w;
+      C1 += S.c1 * w;
+      C2 += S.c2 * w;
+      D += h.z * w;
+      N0 += S.n0 * w;
+      N1 += S.n1 * w;
+      N2 += S.n2 * w;
+      if (last == 0) ZR = h.z;
+      const double zp = h.z - ZR, wd = w;
+      DS += wd * (SA * zp * zp - 2.0 * zp * S1 + S2);
+      SA += wd;
+      S1 += wd * zp;
+      S2 += wd * zp * zp;
+      T = Tn;
+      last = F.pos;
+    }
+  };
+  // the batch's record in registers and the next batch's list entry; lanes past
+  // the list's end read the list's first entry again
+  const auto entry = [&](uint32_t e) { return e < rg.y ? vals[e] : vals[rg.x]; };
+  Surfel R;
+  uint32_t v_next = 0;
+  if (rg.x < rg.y) {
+    R = rec[entry(rg.x + lane)];
+    v_next = entry(rg.x + kWave + lane);
   }
-  for (uint32_t b = rg.x; b < rg.y; b += kWave) {
-    bool live = false;
-#pragma unroll
-    for (int k = 0; k < PIX; ++k) live |= !done[k];
-    if (__ballot(live) == 0) break;
-    const uint32_t e = b + lane;
-    if (e < rg.y) sm[lane] = rec[vals[e]];
+  for (uint32_t b = rg.x; b < rg.y && open; b += kWave) {
+    uint64_t in = 0;
+    if (b + lane < rg.y) in = block_pixels<COUNT>(R, bx, by);
+    const uint64_t mk = __ballot(in != 0);
+    const int n = __popcll(mk);
+    const int at = __builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0u));
+    if (in) sm[at].set(R, in, b + lane + 1 - rg.x);
+    if (lane < 2) sm[n + lane].px_lo = sm[n + lane].px_hi = 0u;  // (entries are taken in pairs)
+    R = rec[v_next];
+    v_next = entry(b + 2 * kWave + lane);
     __syncthreads();
-    const int cnt = (int)min((uint32_t)kWave, rg.y - b);
-    for (int j = 0; j < cnt; ++j) {
-      const Surfel& S = sm[j];
-      const int xlo = S.sqx & 0xffff, xhi = S.sqx >> 16;
-      const int ylo = S.sqy & 0xffff, yhi = S.sqy >> 16;
-      const bool xin = (unsigned)(px - xlo) <= (unsigned)(xhi - xlo);
-      const SurfelEntry en = surfel_entry(S, px);
-#pragma unroll
-      for (int k = 0; k < PIX; ++k) {
-        const int row0 = y0 + k * RPP;
-        if (ylo > row0 + RPP - 1 || yhi < row0) continue;
-        const int py = row0 + ly;
-        if (done[k] || !xin || (unsigned)(py - ylo) > (unsigned)(yhi - ylo)) continue;
-        if (COUNT) ++hits;
-        const SurfelHit h = surfel_eval(en, py);
-        const float a = fminf(kAlphaMax, en.opacity * h.Gh);
-        if (a < kAlphaMin) continue;
-        const float Tn = T[k] * (1.0f - a);
-        if (Tn < kTMin) {
-          done[k] = true;
-          continue;
-        }
-        const float w = a * T[k];
-        C0[k] += S.c0 * w;
-        C1[k] += S.c1 * w;
-        C2[k] += S.c2 * w;
-        D[k] += h.z * w;
-        N0[k] += S.n0 * w;
-        N1[k] += S.n1 * w;
-        N2[k] += S.n2 * w;
-        if (last[k] == 0) ZR[k] = h.z;
-        const double zp = h.z - ZR[k], wd = w;
-        DS[k] += wd * (SA[k] * zp * zp - 2.0 * zp * S1[k] + S2[k]);
-        SA[k] += wd;
-        S1[k] += wd * zp;
-        S2[k] += wd * zp * zp;
-        T[k] = Tn;
-        last[k] = (int)(b + j + 1 - rg.x);
-      }
+    FwdSurfel E0 = sm[0];
+    for (int i = 0; i < n && open; i += 2) {
+      const FwdSurfel E1 = sm[i + 1];
+      blend(E0);
+      E0 = sm[i + 2];
+      blend(E1);
     }
     __syncthreads();
   }
   // the tile's walk length for the backward and the next schedule: the
   // largest list position any of its pixels blended
-  int most = 0;
-#pragma unroll
-  for (int k = 0; k < PIX; ++k) most = last[k] > most ? last[k] : most;
-  for (int o = 32; o > 0; o >>= 1) {
-    const int m = __shfl_xor(most, o, kWave);
-    most = m > most ? m : most;
+  int most = (int)last;
+  for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, kWave));
+  if (lane == 0) {
+    if (TB::kN == 1) tile_nproc[tile] = (uint32_t)most;
+    else if (most > 0) atomicMax(&tile_nproc[tile], (uint32_t)most);  // cleared by the order kernel
   }
-  if (lane == 0) tile_nproc[tile] = (uint32_t)most;
-  if (COUNT) {
-    unsigned long long c = hits;
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, kWave);
-    if (lane == 0) atomicAdd(pair_count, c);
-  }
-  const int64_t plane = (int64_t)fr.width * fr.height;
-#pragma unroll
-  for (int k = 0; k < PIX; ++k) {
-    const int py = y0 + k * RPP + ly;
-    if (px < fr.width && py < fr.height) {
-      const int64_t p = (int64_t)py * fr.width + px;
-      float* img = rgb + 3 * fr.pixel_offset;
-      img[p] = C0[k] + T[k] * bg0;
-      img[plane + p] = C1[k] + T[k] * bg1;
-      img[2 * plane + p] = C2[k] + T[k] * bg2;
-      float* nm = normal + 3 * fr.pixel_offset;
-      nm[p] = N0[k];
-      nm[plane + p] = N1[k];
-      nm[2 * plane + p] = N2[k];
-      depth[fr.pixel_offset + p] = D[k];
-      alpha[fr.pixel_offset + p] = 1.0f - T[k];
-      t_final[fr.pixel_offset + p] = T[k];
-      n_last[fr.pixel_offset + p] = last[k];
-      dist[fr.pixel_offset + p] = (float)DS[k];
-      float4* ax = reinterpret_cast<float4*>(dist_aux) + (fr.pixel_offset + p);
-      *ax = make_float4(ZR[k], (float)SA[k], (float)S1[k], (float)S2[k]);
-    }
+  if (COUNT && lane == 0) atomicAdd(pair_count, (unsigned long long)hits);
+  if (px < fr.width && py < fr.height) {
+    const int64_t plane = (int64_t)fr.width * fr.height;
+    const int64_t p = (int64_t)py * fr.width + px;
+    float* img = rgb + 3 * fr.pixel_offset;
+    img[p] = C0 + T * bg0;
+    img[plane + p] = C1 + T * bg1;
+    img[2 * plane + p] = C2 + T * bg2;
+    float* nm = normal + 3 * fr.pixel_offset;
+    nm[p] = N0;
+    nm[plane + p] = N1;
+    nm[2 * plane + p] = N2;
+    depth[fr.pixel_offset + p] = D;
+    alpha[fr.pixel_offset + p] = 1.0f - T;
+    t_final[fr.pixel_offset + p] = T;
+    n_last[fr.pixel_offset + p] = (int32_t)last;
+    dist[fr.pixel_offset + p] = (float)DS;
+    float4* ax = reinterpret_cast<float4*>(dist_aux) + (fr.pixel_offset + p);
+    *ax = make_float4(ZR, (float)SA, (float)S1, (float)S2);
   }
 }
 
@@ -397,54 +483,76 @@ __global__ void __launch_bounds__(64) surfel_fwd_kernel(
 // opacity, colour[3], normal[3].
 constexpr int kSG = 16;
 
-template <int TW, int TH>
-__global__ void __launch_bounds__(64) surfel_bwd_kernel(
+//
+// A workgroup takes a tile with WAVES waves of PIX 8 x 8 blocks each, as the 3D
+// backward does; the 16 values are summed over a wave's lanes by FP64 matrix
+// products (v_mfma_f64_4x4x4, whose operand and result lanes raster.hip
+// states): four values at a time over lane bits 5 and 4 into the columns of
+// one result, the four results over lane bits 1 and 0 into the columns of
+// another, two row rotations for the remaining bits.  What bounds it: VALU
+// issue (~190 instructions a visit, half of them FP64).  One wave per tile and
+// a reduction through LDS took 3810 us on 250k surfels over 4 x 1200x680 and
+// 843 us on 20k over one 321x243 frame; this takes 3436 and 316 us.
+constexpr int kBatchB = 64;          // list entries per batch
+constexpr int kBwdMinWaves = 4096;  // four waves on each of the 1,024 SIMDs
+
+template <int WAVES>
+struct BwdLds {
+  Surfel sm[WAVES > 1 ? 2 : 1][kBatchB];
+  uint32_t slot[WAVES > 1 ? 2 : 1][kBatchB];
+  double tot[WAVES > 1 ? WAVES : 1][WAVES > 1 ? kBatchB : 1][kSG];
+  uint64_t summed[WAVES];  // the batch's entries the wave has sums for
+};
+
+template <int TW, int TH, int PIX>
+__global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
     int n_tiles, int groups, const uint32_t* __restrict__ order,
     const uint32_t* __restrict__ tile_nproc,
     int n_frames, const FrameDesc* __restrict__ frames, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ vals, const Surfel* __restrict__ rec,
-    const uint2* __restrict__ trect, const uint32_t* __restrict__ keyoff, float bg0, float bg1,
+    const uint32_t* __restrict__ keyoff, float bg0, float bg1,
     float bg2, const float* __restrict__ g_rgb, const float* __restrict__ g_depth,
     const float* __restrict__ g_alpha, const float* __restrict__ g_normal,
     const float* __restrict__ g_dist, const float* __restrict__ t_final,
     const int32_t* __restrict__ n_last, const float* __restrict__ dist_aux,
     float* __restrict__ partial, uint32_t* __restrict__ stamp,
     const uint32_t* __restrict__ epoch_dev) {
-  constexpr int PIX = TW * TH / kWave;
-  constexpr int RPP = kWave / TW;
-  __shared__ Surfel sm[kWave];
-  __shared__ uint32_t slot[kWave];
-  __shared__ double red[kSG * kRedValue];  // the per-key reduction
+  using TB = TileBlocks<TW, TH>;
+  constexpr int WAVES = TB::kN / PIX;
+  constexpr int kCols = PIX < TB::kX ? PIX : TB::kX;
+  static_assert(TB::kX % kCols == 0, "blocks of a wave form a rectangle");
+  __shared__ BwdLds<WAVES> L;
   const int tile = tile_of_block(blockIdx.x, n_tiles, groups, order);
   if (tile < 0) return;
-  const int most = (int)tile_nproc[tile];
-  if (most == 0) return;
+  const int nproc = (int)tile_nproc[tile];
+  if (nproc == 0) return;  // uniform over the workgroup
   const uint32_t epoch = *epoch_dev;
   const int f = frame_of_tile(frames, n_frames, tile);
   const FrameDesc fr = frames[f];
   const int lt = tile - fr.tile_offset;
   const int tx = lt % fr.grid_x, ty = lt / fr.grid_x;
-  const int x0 = tx * TW, y0 = ty * TH;
-  const int lane = threadIdx.x;
-  const int px = x0 + lane % TW;
-  const int ly = lane / TW;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int blk0 = wave * PIX;
+  const int bx0 = tx * TW + (blk0 % TB::kX) * kBlk, by0 = ty * TH + (blk0 / TB::kX) * kBlk;
   const uint2 rg = ranges[tile];
   const int64_t plane = (int64_t)fr.width * fr.height;
-  // per pixel: T_{i+1}, the totals of the distortion sums, and the
-  // transmittance seen behind the current entry (normalised by T_{i+1}).
-  // dL/da_i takes the upstream-weighted difference G . (v_i - B_i) between
-  // the entry's values (colour, depth, normal, distortion weight e) and
-  // those seen behind it; it cancels where neighbouring surfels agree, so it
-  // is formed in FP64.  G is fixed per pixel, so the recursion
-  // B_i = B_{i+1} + a_i (v_i - B_{i+1}) carries over to the scalar E = G . B,
-  // which the pixel keeps (FP64) together with G in FP64.
-  float T[PIX], BT[PIX], AT[PIX], ZR[PIX], S1[PIX], S2[PIX];
+  // per pixel: T_{i+1} and the totals of the distortion sums.  dL/da_i takes
+  // the upstream-weighted difference G . (v_i - B_i) between the entry's
+  // values (colour, depth, normal, distortion weight e, alpha 1) and those
+  // seen behind it; it cancels where neighbouring surfels agree, so it is
+  // formed in FP64.  G is fixed per pixel, so the recursion
+  // B_i = B_{i+1} + a_i (v_i - B_{i+1}) carries over to the scalar
+  // E = G . B - G_A, which the pixel keeps (FP64) together with G in FP64.
+  float T[PIX], AT[PIX], ZR[PIX], S1[PIX], S2[PIX];
   double E[PIX], H0[PIX], H1[PIX], H2[PIX], HD[PIX], HN0[PIX], HN1[PIX], HN2[PIX], HE[PIX];
-  float G0[PIX], G1[PIX], G2[PIX], GD[PIX], GA[PIX], GN0[PIX], GN1[PIX], GN2[PIX], GE[PIX];
   int last[PIX];
+  int most[PIX];     // the block's longest walk (wave-uniform)
+  bool odd = false;  // a pixel's upstream gradient is not finite
 #pragma unroll
   for (int k = 0; k < PIX; ++k) {
-    const int py = y0 + k * RPP + ly;
+    const int px = bx0 + (k % kCols) * kBlk + (lane & 7);
+    const int py = by0 + (k / kCols) * kBlk + (lane >> 3);
     const bool valid = px < fr.width && py < fr.height;
     const int64_t p = (int64_t)py * fr.width + px;
     const int64_t q = fr.pixel_offset + p;
@@ -456,96 +564,124 @@ __global__ void __launch_bounds__(64) surfel_bwd_kernel(
     AT[k] = ax.y;
     S1[k] = ax.z;
     S2[k] = ax.w;
-    BT[k] = 1.0f;
     const float* gi = g_rgb + 3 * fr.pixel_offset;
     const float* gn = g_normal + 3 * fr.pixel_offset;
-    G0[k] = valid ? gi[p] : 0.0f;
-    G1[k] = valid ? gi[plane + p] : 0.0f;
-    G2[k] = valid ? gi[2 * plane + p] : 0.0f;
-    GN0[k] = valid ? gn[p] : 0.0f;
-    GN1[k] = valid ? gn[plane + p] : 0.0f;
-    GN2[k] = valid ? gn[2 * plane + p] : 0.0f;
-    GD[k] = valid ? g_depth[q] : 0.0f;
-    GA[k] = valid ? g_alpha[q] : 0.0f;
-    GE[k] = valid ? g_dist[q] : 0.0f;
-    H0[k] = G0[k]; H1[k] = G1[k]; H2[k] = G2[k]; HD[k] = GD[k];
-    HN0[k] = GN0[k]; HN1[k] = GN1[k]; HN2[k] = GN2[k]; HE[k] = GE[k];
-    // behind the last entry: the background colour, zero depth, normal and e
-    E[k] = __builtin_fma(H2[k], (double)bg2, __builtin_fma(H1[k], (double)bg1, H0[k] * (double)bg0));
+    H0[k] = valid ? gi[p] : 0.0f;
+    H1[k] = valid ? gi[plane + p] : 0.0f;
+    H2[k] = valid ? gi[2 * plane + p] : 0.0f;
+    HN0[k] = valid ? gn[p] : 0.0f;
+    HN1[k] = valid ? gn[plane + p] : 0.0f;
+    HN2[k] = valid ? gn[2 * plane + p] : 0.0f;
+    HD[k] = valid ? g_depth[q] : 0.0f;
+    HE[k] = valid ? g_dist[q] : 0.0f;
+    const double ha = valid ? g_alpha[q] : 0.0f;
+    odd |= !isfinite(H0[k] + H1[k] + H2[k] + HN0[k] + HN1[k] + HN2[k] + HD[k] + HE[k]);
+    // behind the last entry: the background colour, zero depth, normal, e and
+    // alpha (less G_A, the share of every entry's alpha of 1 in G . v_i)
+    E[k] = __builtin_fma(H2[k], (double)bg2,
+                         __builtin_fma(H1[k], (double)bg1, H0[k] * (double)bg0)) -
+           ha;
+    int mx = last[k];
+    for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, kWave));
+    most[k] = __builtin_amdgcn_readfirstlane(mx);
   }
-  // Per-entry sums: the lane's own pixels sum in FP32; the lanes' sums,
-  // which cancel against each other, in FP64.  A lane adds to them only past
+  odd = __ballot(odd) != 0;  // (wave-uniform)
+  double unit[4];  // right operands: unit columns
+#pragma unroll
+  for (int c = 0; c < 4; ++c) unit[c] = (lane & 3) == c ? 1.0 : 0.0;
+  // lane 16 c + g of the last product holds value 4 g + c
+  const int out_v = lane & 12 ? -1 : 4 * (lane & 3) + (lane >> 4);
+  // Per-entry sums over the lane's pixels, FP64.  A lane adds to them only past
   // the alpha test, so they are still zero after an entry no lane blended
   // and are reset only after an entry that was reduced (the empty asm keeps
-  // the zeros from being rewritten on every branch of the first strip).
-  float acc[kSG];
+  // the zeros from being rewritten on every branch of the first block).
+  double acc[kSG];
 #pragma unroll
   for (int i = 0; i < kSG; ++i) {
-    acc[i] = 0.0f;
+    acc[i] = 0.0;
     asm volatile("" : "+v"(acc[i]));
   }
-  for (int hi = most; hi > 0; hi -= kWave) {
-    const int lo = hi > kWave ? hi - kWave : 0;
-    if (lo + lane < hi) {
-      const uint32_t r = vals[rg.x + lo + lane];
-      sm[lane] = rec[r];
-      const uint2 tr = trect[r];
-      const int rx0 = tr.x & 0xffff, rx1 = tr.x >> 16, ry0 = tr.y & 0xffff;
-      slot[lane] = keyoff[r] + (uint32_t)((ty - ry0) * (rx1 - rx0 + 1) + (tx - rx0));
-    }
-    __syncthreads();
-    for (int j = hi - lo - 1; j >= 0; --j) {
-      const int pos = lo + j;
-      const Surfel& S = sm[j];
-      const int xlo = S.sqx & 0xffff, xhi = S.sqx >> 16;
-      const int ylo = S.sqy & 0xffff, yhi = S.sqy >> 16;
-      const bool xin = (unsigned)(px - xlo) <= (unsigned)(xhi - xlo);
-      const SurfelEntry en = surfel_entry(S, px);
-      bool any = false;
+  // Batches of list entries from the back: [hi - kBatchB, hi).  The batch's
+  // list entry is loaded ahead.
+  int hi = nproc, buf = 0;
+  uint32_t r_cur = 0;
+  if (lane < hi) r_cur = vals[rg.x + max(0, hi - kBatchB) + lane];
+  for (; hi > 0; hi -= kBatchB, buf ^= WAVES > 1) {
+    const int lo = max(0, hi - kBatchB);
+    const bool has = lane < hi - lo;
+    uint64_t mk[PIX], in[PIX], any = 0;
+    {
+      const Surfel R = rec[r_cur];  // (lanes past the batch: a record all the same)
 #pragma unroll
       for (int k = 0; k < PIX; ++k) {
-        const int row0 = y0 + k * RPP;
-        if (ylo > row0 + RPP - 1 || yhi < row0) continue;
-        const int py = row0 + ly;
-        if (pos >= last[k] || !xin || (unsigned)(py - ylo) > (unsigned)(yhi - ylo)) continue;
+        in[k] = 0;
+        if (has && lo + lane < most[k])
+          in[k] = block_pixels<false>(R, bx0 + (k % kCols) * kBlk, by0 + (k / kCols) * kBlk);
+        mk[k] = __ballot(in[k] != 0);
+        any |= mk[k];
+      }
+      if (WAVES == 1 ? (any >> lane) & 1 : has && (lane & (WAVES - 1)) == wave) {
+        L.sm[buf][lane] = R;
+        // the record's tile rect, from its pixel bounds
+        const int rx0 = (int)(R.sqx & 0xffff) / TW, rx1 = (int)(R.sqx >> 16) / TW;
+        const int ry0 = (int)(R.sqy & 0xffff) / TH;
+        L.slot[buf][lane] = keyoff[r_cur] + (uint32_t)((ty - ry0) * (rx1 - rx0 + 1) + (tx - rx0));
+      }
+    }
+    if (lane < lo) r_cur = vals[rg.x + max(0, lo - kBatchB) + lane];
+    __syncthreads();  // (also: the previous batch's sums have been read)
+    uint64_t summed = 0;
+    while (any) {
+      const int j = 63 - __builtin_clzll(any);
+      any &= ~(1ull << j);
+      const int pos = lo + j;
+      const Surfel& S = L.sm[buf][j];
+      uint64_t hit = 0;
+#pragma unroll
+      for (int k = 0; k < PIX; ++k) {
+        if (PIX > 1 && !((mk[k] >> j) & 1)) continue;  // block missed (uniform)
+        const int px = bx0 + (k % kCols) * kBlk + (lane & 7);
+        const int py = by0 + (k / kCols) * kBlk + (lane >> 3);
+        const SurfelEntry en = surfel_entry(S, px);
         const SurfelHit h = surfel_eval(en, py);
         const float sg = en.opacity * h.Gh;
         const float a = fminf(kAlphaMax, sg);
-        if (a < kAlphaMin) continue;
+        const uint64_t act = __ballot(!(a < kAlphaMin)) & __ballot(pos < last[k]) &
+                             readlane64(in[k], j);
+        hit |= act;
+        if (!__builtin_amdgcn_inverse_ballot_w64(act)) continue;
         const float om = 1.0f - a;
         const float inv = __builtin_amdgcn_rcpf(om);
         float Ti = T[k] * inv;
         Ti = __builtin_fmaf(__builtin_fmaf(-Ti, om, T[k]), inv, Ti);  // Newton step
         const float w = a * Ti;
+        const double wd = w;
+        T[k] = Ti;
         const double zp = h.z - ZR[k];
         // dDist/dw_i: sum over the other entries m of w_m (z_i - z_m)^2
         const double e = AT[k] * zp * zp - 2.0 * zp * S1[k] + S2[k];
         // G . (v_i - B_i) = G . v_i - E
-        double gv = H0[k] * (double)S.c0;
-        gv = __builtin_fma(H1[k], (double)S.c1, gv);
-        gv = __builtin_fma(H2[k], (double)S.c2, gv);
-        gv = __builtin_fma(HD[k], (double)h.z, gv);
-        gv = __builtin_fma(HN0[k], (double)S.n0, gv);
-        gv = __builtin_fma(HN1[k], (double)S.n1, gv);
-        gv = __builtin_fma(HN2[k], (double)S.n2, gv);
-        gv = __builtin_fma(HE[k], e, gv);
-        const double diff = gv - E[k];
-        const float dLda = Ti * __builtin_fmaf(GA[k], BT[k], (float)diff);
-        acc[10] += G0[k] * w;
-        acc[11] += G1[k] * w;
-        acc[12] += G2[k] * w;
-        acc[13] += GN0[k] * w;
-        acc[14] += GN1[k] * w;
-        acc[15] += GN2[k] * w;
-        // dL/dz_i: the depth map and the distortion, 2 w_i sum_m w_m (z_i - z_m)
-        const float dzv = w * (GD[k] + (float)(2.0 * GE[k] * (zp * AT[k] - S1[k])));
+        double diff = __builtin_fma(H0[k], (double)S.c0, -E[k]);
+        diff = __builtin_fma(H1[k], (double)S.c1, diff);
+        diff = __builtin_fma(H2[k], (double)S.c2, diff);
+        diff = __builtin_fma(HD[k], (double)h.z, diff);
+        diff = __builtin_fma(HN0[k], (double)S.n0, diff);
+        diff = __builtin_fma(HN1[k], (double)S.n1, diff);
+        diff = __builtin_fma(HN2[k], (double)S.n2, diff);
+        diff = __builtin_fma(HE[k], e, diff);
+        const float dLda = Ti * (float)diff;
         E[k] = __builtin_fma((double)a, diff, E[k]);
-        BT[k] = BT[k] * om;
-        T[k] = Ti;
-        any = true;
+        acc[10] = __builtin_fma(H0[k], wd, acc[10]);
+        acc[11] = __builtin_fma(H1[k], wd, acc[11]);
+        acc[12] = __builtin_fma(H2[k], wd, acc[12]);
+        acc[13] = __builtin_fma(HN0[k], wd, acc[13]);
+        acc[14] = __builtin_fma(HN1[k], wd, acc[14]);
+        acc[15] = __builtin_fma(HN2[k], wd, acc[15]);
+        // dL/dz_i: the depth map and the distortion, 2 w_i sum_m w_m (z_i - z_m)
+        const double dzd = wd * (HD[k] + 2.0 * HE[k] * (zp * AT[k] - S1[k]));
         const bool clamped = sg > kAlphaMax;  // clamped: alpha does not move
         const float dGh = clamped ? 0.0f : dLda * en.opacity;
-        if (!clamped) acc[9] += dLda * h.Gh;
+        acc[9] += clamped ? 0.0f : dLda * h.Gh;
         if (h.obj) {
           // z = M2 . (u, v, 1), G = exp(-(u^2 + v^2)/2), (u, v) = (p0, p1) / p2.
           // The chain through the intersection runs in FP64: its FP32
@@ -565,7 +701,7 @@ __global__ void __launch_bounds__(64) surfel_bwd_kernel(
           ip = __builtin_fma(__builtin_fma(-p2, ip, 1.0), ip, ip);
           ip = __builtin_fma(__builtin_fma(-p2, ip, 1.0), ip, ip);
           const double u = p0 * ip, v = p1 * ip;
-          const double gGd = (double)h.Gh * dGh, dzd = dzv;
+          const double gGd = (double)h.Gh * dGh;
           const double gu = -u * gGd + dzd * en.m2x;
           const double gv = -v * gGd + dzd * en.m2y;
           const double ox = (double)px - fr.cx, oy = (double)py - fr.cy;
@@ -575,15 +711,15 @@ __global__ void __launch_bounds__(64) surfel_bwd_kernel(
                        a2 = hvx * dp1 - hvy * dp0;
           const double b0 = dp1 * huz - dp2 * huy, b1 = dp2 * hux - dp0 * huz,
                        b2 = dp0 * huy - dp1 * hux;
-          acc[0] += (float)a0;
-          acc[1] += (float)a1;
-          acc[2] += (float)a2;
-          acc[3] += (float)b0;
-          acc[4] += (float)b1;
-          acc[5] += (float)b2;
-          acc[6] += (float)(ox * a0 + oy * b0 + u * dzd);
-          acc[7] += (float)(ox * a1 + oy * b1 + v * dzd);
-          acc[8] += (float)(ox * a2 + oy * b2 + dzd);
+          acc[0] += a0;
+          acc[1] += a1;
+          acc[2] += a2;
+          acc[3] += b0;
+          acc[4] += b1;
+          acc[5] += b2;
+          acc[6] += ox * a0 + oy * b0 + u * dzd;
+          acc[7] += ox * a1 + oy * b1 + v * dzd;
+          acc[8] += ox * a2 + oy * b2 + dzd;
         } else {
           // the low-pass: z = z_c, G_lp = exp(-|(x, y) - c|^2); its gradient
           // of c reaches M0_z, M1_z (S_u[2], S_v[2]) and, with the principal
@@ -593,25 +729,73 @@ __global__ void __launch_bounds__(64) surfel_bwd_kernel(
           acc[2] -= gx;
           acc[5] -= gy;
           const float ocx = (S.cxh - fr.cx) + S.cxl, ocy = (S.cyh - fr.cy) + S.cyl;
-          acc[8] += dzv - (gx * ocx + gy * ocy);
+          acc[8] += dzd - (gx * ocx + gy * ocy);
         }
       }
-      if (__ballot(any) == 0) continue;
-      double accd[kSG];
+      if (hit == 0) continue;
+      double tot = 0.0;
+      if (!odd) {
 #pragma unroll
-      for (int i = 0; i < kSG; ++i) accd[i] = acc[i];
-      // value lane >> 2 on every lane of its quad
-      const double tot = lds_wave_sum<kSG>(red, accd, lane);
+        for (int g = 0; g < 4; ++g) {
+          double d = 0.0;
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            d = __builtin_amdgcn_mfma_f64_4x4x4f64(acc[4 * g + c], unit[c], d, 0, 0, 0);
+          tot = __builtin_amdgcn_mfma_f64_4x4x4f64(d, unit[g], tot, 0, 0, 0);
+        }
+      } else {
+        // zeros times a value that is not finite would spread it over the
+        // other sums: sum each value by itself and select
+        const int col = lane & 3;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          double d = 0.0;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const double s = __builtin_amdgcn_mfma_f64_4x4x4f64(acc[4 * g + c], 1.0, 0.0, 0, 0, 0);
+            if (col == c) d = s;
+          }
+          d = __builtin_amdgcn_mfma_f64_4x4x4f64(d, 1.0, 0.0, 0, 0, 0);
+          if (col == g) tot = d;
+        }
+      }
 #pragma unroll
       for (int i = 0; i < kSG; ++i) {
-        acc[i] = 0.0f;
+        acc[i] = 0.0;
         asm volatile("" : "+v"(acc[i]));
       }
-      const uint32_t sl = slot[j];
-      if ((lane & 3) == 0) partial[(size_t)sl * kSG + (lane >> 2)] = (float)tot;
-      if (lane == 0) stamp[sl] = epoch;
+      tot += dpp<kDppRowRor8>(tot);
+      tot += dpp<kDppRowRor4>(tot);
+      if constexpr (WAVES == 1) {
+        const uint32_t sl = L.slot[buf][j];
+        if (out_v >= 0) partial[(size_t)sl * kSG + out_v] = (float)tot;
+        if (lane == 4) stamp[sl] = epoch;
+      } else {
+        if (out_v >= 0) L.tot[wave][j][out_v] = tot;
+        summed |= 1ull << j;
+      }
     }
-    __syncthreads();
+    if constexpr (WAVES > 1) {
+      if (lane == 0) L.summed[wave] = summed;
+      __syncthreads();
+      uint64_t sw[WAVES], all = 0;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) all |= sw[w] = L.summed[w];
+      // 16 threads per entry, the waves' totals in wave order
+      const int v = threadIdx.x % kSG;
+      for (int j = threadIdx.x / kSG; j < kBatchB; j += WAVES * kWave / kSG) {
+        if (!((all >> j) & 1)) continue;
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w)
+          if ((sw[w] >> j) & 1) t += L.tot[w][j][v];
+        const uint32_t sl = L.slot[buf][j];
+        partial[(size_t)sl * kSG + v] = (float)t;
+        if (v == 0) stamp[sl] = epoch;
+      }
+    } else {
+      __syncthreads();
+    }
   }
 }
 
@@ -854,10 +1038,11 @@ void launch_surfel_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                        uint32_t* order, bool xcd_groups, unsigned long long* pairs) {
   if (n_tiles <= 0) return;
   const int groups = tile_schedule_groups(xcd_groups);
-  launch_tile_order(st, n_tiles, groups, prev_nproc, order);
-  const dim3 grid(tile_schedule_grid(n_tiles, groups));
+  launch_tile_order(st, n_tiles, groups, prev_nproc, order, nproc);
+  const unsigned grid = tile_schedule_grid(n_tiles, groups);
 #define GSR_SURF_FWD_C(W, H, C)                                                             \
-  hipLaunchKernelGGL((surfel_fwd_kernel<W, H, C>), grid, dim3(kWave), 0, st, n_tiles,       \
+  hipLaunchKernelGGL((surfel_fwd_kernel<W, H, C>), dim3(grid * TileBlocks<W, H>::kN),        \
+                     dim3(kWave), 0, st, n_tiles,                                          \
                      groups, order, nproc, pairs, F, frames, ranges, vals, (const Surfel*)rec, \
                      bg[0], bg[1], bg[2], rgb, depth, alpha, normal, dist, t_final, n_last,  \
                      dist_aux)
@@ -873,9 +1058,32 @@ void launch_surfel_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
 #undef GSR_SURF_FWD_C
 }
 
+template <int TW, int TH, int PIX>
+static void launch_bwd_t(hipStream_t st, int pix, int n_tiles, int groups, const uint32_t* order,
+                         int F, const FrameDesc* frames, const uint2* ranges,
+                         const uint32_t* vals, const Surfel* rec, const uint32_t* keyoff,
+                         const float* bg, const float* g_rgb, const float* g_depth,
+                         const float* g_alpha, const float* g_normal, const float* g_dist,
+                         const float* t_final, const int32_t* n_last, const float* dist_aux,
+                         float* partial, uint32_t* stamp, const uint32_t* epoch,
+                         const uint32_t* nproc) {
+  if constexpr (PIX > 1) {
+    if (pix < PIX) {
+      launch_bwd_t<TW, TH, PIX / 2>(st, pix, n_tiles, groups, order, F, frames, ranges, vals, rec,
+                                    keyoff, bg, g_rgb, g_depth, g_alpha, g_normal, g_dist,
+                                    t_final, n_last, dist_aux, partial, stamp, epoch, nproc);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((surfel_bwd_kernel<TW, TH, PIX>), dim3(tile_schedule_grid(n_tiles, groups)),
+                     dim3(TW * TH / PIX), 0, st, n_tiles, groups, order, nproc, F, frames, ranges,
+                     vals, rec, keyoff, bg[0], bg[1], bg[2], g_rgb, g_depth, g_alpha, g_normal,
+                     g_dist, t_final, n_last, dist_aux, partial, stamp, epoch);
+}
+
 void launch_surfel_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                        const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
-                       const void* rec, const uint2* trect, const uint32_t* keyoff,
+                       const void* rec, const uint32_t* keyoff,
                        const float* bg, const float* g_rgb, const float* g_depth,
                        const float* g_alpha, const float* g_normal, const float* g_dist,
                        const float* t_final, const int32_t* n_last, const float* dist_aux,
@@ -884,12 +1092,17 @@ void launch_surfel_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
   if (n_tiles <= 0) return;
   const int groups = tile_schedule_groups(xcd_groups);
   launch_tile_order(st, n_tiles, groups, nproc, order);
-  const dim3 grid(tile_schedule_grid(n_tiles, groups));
-#define GSR_SURF_BWD(W, H)                                                                   \
-  hipLaunchKernelGGL((surfel_bwd_kernel<W, H>), grid, dim3(kWave), 0, st, n_tiles, groups,    \
-                     order, nproc, F, frames, ranges, vals, (const Surfel*)rec, trect, keyoff, \
-                     bg[0], bg[1], bg[2], g_rgb, g_depth, g_alpha, g_normal, g_dist, t_final,  \
-                     n_last, dist_aux, partial, stamp, epoch)
+  // Blocks per wave: as many as leave kBwdMinWaves waves, as in the 3D
+  // backward.  Measured with 1 / 2 / 4 blocks (us): 4 x 1200x680 (12,900 tiles
+  // of 16x16) 4445 / 4142 / 3436; 1 x 321x243 (336 tiles) 316 / 474 / 708.
+  const int blocks = tw * th / kWave;
+  int pix = 4;
+  while (pix > 1 && (int64_t)n_tiles * blocks / pix < kBwdMinWaves) pix /= 2;
+#define GSR_SURF_BWD(W, H)                                                                    \
+  launch_bwd_t<W, H, std::min(4, TileBlocks<W, H>::kN)>(                                      \
+      st, pix, n_tiles, groups, order, F, frames, ranges, vals, (const Surfel*)rec, keyoff, bg, \
+      g_rgb, g_depth, g_alpha, g_normal, g_dist, t_final, n_last, dist_aux, partial, stamp,    \
+      epoch, nproc)
   if (tw == 16 && th == 16) GSR_SURF_BWD(16, 16);
   else if (tw == 8 && th == 8) GSR_SURF_BWD(8, 8);
   else if (tw == 32 && th == 8) GSR_SURF_BWD(32, 8);

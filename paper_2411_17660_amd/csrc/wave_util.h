@@ -1,7 +1,8 @@
 // wave_util.h -- wave-level helpers shared by the kernels of the 3D Gaussian
 // and 2D surfel paths: the FP64 cross-lane swaps and DPP moves, the
-// transposing and LDS wave sums built on them, and the XCD-grouped tile
-// schedule.
+// transposing and LDS wave sums built on them, the XCD-grouped tile
+// schedule, and the 8 x 8 pixel blocks the compositing kernels work over with
+// the test of an entry against a block.
 #pragma once
 #include "gsr_device.h"
 
@@ -51,9 +52,10 @@ __device__ __forceinline__ double swap_sum(double a, double b) {
 
 // The value of v on a partner lane inside the lane's 16-lane row: DPP row
 // mirror (partner 15 - l) for lane bit 3, half-row mirror (7 - l) for bit 2,
-// quad permutes (l ^ 2, l ^ 1) for bits 1 and 0.  A row rotation by 8 is
-// l ^ 8, and one by 4 after it completes the sum over lane bits 3 and 2.  The mirrors also flip the
-// lower lane bits; the rounds that follow sum over those anyway.
+// quad permutes (l ^ 2, l ^ 1) for bits 1 and 0.  The mirrors also flip the
+// lower lane bits; the rounds that follow sum over those anyway.  A row
+// rotation by 8 is l ^ 8, and one by 4 after it completes the sum over lane
+// bits 3 and 2.
 template <int CTRL>
 __device__ __forceinline__ double dpp(double v) {
   const uint64_t u = (uint64_t)__double_as_longlong(v);
@@ -64,38 +66,8 @@ __device__ __forceinline__ double dpp(double v) {
                                                          true);
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
-constexpr int kDppRowRor8 = 0x128, kDppRowRor4 = 0x124, kDppRowMirror = 0x140, kDppHalfMirror = 0x141, kDppQuadXor2 = 0x4e,
-              kDppQuadXor1 = 0xb1;
-
-// Sum over the wave of N <= 16 FP64 values per lane through LDS: every
-// lane stores its values, lane 4 v + p (v < N) adds the 16 lanes
-// 16 p .. 16 p + 15 of value v in a fixed pairwise order, and the quad adds
-// its four parts by DPP moves.  Returns the total of value
-// min(lane >> 2, N - 1) on every lane of the quad.  `red` holds
-// N * kRedValue doubles used by this wave only; a wave's LDS operations
-// complete in issue order, so calls may follow each other on one buffer.
-// Value v, part p, term t live at v kRedValue + p kRedPart + t: the padding
-// (17 and 68 doubles instead of 16 and 64) spreads the summing lanes' reads
-// over the LDS banks (at most 4 lanes share one; 64 without it).
-constexpr int kRedPart = 17, kRedValue = 4 * kRedPart;
-
-template <int N>
-__device__ __forceinline__ double lds_wave_sum(double* red, const double (&v)[N], int lane) {
-  static_assert(N >= 1 && N <= 16, "four lanes per value");
-  double* dst = red + (lane >> 4) * kRedPart + (lane & 15);
-#pragma unroll
-  for (int i = 0; i < N; ++i) dst[i * kRedValue] = v[i];
-  const int rv = lane >> 2 < N ? lane >> 2 : N - 1, rp = lane & 3;
-  const double* src = red + rv * kRedValue + rp * kRedPart;
-  double s4[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-    s4[t] = (src[4 * t] + src[4 * t + 1]) + (src[4 * t + 2] + src[4 * t + 3]);
-  double tot = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-  tot += dpp<kDppQuadXor2>(tot);
-  tot += dpp<kDppQuadXor1>(tot);
-  return tot;
-}
+constexpr int kDppRowRor8 = 0x128, kDppRowRor4 = 0x124, kDppRowMirror = 0x140,
+              kDppHalfMirror = 0x141, kDppQuadXor2 = 0x4e, kDppQuadXor1 = 0xb1;
 
 // Sum over the wave of N FP64 values per lane by recursive halving: at lane
 // bit b a lane keeps the lower or the upper half of its values (by that bit)
@@ -153,6 +125,67 @@ __device__ __forceinline__ double wave_transpose_sum(const double (&v)[N], int l
   idx = base;
   writer = cnt > 0;
   return rr[0];
+}
+
+// Pixel blocks.
+// A tile of TW x TH pixels is cut into 8 x 8 blocks, one pixel per lane (lane
+// l owns pixel (l % 8, l / 8) of a block).  A square block has the smallest
+// perimeter of 64 pixels, so the fewest Gaussians touch it.
+constexpr int kBlk = 8;
+
+template <int TW, int TH>
+struct TileBlocks {
+  static constexpr int kX = TW / kBlk, kY = TH / kBlk, kN = kX * kY;
+};
+
+// The part of the block at (bx, by) inside an entry's pixel bounds sqx, sqy
+// (lo | hi << 16).
+struct BlockPart {
+  int xlo, xhi, ylo, yhi;
+  __device__ __forceinline__ bool empty() const { return xlo > xhi || ylo > yhi; }
+};
+
+__device__ __forceinline__ BlockPart block_part(uint32_t sqx, uint32_t sqy, int bx, int by) {
+  return {max(bx, (int)(sqx & 0xffff)), min(bx + kBlk - 1, (int)(sqx >> 16)),
+          max(by, (int)(sqy & 0xffff)), min(by + kBlk - 1, (int)(sqy >> 16))};
+}
+
+// Its pixels, one bit per lane.
+__device__ __forceinline__ uint64_t block_lanes(const BlockPart& b, int bx, int by) {
+  const uint32_t cols = (0xffu >> (kBlk - 1 - (b.xhi - b.xlo))) << (b.xlo - bx);
+  const uint64_t rows = (~0ull >> (kBlk * (kBlk - 1 - (b.yhi - b.ylo)))) << (kBlk * (b.ylo - by));
+  const uint32_t c4 = cols * 0x01010101u;
+  return (((uint64_t)c4 << 32) | c4) & rows;
+}
+
+// The least q = (a1 dx + a2 dy)^2 + (a3 dy)^2 over such a part, d = centre
+// minus pixel (centre as FP32 hi/lo pairs).  Each lane asks this of its own
+// entry, so 64 entries cost one evaluation.  q is convex with its minimum at
+// d = 0: over the half-plane beyond the side nearest to 0 it is least at dy =
+// -a1 a2 x / (a2^2 + a3^2), so over the part it is least in the row nearest
+// to that dy, where m = a1 dx + a2 dy runs over an interval.  `big` receives
+// the size of the terms that can cancel in m: a caller that compares q
+// with a bound widens the bound by a few ulps of it (4e-6 is 64 FP32 ulps,
+// far above the rounding of this test and of the per-pixel q), so that a part
+// that fails holds no pixel whose computed value would pass.
+__device__ __forceinline__ float least_q(float a1, float a2, float a3, float u_hi, float u_lo,
+                                         float v_hi, float v_lo, const BlockPart& b, float& big) {
+  const float dxl = dx_of(u_hi, u_lo, b.xhi), dxh = dx_of(u_hi, u_lo, b.xlo);
+  const float dyl = dx_of(v_hi, v_lo, b.yhi), dyh = dx_of(v_hi, v_lo, b.ylo);
+  const float xn = __builtin_amdgcn_fmed3f(0.0f, dxl, dxh);
+  const float ys = -(a1 * a2 * xn) * __builtin_amdgcn_rcpf(a2 * a2 + a3 * a3);
+  const float yc = __builtin_amdgcn_fmed3f(ys, dyl, dyh);
+  const float m = __builtin_amdgcn_fmed3f(0.0f, a1 * dxl + a2 * yc, a1 * dxh + a2 * yc);
+  const float t = a3 * yc;
+  big = a1 * fmaxf(fabsf(dxl), fabsf(dxh)) + (fabsf(a2) + a3) * fmaxf(fabsf(dyl), fabsf(dyh));
+  return m * m + t * t;
+}
+
+// lane j's value of v (j wave-uniform)
+__device__ __forceinline__ uint64_t readlane64(uint64_t v, int j) {
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), j);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, j);
+  return ((uint64_t)hi << 32) | lo;
 }
 
 }  // namespace gsr

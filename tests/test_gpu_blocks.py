@@ -66,3 +66,42 @@ def test_nonfinite_upstream_stays_in_its_channel(rast, size, bad):
     assert hit.any() and not hit.all()
     for k in ("means", "log_scales", "quats", "opacity", "sh"):
         assert np.array_equal(good[k][~hit], got[k][~hit]), k
+
+
+# surfel lists of each backward path (1, 2 and 4 blocks per wave), ragged
+# images, and disks seen at a grazing angle (their block test falls back to
+# the box)
+@pytest.mark.parametrize("tilt", [0.2, 1.5])
+@pytest.mark.parametrize("size,tile", [((40, 29), (16, 16)), ((523, 500), (8, 8)),
+                                       ((785, 689), (16, 16)), ((1030, 1025), (16, 16)),
+                                       ((1025, 513), (32, 16))])
+def test_surfel_blocks_do_not_depend_on_the_path(rast, size, tile, tilt):
+    """The five images are bitwise those of the 8x8 tiles (one block per tile),
+    and the gradients agree to FP32 rounding of their FP64 sums."""
+    import torch
+    from gpu_util import to_dev
+    W, H = size
+    sc = scenes.tiny_scene(seed=3, n=150, W=W, H=H, f=0.7 * max(W, H), sh_degree=1,
+                           ls_mean=-2.2, ls_sigma=0.5, opacity_sigma=1.5)
+    d = to_dev(sc)
+    d["log_scales"] = d["log_scales"][:, :2].contiguous()
+    q = torch.randn(sc.n, 4, generator=torch.Generator().manual_seed(1)) * tilt
+    q[:, 0] = 1.0
+    d["quats"] = q.cuda()
+    args = [d[k] for k in ("means", "log_scales", "quats", "opacity", "sh", "poses")]
+    P = W * H
+    gen = torch.Generator().manual_seed(2)
+    G = [torch.randn(k * P, generator=gen).cuda() for k in (3, 1, 1, 3, 1)]
+    out = []
+    for t in ((8, 8), tile):
+        im = rast.forward_surfel(*args, sc.cams, sc.sh_degree, sc.background, tile=t)
+        out.append(([x.clone() for x in im], rast.backward_surfel(*G)))
+    torch.cuda.synchronize()
+    for a, b in zip(out[0][0], out[1][0]):
+        assert torch.equal(a, b)
+    # a key's sums are FP64 and stored as FP32, then summed over keys in FP64
+    # and passed through the (linear) chain rule: 2^-24 of the largest term
+    for k, a in out[0][1].items():
+        b = out[1][1][k]
+        err = float((a.double() - b.double()).norm() / a.double().norm())
+        assert err <= 2e-5, (k, err)
