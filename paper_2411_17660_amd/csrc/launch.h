@@ -23,8 +23,6 @@ void launch_preprocess_bwd(hipStream_t st, int64_t n, int F, const FrameDesc* fr
                            double* grad2d, float* g_means, float* g_log_scales, float* g_quats,
                            float* g_opac, float* g_sh, double* twist_partial, float* g_twist);
 void launch_bump_epoch(hipStream_t st, uint32_t* epoch);
-// cls[r] = 1 + floor(log2(ntiles[r])) (0 when culled), idx[r] = r: the input
-// of the radix sort that orders the per-record reduction
 // Statistics of the last forward: out[0] += records with no tile (culled),
 // out[1] += Gaussians with a non-finite parameter (log_per = 3 log-scales
 // per Gaussian, or 2 for surfels; nb3 = 3 (d+1)^2 SH values).
@@ -32,13 +30,9 @@ void launch_cull_stats(hipStream_t st, uint64_t m, const uint32_t* ntiles, int64
                        const float* means, const float* log_scales, int log_per,
                        const float* quats, const float* opac, const float* sh, int nb3,
                        unsigned long long* out);
-void launch_size_class(hipStream_t st, uint64_t m, const uint32_t* ntiles, uint32_t* cls,
-                       uint32_t* idx);
-// *first_wide = the first position of the ascending sorted classes whose
-// record has 128 or more slots (m if none); the 3D backward reduces those
-// records a wave each
-void launch_wide_boundary(hipStream_t st, uint64_t m, const uint32_t* sorted_cls,
-                          uint32_t* first_wide);
+// The class of the records that the 3D backward's slot reduction gives a wave
+// each (1 + floor(log2 of the key count)).
+uint32_t wide_class();
 
 // sort.hip: depth sort, offsets, tile keys and their sort, ranges.
 // radix_hist_elems / radix_scan_elems: u32 workspace of a sort of up to
@@ -51,15 +45,26 @@ void launch_copy16(hipStream_t st, const void* src, void* dst, uint64_t n16);
 size_t radix_hist_elems(uint64_t n_max, int bits);
 size_t scan_block_elems(uint64_t n_max);
 size_t radix_scan_elems(uint64_t n_max, int bits);
-bool launch_radix_sort(hipStream_t st, uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
-                       uint32_t* vals_b, const uint64_t* n_dev, uint64_t n_max, int bits,
-                       uint32_t* hist, uint32_t* scan_tmp);
+// Stable sort of m records by their 32 depth bits; ends in (keys_a, vals_a).
+void launch_depth_sort(hipStream_t st, uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
+                       uint32_t* vals_b, uint64_t m, uint32_t* hist, uint32_t* scan_tmp);
 // skey: the sorted depth keys (all ones: culled); trect_sorted[i] and
 // cnt_sorted[i]: the tile rect and tile count of record perm[i].
 void launch_offsets_scan(hipStream_t st, const uint32_t* skey, const uint32_t* perm,
                          const uint2* trect, uint64_t m, uint32_t* cnt_sorted,
                          uint2* trect_sorted, uint64_t* offsets, uint64_t* block_tmp,
                          uint64_t* total);
+// Few records: both of the above in two launches, from (keys, vals).
+bool rank_records(uint64_t m);
+void launch_rank_records(hipStream_t st, const uint32_t* keys, const uint32_t* vals, uint64_t m,
+                         const uint2* trect, uint32_t* keys_out, uint32_t* vals_out,
+                         uint32_t* cnt_sorted, uint2* trect_sorted, uint64_t* offsets,
+                         uint64_t* total);
+// order: the records 0..m-1 in ascending order of size class (0: no key, else
+// 1 + floor(log2 of the key count)); *first (unless NULL) receives the
+// position of the first one of class `mark` or above (m if none).
+void launch_class_order(hipStream_t st, uint64_t m, const uint32_t* ntiles, uint32_t* order,
+                        uint32_t mark, uint32_t* first, uint32_t* hist, uint32_t* scan_tmp);
 // Tile keys are 16-bit when the tile ids and the all-ones sentinel fit
 // (bits <= 16), else 32-bit; `keys` buffers hold that type.
 bool tile_keys_16bit(int bits);

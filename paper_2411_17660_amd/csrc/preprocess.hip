@@ -276,31 +276,10 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(
 constexpr uint32_t kWideSlots = 128;
 constexpr uint64_t kWideWaves = 8192;  // the wide pass's grid (32 waves per CU)
 
-// The class of kWideSlots slots: records of this class or above are wide.
+// The class of kWideSlots slots: records of this class or above are wide, and
+// *first_wide is the position of the first one in `order` (m if none).
 constexpr uint32_t kWideClass = 8;  // 1 + log2(kWideSlots)
 static_assert((1u << (kWideClass - 1)) == kWideSlots, "wide class");
-
-// *first_wide (pre-filled with m) = the first position of the ascending
-// class keys with class >= kWideClass: the one position where the class
-// crosses it is written by its own thread.
-__global__ void __launch_bounds__(256) wide_boundary_kernel(uint64_t m,
-                                                            const uint32_t* __restrict__ cls,
-                                                            uint32_t* __restrict__ first_wide) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  if (cls[i] >= kWideClass && (i == 0 || cls[i - 1] < kWideClass)) *first_wide = (uint32_t)i;
-}
-
-__global__ void __launch_bounds__(256) size_class_kernel(uint64_t m,
-                                                         const uint32_t* __restrict__ ntiles,
-                                                         uint32_t* __restrict__ cls,
-                                                         uint32_t* __restrict__ idx) {
-  const uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= m) return;
-  const uint32_t c = ntiles[r];
-  cls[r] = c == 0 ? 0u : 32u - (uint32_t)__clz(c);  // 1 + floor(log2 c)
-  idx[r] = (uint32_t)r;
-}
 
 constexpr int kSlotGroup = 4;
 constexpr int kSlotUnroll = 4;
@@ -724,20 +703,7 @@ void launch_cull_stats(hipStream_t st, uint64_t m, const uint32_t* ntiles, int64
                      m, ntiles, n, means, log_scales, log_per, quats, opac, sh, nb3, out);
 }
 
-void launch_size_class(hipStream_t st, uint64_t m, const uint32_t* ntiles, uint32_t* cls,
-                       uint32_t* idx) {
-  if (m == 0) return;
-  hipLaunchKernelGGL(size_class_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, m,
-                     ntiles, cls, idx);
-}
-
-void launch_wide_boundary(hipStream_t st, uint64_t m, const uint32_t* sorted_cls,
-                          uint32_t* first_wide) {
-  launch_fill_u32(st, first_wide, 1, (uint32_t)m);
-  if (m == 0) return;
-  hipLaunchKernelGGL(wide_boundary_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st,
-                     m, sorted_cls, first_wide);
-}
+uint32_t wide_class() { return kWideClass; }
 
 void launch_bump_epoch(hipStream_t st, uint32_t* epoch) {
   hipLaunchKernelGGL(bump_epoch_kernel, dim3(1), dim3(1), 0, st, epoch);

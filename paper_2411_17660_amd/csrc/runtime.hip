@@ -39,7 +39,6 @@ struct Saved {
   bool k_known = false;
   bool sorted_in_b = false;   // tile sort result buffer
   bool keys16 = false;        // tile keys stored as 16 bits
-  bool recs_in_b = false;     // depth sort result buffer
   bool surfel = false;        // the forward rendered 2D surfels
   bool has_backward = false;  // a backward of this forward has filled grad2d
 };
@@ -63,7 +62,7 @@ struct gsr_context {
   DBuf up_rgb, up_depth, up_alpha;  // upstream gradients for gsr_step_l1
   DBuf tune_out;                    // scratch outputs of the autotuner
   DBuf order_f, order_b;            // compositing tile schedules (forward, backward)
-  DBuf cls_a, cls_b, clsv_a, clsv_b;  // records ordered by key count (per-record reduction)
+  DBuf cls_order;  // records ordered by key count (per-record reduction)
   // layout (tile shape and frame sizes) whose processed-entry counts nproc
   // holds, so that the next forward over the same tiles can order its queue
   // by them; empty when nproc holds none
@@ -234,8 +233,8 @@ gsr_status gsr_destroy(gsr_context* ctx) {
                   &ctx->ssim_part, &ctx->ssim_tiles, &ctx->ssim_scale, &ctx->med_pos,
                   &ctx->reloc_cnt, &ctx->reloc_rule,
                   &ctx->up_rgb, &ctx->up_depth, &ctx->up_alpha, &ctx->tune_out,
-                  &ctx->order_f, &ctx->order_b, &ctx->cls_a, &ctx->cls_b, &ctx->clsv_a,
-                  &ctx->clsv_b, &ctx->dist_aux, &ctx->spart, &ctx->sgrad, &ctx->nc_part};
+                  &ctx->order_f, &ctx->order_b, &ctx->cls_order, &ctx->dist_aux, &ctx->spart,
+                  &ctx->sgrad, &ctx->nc_part};
   for (DBuf* b : bufs)
     if (b->p) (void)hipFree(b->p);
   if (ctx->h_count) (void)hipHostFree(ctx->h_count);
@@ -319,19 +318,22 @@ gsr_status forward_impl(gsr_context* ctx, const gsr_settings* s, int64_t n, cons
   uint64_t* d_count = P<uint64_t>(ctx->counters);               // [0] = K
   uint32_t* d_overflow = (uint32_t*)(P<uint64_t>(ctx->counters) + 1);
   const bool timing = (s->flags & GSR_FLAG_TIMING) != 0;
-  // A1 preprocess
+  // A1 preprocess: the keys go where the depth sort ends in (.._a) after it
+  const bool few = rank_records(M);
+  uint32_t* dkey = P<uint32_t>(few ? ctx->dkey_b : ctx->dkey_a);
+  uint32_t* dval = P<uint32_t>(few ? ctx->dval_b : ctx->dval_a);
   {
     StageTimer t(ctx, st, timing, GSR_STAGE_PREPROCESS);
     if (surfel)
       launch_surfel_preprocess(st, n, F, P<FrameDesc>(ctx->frames), poses, means, log_scales,
                                quats, opac, sh, s->sh_degree, tw, th, ctx->rec.p,
-                               P<uint2>(ctx->trect), P<uint32_t>(ctx->dkey_a),
-                               P<uint32_t>(ctx->dval_a), P<uint32_t>(ctx->ntiles));
+                               P<uint2>(ctx->trect), dkey,
+                               dval, P<uint32_t>(ctx->ntiles));
     else
       launch_preprocess_fwd(st, n, F, P<FrameDesc>(ctx->frames), poses, means, log_scales,
                             quats, opac, sh, s->sh_degree, tw, th, P<Record>(ctx->rec),
-                            P<uint2>(ctx->trect), P<uint32_t>(ctx->dkey_a),
-                            P<uint32_t>(ctx->dval_a), P<uint32_t>(ctx->ntiles));
+                            P<uint2>(ctx->trect), dkey,
+                            dval, P<uint32_t>(ctx->ntiles));
   }
   // depth sort of the records (32-bit keys)
   const uint64_t kcap_guess = std::max<uint64_t>(ctx->key_cap, s->key_capacity);
@@ -343,22 +345,24 @@ gsr_status forward_impl(gsr_context* ctx, const gsr_settings* s, int64_t n, cons
       std::max({scan_block_elems(M) * 8, radix_scan_elems(M, 0) * 4,
                 radix_scan_elems(std::max<uint64_t>(kcap_guess, 1), tile_bits) * 4});
   if ((rc = ensure(ctx, ctx->scan_tmp, scan_need, st))) return rc;
-  bool recs_in_b = false;
   {
     StageTimer t(ctx, st, timing, GSR_STAGE_DEPTH_SORT);
-    if (M > 0)
-      recs_in_b = launch_radix_sort(st, P<uint32_t>(ctx->dkey_a), P<uint32_t>(ctx->dval_a),
-                                    P<uint32_t>(ctx->dkey_b), P<uint32_t>(ctx->dval_b), nullptr,
-                                    M, 32, P<uint32_t>(ctx->hist), P<uint32_t>(ctx->scan_tmp));
+    if (few)
+      launch_rank_records(st, dkey, dval, M, P<uint2>(ctx->trect), P<uint32_t>(ctx->dkey_a),
+                          P<uint32_t>(ctx->dval_a), P<uint32_t>(ctx->cnt_sorted),
+                          P<uint2>(ctx->trect_s), P<uint64_t>(ctx->offsets), d_count);
+    else
+      launch_depth_sort(st, P<uint32_t>(ctx->dkey_a), P<uint32_t>(ctx->dval_a),
+                        P<uint32_t>(ctx->dkey_b), P<uint32_t>(ctx->dval_b), M,
+                        P<uint32_t>(ctx->hist), P<uint32_t>(ctx->scan_tmp));
   }
-  const uint32_t* perm = P<uint32_t>(recs_in_b ? ctx->dval_b : ctx->dval_a);
+  const uint32_t* perm = P<uint32_t>(ctx->dval_a);
   // A2 offsets over the depth-ordered records, K on the device
-  {
+  if (!few) {
     StageTimer t(ctx, st, timing, GSR_STAGE_OFFSETS);
-    launch_offsets_scan(st, P<uint32_t>(recs_in_b ? ctx->dkey_b : ctx->dkey_a), perm,
-                        P<uint2>(ctx->trect), M, P<uint32_t>(ctx->cnt_sorted),
-                        P<uint2>(ctx->trect_s), P<uint64_t>(ctx->offsets),
-                        P<uint64_t>(ctx->scan_tmp), d_count);
+    launch_offsets_scan(st, P<uint32_t>(ctx->dkey_a), perm, P<uint2>(ctx->trect), M,
+                        P<uint32_t>(ctx->cnt_sorted), P<uint2>(ctx->trect_s),
+                        P<uint64_t>(ctx->offsets), P<uint64_t>(ctx->scan_tmp), d_count);
   }
   // key capacity
   uint64_t K = 0, cap = 0;
@@ -459,7 +463,6 @@ gsr_status forward_impl(gsr_context* ctx, const gsr_settings* s, int64_t n, cons
   sv.k_known = k_known;
   sv.sorted_in_b = keys_in_b;
   sv.keys16 = tile_keys_16bit(tile_bits);
-  sv.recs_in_b = recs_in_b;
   sv.surfel = surfel;
   return GSR_OK;
 }
@@ -543,10 +546,7 @@ gsr_status gsr_backward_surfel(gsr_context* ctx, const float* g_rgb, const float
   const uint64_t kcap = std::min<uint64_t>(sv.K, ctx->key_cap);
   if ((rc = ensure(ctx, ctx->spart, std::max<uint64_t>(kcap, 1) * ng * 4, st))) return rc;
   if ((rc = ensure(ctx, ctx->sgrad, std::max<uint64_t>(M, 1) * ng * 8, st))) return rc;
-  if ((rc = ensure(ctx, ctx->cls_a, M * 4, st))) return rc;
-  if ((rc = ensure(ctx, ctx->cls_b, M * 4, st))) return rc;
-  if ((rc = ensure(ctx, ctx->clsv_a, M * 4, st))) return rc;
-  if ((rc = ensure(ctx, ctx->clsv_b, M * 4, st))) return rc;
+  if ((rc = ensure(ctx, ctx->cls_order, M * 4, st))) return rc;
   const int64_t waves = sv.n > 0 ? surfel_preprocess_bwd_waves(sv.n) : 0;
   if ((rc = ensure(ctx, ctx->twist_part, (size_t)std::max<int64_t>(waves, 1) * sv.F * 6 * 8, st)))
     return rc;
@@ -567,15 +567,9 @@ gsr_status gsr_backward_surfel(gsr_context* ctx, const float* g_rgb, const float
   }
   {
     StageTimer t(ctx, st, timing, GSR_STAGE_PREPROCESS_BWD);
-    bool cls_in_b = false;
-    if (M > 0) {
-      launch_size_class(st, M, P<uint32_t>(ctx->ntiles), P<uint32_t>(ctx->cls_a),
-                        P<uint32_t>(ctx->clsv_a));
-      cls_in_b = launch_radix_sort(st, P<uint32_t>(ctx->cls_a), P<uint32_t>(ctx->clsv_a),
-                                   P<uint32_t>(ctx->cls_b), P<uint32_t>(ctx->clsv_b), nullptr, M,
-                                   8, P<uint32_t>(ctx->hist), P<uint32_t>(ctx->scan_tmp));
-    }
-    launch_surfel_slot_reduce(st, M, P<uint32_t>(cls_in_b ? ctx->clsv_b : ctx->clsv_a),
+    launch_class_order(st, M, P<uint32_t>(ctx->ntiles), P<uint32_t>(ctx->cls_order), 0, nullptr,
+                       P<uint32_t>(ctx->hist), P<uint32_t>(ctx->scan_tmp));
+    launch_surfel_slot_reduce(st, M, P<uint32_t>(ctx->cls_order),
                               P<uint32_t>(ctx->keyoff), P<uint32_t>(ctx->ntiles),
                               P<float>(ctx->spart), P<uint32_t>(ctx->stamp), d_epoch,
                               kcap, P<double>(ctx->sgrad));
@@ -634,26 +628,17 @@ gsr_status gsr_backward(gsr_context* ctx, const float* g_rgb, const float* g_dep
     return rc;
   if ((rc = ensure(ctx, ctx->grad2d, (size_t)sv.n * sv.F * kNG * 8, st))) return rc;
   const uint64_t M = (uint64_t)sv.n * sv.F;
-  if ((rc = ensure(ctx, ctx->cls_a, M * 4, st))) return rc;
-  if ((rc = ensure(ctx, ctx->cls_b, M * 4, st))) return rc;
-  if ((rc = ensure(ctx, ctx->clsv_a, M * 4, st))) return rc;
-  if ((rc = ensure(ctx, ctx->clsv_b, M * 4, st))) return rc;
+  if ((rc = ensure(ctx, ctx->cls_order, M * 4, st))) return rc;
   {
     StageTimer t(ctx, st, timing, GSR_STAGE_PREPROCESS_BWD);
-    bool cls_in_b = false;
     uint32_t* first_wide = (uint32_t*)(P<uint64_t>(ctx->counters) + 6);
-    if (M > 0) {
-      launch_size_class(st, M, P<uint32_t>(ctx->ntiles), P<uint32_t>(ctx->cls_a),
-                        P<uint32_t>(ctx->clsv_a));
-      cls_in_b = launch_radix_sort(st, P<uint32_t>(ctx->cls_a), P<uint32_t>(ctx->clsv_a),
-                                   P<uint32_t>(ctx->cls_b), P<uint32_t>(ctx->clsv_b), nullptr, M,
-                                   8, P<uint32_t>(ctx->hist), P<uint32_t>(ctx->scan_tmp));
-    }
-    launch_wide_boundary(st, M, P<uint32_t>(cls_in_b ? ctx->cls_b : ctx->cls_a), first_wide);
+    launch_class_order(st, M, P<uint32_t>(ctx->ntiles), P<uint32_t>(ctx->cls_order),
+                       wide_class(), first_wide, P<uint32_t>(ctx->hist),
+                       P<uint32_t>(ctx->scan_tmp));
     launch_preprocess_bwd(st, sv.n, sv.F, P<FrameDesc>(ctx->frames), sv.poses, sv.means,
                           sv.log_scales, sv.quats, sv.opac, sv.sh, s.sh_degree,
                           P<Record>(ctx->rec),
-                          P<uint32_t>(cls_in_b ? ctx->clsv_b : ctx->clsv_a), first_wide,
+                          P<uint32_t>(ctx->cls_order), first_wide,
                           P<uint32_t>(ctx->keyoff), P<uint32_t>(ctx->ntiles), P<float>(ctx->partial),
                           P<uint32_t>(ctx->stamp), d_epoch, ctx->key_cap,
                           P<double>(ctx->grad2d), g_means, g_log_scales, g_quats, g_opac, g_sh,
@@ -1060,8 +1045,8 @@ gsr_status gsr_debug_lists(gsr_context* ctx, uint32_t* ntiles, uint32_t* depth_k
   if (depth_key && M) {
     // the depth keys were sorted in place; rebuild the per-record view
     std::vector<uint32_t> k(M), v(M);
-    const DBuf& kb = sv.recs_in_b ? ctx->dkey_b : ctx->dkey_a;
-    const DBuf& vb = sv.recs_in_b ? ctx->dval_b : ctx->dval_a;
+    const DBuf& kb = ctx->dkey_a;
+    const DBuf& vb = ctx->dval_a;
     GSR_HIP(hipMemcpy(k.data(), kb.p, M * 4, hipMemcpyDeviceToHost));
     GSR_HIP(hipMemcpy(v.data(), vb.p, M * 4, hipMemcpyDeviceToHost));
     for (size_t i = 0; i < M; ++i) depth_key[v[i]] = k[i];

@@ -21,7 +21,9 @@
 // its waves' counts into stable block offsets; no global atomics.  A
 // pass's digit counts are stored one row per block, so the histogram writes
 // and the scatter reads them as whole rows, and their scan runs down the
-// columns (3 launches); the other scans are reduce-then-scan in 3 launches.
+// columns: in the scatter's blocks themselves while there are few rows (2
+// launches a pass), else in 3 launches of its own.  A few thousand elements
+// are ordered in one launch, by counting for each the ones in front of it.
 // Scatter blocks are dealt so that consecutive blocks run on one XCD: the
 // partial cache lines at the two ends of a block's digit run are completed by
 // its neighbour in the same L2 instead of leaving as partial writes.  All
@@ -38,113 +40,163 @@ constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanThreads * kScanItems;  // elements per block
 
+constexpr int kScanFew = 2;  // gather: records per thread up to kGatherBig records
+constexpr uint64_t kGatherBig = 1ull << 22;
+
 constexpr int kSortRounds = 16;  // 64-key rounds per wave in the radix passes
 constexpr int kMaxDigitBits = 10;
 constexpr int kMaxBins = 1 << kMaxDigitBits;
 constexpr unsigned kXcds = 8;  // XCDs of an MI355X: workgroup b runs on XCD b % 8
 
-// ---------------------------------------------------------------------------
-// Block-wide exclusive scan of one value per thread (256 threads).
-// ---------------------------------------------------------------------------
+// Exclusive scan of one value per thread over a block of blockDim.x threads
+// (a multiple of 64, at most 1024); wsum holds 16 values.
 template <typename T>
-__device__ __forceinline__ T block_exclusive_scan(T v, T* sh, T& total) {
-  const int tid = threadIdx.x;
-  sh[tid] = v;
-  __syncthreads();
-  for (int o = 1; o < kScanThreads; o <<= 1) {
-    T add = tid >= o ? sh[tid - o] : (T)0;
-    __syncthreads();
-    sh[tid] += add;
-    __syncthreads();
+__device__ __forceinline__ T block_scan_excl(T v, T* wsum, T& total) {
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  const int nw = blockDim.x / kWave;
+  T x = v;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const T y = __shfl_up(x, o, kWave);
+    if (lane >= o) x += y;
   }
-  total = sh[kScanThreads - 1];
-  const T incl = sh[tid];
+  if (lane == kWave - 1) wsum[w] = x;
   __syncthreads();
-  return incl - v;
+  T base = 0, tot = 0;
+  for (int k = 0; k < nw; ++k) {
+    const T s = wsum[k];
+    if (k < w) base += s;
+    tot += s;
+  }
+  __syncthreads();
+  total = tot;
+  return base + x - v;
 }
 
-// Loaders: element i of the scanned sequence.
-struct LoadU32 {
-  const uint32_t* a;
-  __device__ uint32_t operator()(uint64_t i) const { return a[i]; }
-};
+// The tile counts in depth order, cnt_sorted[i] = ntiles[perm[i]], gathered
+// once so that the offsets scan and keygen read them in order, together
+// with the tile rects (keygen's one random read per record happens here, as
+// part of the gather that has to be random anyway).  A record is kept iff its
+// sorted depth key is not the all-ones of a culled record, and a kept
+// record's tile count is the area of its rect (the preprocess writes the two
+// together; a culled record has neither).
+__device__ __forceinline__ uint32_t kept_tiles(uint32_t skey, uint32_t r,
+                                               const uint2* __restrict__ trect, uint2& tr) {
+  tr = make_uint2(0u, 0u);
+  if (skey == 0xffffffffu) return 0u;
+  tr = trect[r];
+  return ((tr.x >> 16) - (tr.x & 0xffffu) + 1u) * ((tr.y >> 16) - (tr.y & 0xffffu) + 1u);
+}
 
-template <typename T, typename Load>
-__global__ void __launch_bounds__(kScanThreads) scan_reduce_kernel(Load ld, const uint64_t* n_dev,
-                                                                   uint64_t n_host,
-                                                                   T* __restrict__ block_sums) {
-  __shared__ T sh[kScanThreads];
-  const uint64_t n = n_dev ? min(*n_dev, n_host) : n_host;
-  const uint64_t base = (uint64_t)blockIdx.x * kScanTile;
-  T s = 0;
-  for (int k = 0; k < kScanItems; ++k) {
+// Gathers a block's ITEMS * kScanThreads records (all loads of a thread in
+// flight) and leaves their total.
+template <int ITEMS>
+__global__ void __launch_bounds__(kScanThreads) gather_counts_kernel(
+    uint64_t m, const uint32_t* __restrict__ skey, const uint32_t* __restrict__ perm,
+    const uint2* __restrict__ trect, uint32_t* __restrict__ cnt_sorted,
+    uint2* __restrict__ trect_sorted, uint64_t* __restrict__ block_sums) {
+  __shared__ uint64_t wsum[kScanThreads / kWave];
+  const uint64_t base = (uint64_t)blockIdx.x * (ITEMS * kScanThreads);
+  uint64_t s = 0;
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
     const uint64_t i = base + (uint64_t)k * kScanThreads + threadIdx.x;
-    if (i < n) s += (T)ld(i);
+    if (i >= m) continue;
+    uint2 tr;
+    const uint32_t c = kept_tiles(skey[i], perm[i], trect, tr);
+    cnt_sorted[i] = c;
+    trect_sorted[i] = tr;
+    s += c;
   }
-  T total;
-  block_exclusive_scan<T>(s, sh, total);
-  if (threadIdx.x == 0) block_sums[blockIdx.x] = total;
+  for (int o = kWave / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
+  if (threadIdx.x % kWave == 0) wsum[threadIdx.x / kWave] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint64_t t = 0;
+    for (int w = 0; w < kScanThreads / kWave; ++w) t += wsum[w];
+    block_sums[blockIdx.x] = t;
+  }
 }
 
-// Single block: exclusive scan of the block sums in place; total -> *total.
-template <typename T>
-__global__ void __launch_bounds__(kScanThreads) scan_spine_kernel(T* __restrict__ sums, int nb,
-                                                                  T* __restrict__ total_out) {
-  __shared__ T sh[kScanThreads];
-  T carry = 0;
-  for (int base = 0; base < nb; base += kScanThreads) {
-    const int i = base + threadIdx.x;
-    const T v = i < nb ? sums[i] : (T)0;
-    T tot;
-    const T ex = block_exclusive_scan<T>(v, sh, tot);
-    if (i < nb) sums[i] = carry + ex;
-    carry += tot;
-  }
-  if (threadIdx.x == 0 && total_out) *total_out = carry;
-}
-
-// The block's kScanTile elements pass through LDS rows of kScanItems + 1
-// (padded against bank conflicts) so that global loads and stores are
-// coalesced while each thread scans kScanItems consecutive elements.
-template <typename T, typename Load>
-__global__ void __launch_bounds__(kScanThreads) scan_down_kernel(Load ld, const uint64_t* n_dev,
-                                                                 uint64_t n_host,
-                                                                 const T* __restrict__ block_base,
-                                                                 T* __restrict__ out) {
+// Exclusive scan of cnt into out.  A block adds up the sums (`per` of them for
+// each scan block) in front of it by itself, which costs less than a launch
+// between the two kernels.  Its kScanTile elements
+// pass through LDS rows of kScanItems + 1 (padded against bank conflicts) so
+// that global loads and stores are coalesced while each thread scans
+// kScanItems consecutive elements.
+__global__ void __launch_bounds__(kScanThreads) scan_down_kernel(
+    const uint32_t* __restrict__ cnt, uint64_t n, const uint64_t* __restrict__ block_sums,
+    unsigned per, uint64_t* __restrict__ out, uint64_t* __restrict__ total) {
   constexpr int kRow = kScanItems + 1;
-  __shared__ T sh[kScanThreads];
-  __shared__ T stage[kScanThreads * kRow];
-  const uint64_t n = n_dev ? min(*n_dev, n_host) : n_host;
+  __shared__ uint64_t wsum[kScanThreads / kWave];
+  __shared__ uint64_t stage[kScanThreads * kRow];
   const uint64_t b0 = (uint64_t)blockIdx.x * kScanTile;
+#pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     const int e = k * kScanThreads + (int)threadIdx.x;  // element of the tile
     const uint64_t i = b0 + (uint64_t)e;
-    stage[(e / kScanItems) * kRow + e % kScanItems] = i < n ? (T)ld(i) : (T)0;
+    stage[(e / kScanItems) * kRow + e % kScanItems] = i < n ? (uint64_t)cnt[i] : 0u;
   }
-  __syncthreads();
-  T v[kScanItems];
-  T s = 0;
+  uint64_t front = 0, base, all;
+  for (unsigned b = threadIdx.x; b < blockIdx.x * per; b += kScanThreads) front += block_sums[b];
+  block_scan_excl<uint64_t>(front, wsum, base);  // (its barriers also cover stage)
+  uint64_t v[kScanItems];
+  uint64_t s = 0;
   for (int k = 0; k < kScanItems; ++k) {
     v[k] = stage[threadIdx.x * kRow + k];
     s += v[k];
   }
-  T total;
-  T run = block_exclusive_scan<T>(s, sh, total) + block_base[blockIdx.x];
+  uint64_t run = block_scan_excl<uint64_t>(s, wsum, all) + base;
   for (int k = 0; k < kScanItems; ++k) {
     stage[threadIdx.x * kRow + k] = run;
     run += v[k];
   }
   __syncthreads();
+#pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     const int e = k * kScanThreads + (int)threadIdx.x;
     const uint64_t i = b0 + (uint64_t)e;
     if (i < n) out[i] = stage[(e / kScanItems) * kRow + e % kScanItems];
   }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = base + all;
 }
 
-// Note: scan_reduce sums a strided set of kScanTile elements and scan_down a
-// thread-contiguous set; both cover exactly the block's kScanTile elements,
-// so the block totals agree.
+// One workgroup: the scan of up to kScanFewThreads * 16 counts, 16 or fewer
+// consecutive ones per thread.
+constexpr int kScanFewThreads = 1024;
+__global__ void __launch_bounds__(kScanFewThreads) scan_few_kernel(
+    const uint32_t* __restrict__ cnt, uint32_t n, uint64_t* __restrict__ out,
+    uint64_t* __restrict__ total) {
+  __shared__ uint64_t wsum[kScanFewThreads / kWave];
+  const uint32_t per = ((n + kScanFewThreads - 1) / kScanFewThreads + 3) & ~3u;
+  const uint32_t i0 = threadIdx.x * per;
+  uint32_t v[16];
+  uint64_t s = 0, all;
+#pragma unroll
+  for (uint32_t q = 0; q < 4; ++q) {
+    uint4 x = make_uint4(0u, 0u, 0u, 0u);
+    const uint32_t i = i0 + 4 * q;
+    if (4 * q < per) {
+      if (i + 4 <= n) {
+        x = *reinterpret_cast<const uint4*>(cnt + i);  // i % 4 == 0
+      } else {
+        if (i < n) x.x = cnt[i];
+        if (i + 1 < n) x.y = cnt[i + 1];
+        if (i + 2 < n) x.z = cnt[i + 2];
+      }
+    }
+    v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+  }
+#pragma unroll
+  for (int k = 0; k < 16; ++k) s += v[k];
+  uint64_t run = block_scan_excl<uint64_t>(s, wsum, all);
+#pragma unroll
+  for (uint32_t k = 0; k < 16; ++k) {
+    if (k < per && i0 + k < n) out[i0 + k] = run;
+    run += v[k];
+  }
+  if (threadIdx.x == 0) *total = all;
+}
 
 // ---------------------------------------------------------------------------
 // Stable LSD radix pass over the digit of `width` <= 10 bits at `shift`.
@@ -193,48 +245,82 @@ __device__ __forceinline__ unsigned xcd_block(unsigned bid, unsigned per) {
   return (bid % kXcds) * per + bid / kXcds;
 }
 
-// Exclusive scan of one value per thread over a block of blockDim.x threads
-// (a multiple of 64, at most 1024); wsum holds 16 values.
-template <typename T>
-__device__ __forceinline__ T block_scan_excl(T v, T* wsum, T& total) {
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  const int nw = blockDim.x / kWave;
-  T x = v;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const T y = __shfl_up(x, o, kWave);
-    if (lane >= o) x += y;
-  }
-  if (lane == kWave - 1) wsum[w] = x;
-  __syncthreads();
-  T base = 0, tot = 0;
-  for (int k = 0; k < nw; ++k) {
-    const T s = wsum[k];
-    if (k < w) base += s;
-    tot += s;
-  }
-  __syncthreads();
-  total = tot;
-  return base + x - v;
-}
-
 template <int WAVES>
 struct RadixShape {
   static constexpr int kThreads = WAVES * kWave;
   static constexpr int kTile = kThreads * kSortRounds;  // keys per block
 };
 
+// Where a pass reads its (key, value) pairs.  kPer: keys per 16-byte load.
+template <typename K>
+struct StoredPairs {  // K: uint32_t, or uint16_t (tile ids below 2^16)
+  using KeyT = K;
+  static constexpr int kPer = 16 / (int)sizeof(K);
+  const K* __restrict__ keys;
+  const uint32_t* __restrict__ vals;
+  __device__ uint32_t key(uint64_t i) const { return keys[i]; }
+  __device__ uint32_t val(uint64_t i) const { return vals[i]; }
+  __device__ void load(uint64_t i, uint32_t (&k)[kPer]) const {  // i % kPer == 0
+    union {
+      uint4 v;
+      K k[kPer];
+    } u;
+    u.v = *reinterpret_cast<const uint4*>(keys + i);
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) k[t] = u.k[t];
+  }
+};
+
+// The records by size class, 0 for no key and else 1 + floor(log2 of the key
+// count): the keys come from the counts and the values are the indices, so
+// neither is stored.
+struct SizeClasses {
+  using KeyT = uint32_t;
+  static constexpr int kPer = 4;
+  const uint32_t* __restrict__ ntiles;
+  __device__ static uint32_t of(uint32_t c) { return c == 0 ? 0u : 32u - (uint32_t)__clz(c); }
+  __device__ uint32_t key(uint64_t i) const { return of(ntiles[i]); }
+  __device__ uint32_t val(uint64_t i) const { return (uint32_t)i; }
+  __device__ void load(uint64_t i, uint32_t (&k)[kPer]) const {
+    const uint4 v = *reinterpret_cast<const uint4*>(ntiles + i);
+    k[0] = of(v.x); k[1] = of(v.y); k[2] = of(v.z); k[3] = of(v.w);
+  }
+};
+constexpr int kClassBits = 6;  // classes 0 .. 32
+
+// Where a pass leaves its pairs: the class order keeps the values only, and
+// the position of the first key at or above `mark` (the pass's count n if
+// there is none) unless `first` is NULL.
+template <typename K>
+struct StorePairs {
+  K* __restrict__ keys;
+  uint32_t* __restrict__ vals;
+  __device__ void put(uint32_t i, uint32_t k, uint32_t v) const {
+    keys[i] = (K)k;
+    vals[i] = v;
+  }
+  __device__ void start(uint32_t, uint32_t) const {}
+};
+struct StoreOrder {
+  uint32_t* __restrict__ vals;
+  uint32_t mark;
+  uint32_t* first;
+  __device__ void put(uint32_t i, uint32_t, uint32_t v) const { vals[i] = v; }
+  __device__ void start(uint32_t d, uint32_t at) const {
+    if (first && d == mark) *first = at;
+  }
+};
+
 // Digit counts of one block's keys.  A count does not depend on the order,
 // so each thread loads 16 bytes of keys at once and bumps its wave's LDS
-// counters with atomics; the wave histograms are summed.  KeyT is uint32_t
-// or uint16_t (tile ids below 2^16).
-template <int BINS, int WAVES, typename KeyT>
+// counters with atomics; the wave histograms are summed.
+template <int BINS, int WAVES, typename Load>
 __global__ void __launch_bounds__(256) radix_hist_kernel(
-    const KeyT* __restrict__ keys, const uint64_t* n_dev, uint64_t n_host, int shift,
+    Load in, const uint64_t* n_dev, uint64_t n_host, int shift,
     int width, uint32_t* __restrict__ hist /* [nblocks][2^width] */) {
   constexpr int kTile = RadixShape<WAVES>::kTile;
-  constexpr int kHW = 256 / kWave;             // waves of this kernel
-  constexpr int kPer = 16 / (int)sizeof(KeyT);  // keys per 16-byte load
+  constexpr int kHW = 256 / kWave;  // waves of this kernel
+  constexpr int kPer = Load::kPer;
   __shared__ uint32_t wcnt[kHW][BINS];
   const uint64_t n = n_dev ? min(*n_dev, n_host) : n_host;
   const int bins = 1 << width;
@@ -248,16 +334,13 @@ __global__ void __launch_bounds__(256) radix_hist_kernel(
   for (int j = 0; j < kTile / (kPer * 256); ++j) {
     const uint64_t i = bbase + kPer * ((uint64_t)threadIdx.x + (uint64_t)j * 256);
     if (i + kPer <= n) {
-      union {
-        uint4 v;
-        KeyT k[kPer];
-      } u;
-      u.v = *reinterpret_cast<const uint4*>(keys + i);  // i % kPer == 0
+      uint32_t k[kPer];
+      in.load(i, k);
 #pragma unroll
-      for (int t = 0; t < kPer; ++t) atomicAdd(&cw[((uint32_t)u.k[t] >> shift) & mask], 1u);
+      for (int t = 0; t < kPer; ++t) atomicAdd(&cw[(k[t] >> shift) & mask], 1u);
     } else {
       for (uint64_t t = i; t < n && t < i + kPer; ++t)
-        atomicAdd(&cw[((uint32_t)keys[t] >> shift) & mask], 1u);
+        atomicAdd(&cw[(in.key(t) >> shift) & mask], 1u);
     }
   }
   __syncthreads();
@@ -374,17 +457,16 @@ struct ScatterLds {
 // (global start of digit d) + (position inside the block's run of digit d).
 // The combine folds the block-local digit starts into the waves' bases and
 // the global offsets, so that each key reads one LDS word on its way into
-// the staging rows and one on its way out.
-template <int BINS, int WAVES, typename KeyT>
+// the staging rows and one on its way out.  offs: the global starts of the
+// DPT digits that this thread combines.
+template <int BINS, int WAVES, int DPT, typename Store>
 __device__ __forceinline__ void rank_and_scatter(ScatterLds<BINS, WAVES>& L,
                                                  const uint32_t (&key)[kSortRounds],
                                                  const uint32_t (&val)[kSortRounds],
                                                  uint32_t nkeys, int shift, int width,
-                                                 const uint32_t* __restrict__ offs_row,
-                                                 KeyT* __restrict__ keys_out,
-                                                 uint32_t* __restrict__ vals_out) {
+                                                 const uint32_t (&offs)[DPT],
+                                                 const Store& out) {
   constexpr int kThreads = RadixShape<WAVES>::kThreads;
-  constexpr int DPT = (BINS + kThreads - 1) / kThreads;  // digits per thread in the combine
   static_assert(BINS == 256 || BINS == kMaxBins, "8- or 10-bit digit counters");
   constexpr int kBinBits = BINS == 256 ? 8 : kMaxDigitBits;
   const int bins = 1 << width;
@@ -437,7 +519,7 @@ __device__ __forceinline__ void rank_and_scatter(ScatterLds<BINS, WAVES>& L,
       const int d = threadIdx.x * DPT + j;
       if (d < bins) {
         for (int ww = 0; ww < WAVES; ++ww) L.wcnt[ww][d] += base;
-        L.gofs[d] = offs_row[d] - base;  // mod 2^32: the output index adds base back
+        L.gofs[d] = offs[j] - base;  // mod 2^32: the output index adds base back
       }
       base += tot[j];
     }
@@ -480,8 +562,7 @@ __device__ __forceinline__ void rank_and_scatter(ScatterLds<BINS, WAVES>& L,
     for (int k = 0; k < kSortRounds; ++k) {
       const uint32_t idx = threadIdx.x + (uint32_t)k * kThreads;
       const uint32_t dst = L.gofs[__builtin_amdgcn_ubfe(kk[k], shift, width)] + idx;
-      keys_out[dst] = (KeyT)kk[k];
-      vals_out[dst] = vv[k];
+      out.put(dst, kk[k], vv[k]);
     }
   } else {
 #pragma unroll
@@ -490,21 +571,23 @@ __device__ __forceinline__ void rank_and_scatter(ScatterLds<BINS, WAVES>& L,
       if (idx < nkeys) {
         const uint32_t kk = L.sk[idx];
         const uint32_t dst = L.gofs[__builtin_amdgcn_ubfe(kk, shift, width)] + idx;
-        keys_out[dst] = (KeyT)kk;
-        vals_out[dst] = L.sv[idx];
+        out.put(dst, kk, L.sv[idx]);
       }
     }
   }
 }
 
-template <int BINS, int WAVES, typename KeyT>
+// offsets: the block-major digit counts, scanned by the column kernels or
+// (FOLD) as the histogram left them.  With FOLD a block walks down the whole
+// columns itself: the counts in front of it and the digit totals, whose scan
+// over the digits completes the starts.
+template <int BINS, int WAVES, bool FOLD, typename Load, typename Store>
 __global__ void __launch_bounds__(WAVES * kWave) radix_scatter_kernel(
-    const KeyT* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
-    const uint64_t* n_dev, uint64_t n_host, int shift, int width, unsigned nb, unsigned per,
-    const uint32_t* __restrict__ offsets /* scanned [nblocks][2^width] */,
-    KeyT* __restrict__ keys_out, uint32_t* __restrict__ vals_out) {
+    Load in, const uint64_t* n_dev, uint64_t n_host, int shift, int width, unsigned nb,
+    unsigned per, const uint32_t* __restrict__ offsets /* [nblocks][2^width] */, Store out) {
   constexpr int kThreads = RadixShape<WAVES>::kThreads;
   constexpr int kTile = RadixShape<WAVES>::kTile;
+  constexpr int DPT = (BINS + kThreads - 1) / kThreads;  // digits per thread in the combine
   __shared__ ScatterLds<BINS, WAVES> L;
   const unsigned b = xcd_block(blockIdx.x, per);
   if (b >= nb) return;  // padding workgroup: before any barrier
@@ -518,12 +601,159 @@ __global__ void __launch_bounds__(WAVES * kWave) radix_scatter_kernel(
 #pragma unroll
   for (int k = 0; k < kSortRounds; ++k) {
     const uint32_t i = wbase + (uint32_t)k * kWave + lane;
-    key[k] = i < nkeys ? (uint32_t)keys_in[bbase + i] : 0u;
-    val[k] = i < nkeys ? vals_in[bbase + i] : 0u;
+    key[k] = i < nkeys ? in.key(bbase + i) : 0u;
+    val[k] = i < nkeys ? in.val(bbase + i) : 0u;
   }
+  const unsigned bins = 1u << width;
+  const unsigned d0 = threadIdx.x * DPT;
+  uint32_t offs[DPT];
+  if constexpr (FOLD) {
+    constexpr int kBatch = kColBatch / DPT;
+    uint32_t tot[DPT], mine = 0;
+#pragma unroll
+    for (int j = 0; j < DPT; ++j) offs[j] = tot[j] = 0;
+    if (d0 < bins) {  // bins % DPT == 0: DPT is 1, or 4 with 512 digits or more
+      for (unsigned r0 = 0; r0 < nb; r0 += kBatch) {
+        uint32_t v[kBatch][DPT];
+#pragma unroll
+        for (int r = 0; r < kBatch; ++r)
+#pragma unroll
+          for (int j = 0; j < DPT; ++j)
+            v[r][j] = r0 + r < nb ? offsets[(uint64_t)(r0 + r) * bins + d0 + j] : 0u;
+#pragma unroll
+        for (int r = 0; r < kBatch; ++r)
+#pragma unroll
+          for (int j = 0; j < DPT; ++j) {
+            tot[j] += v[r][j];
+            offs[j] += r0 + r < b ? v[r][j] : 0u;
+          }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < DPT; ++j) mine += tot[j];
+    uint32_t all;
+    uint32_t run = block_scan_excl<uint32_t>(mine, L.wsum, all);
+#pragma unroll
+    for (int j = 0; j < DPT; ++j) {
+      offs[j] += run;
+      run += tot[j];
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < DPT; ++j)
+      offs[j] = d0 + j < bins ? offsets[(uint64_t)b * bins + d0 + j] : 0u;
+  }
+  if (b == 0)
+#pragma unroll
+    for (int j = 0; j < DPT; ++j) out.start(d0 + j, offs[j]);
   __syncthreads();
-  rank_and_scatter<BINS, WAVES, KeyT>(L, key, val, nkeys, shift, width,
-                                offsets + (uint64_t)b * (1u << width), keys_out, vals_out);
+  rank_and_scatter<BINS, WAVES, DPT, Store>(L, key, val, nkeys, shift, width, offs, out);
+}
+
+// ---------------------------------------------------------------------------
+// Few elements: the position of an element in the stable order is the number
+// of elements in front of it, counted outright.  A workgroup takes 64
+// elements, one per lane, and each of its 16 waves counts over a sixteenth
+// of all keys, which arrive as scalars (two VALU instructions per pair); the
+// counts meet in LDS and the first wave moves the elements.
+//
+// An element precedes this lane's if its key is <= `le` (elements with a lower
+// index) or < `lt` (elements with a higher one).
+// ---------------------------------------------------------------------------
+constexpr int kRankWaves = 16;
+constexpr unsigned kRankBatch = 16;  // keys per scalar load
+
+// The number of elements in front of this lane's element blockIdx.x * 64 +
+// lane, valid in the first wave.
+template <typename KeyT>
+__device__ __forceinline__ uint32_t rank_of(const KeyT* __restrict__ keys, uint32_t n, uint32_t le,
+                                            uint32_t lt) {
+  __shared__ uint32_t part[kRankWaves][kWave];
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const uint32_t own = blockIdx.x * kWave;
+  const uint32_t chunk = ((n + kRankWaves - 1) / kRankWaves + kRankBatch - 1) / kRankBatch *
+                         kRankBatch;
+  const uint32_t j1 = min(n, (w + 1) * chunk);
+  uint32_t c = 0;
+  uint32_t j = w * chunk;
+  for (; j + kRankBatch <= j1; j += kRankBatch) {
+    // (the buffers are 16-byte aligned and j % 16 == 0)
+    constexpr unsigned kPack = 4 / sizeof(KeyT);
+    uint32_t k[kRankBatch];
+    const uint32_t* words = reinterpret_cast<const uint32_t*>(keys + j);
+#pragma unroll
+    for (unsigned t = 0; t < kRankBatch; ++t)
+      k[t] = kPack == 1 ? words[t] : words[t / kPack] >> (16 * (t % kPack)) & 0xffffu;
+    if (j + kRankBatch <= own) {
+#pragma unroll
+      for (unsigned t = 0; t < kRankBatch; ++t) c += k[t] <= le ? 1u : 0u;
+    } else if (j >= own + kWave) {
+#pragma unroll
+      for (unsigned t = 0; t < kRankBatch; ++t) c += k[t] < lt ? 1u : 0u;
+    } else {
+#pragma unroll
+      for (unsigned t = 0; t < kRankBatch; ++t)
+        c += (j + t < own + lane ? k[t] <= le : k[t] < lt) ? 1u : 0u;
+    }
+  }
+  for (; j < j1; ++j) c += (j < own + lane ? keys[j] <= le : keys[j] < lt) ? 1u : 0u;
+  part[w][lane] = c;
+  __syncthreads();
+  uint32_t r = 0;
+#pragma unroll
+  for (int v = 0; v < kRankWaves; ++v) r += part[v][lane];
+  return r;
+}
+
+// Stable sort of min(*n_dev, n_max) pairs (n_dev NULL: n_max).
+template <typename KeyT>
+__global__ void __launch_bounds__(kRankWaves* kWave) rank_pairs_kernel(
+    const KeyT* __restrict__ keys, const uint32_t* __restrict__ vals, const uint64_t* n_dev,
+    uint32_t n_max, KeyT* __restrict__ keys_out, uint32_t* __restrict__ vals_out) {
+  const uint32_t n = n_dev ? (uint32_t)min(*n_dev, (uint64_t)n_max) : n_max;
+  const uint32_t i = blockIdx.x * kWave + (threadIdx.x & (kWave - 1));
+  if (blockIdx.x * kWave >= n) return;  // uniform
+  const uint32_t k = i < n ? (uint32_t)keys[i] : 0u;
+  const uint32_t r = rank_of(keys, n, k, k);
+  if (threadIdx.x >= kWave || i >= n) return;
+  keys_out[r] = (KeyT)k;
+  vals_out[r] = vals[i];
+}
+
+// The depth sort, with each record's tile rect and count (kept_tiles).
+__global__ void __launch_bounds__(kRankWaves* kWave) rank_records_kernel(
+    const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals, uint32_t n,
+    const uint2* __restrict__ trect, uint32_t* __restrict__ keys_out,
+    uint32_t* __restrict__ vals_out, uint32_t* __restrict__ cnt_sorted,
+    uint2* __restrict__ trect_sorted) {
+  const uint32_t i = blockIdx.x * kWave + (threadIdx.x & (kWave - 1));
+  const uint32_t k = i < n ? keys[i] : 0u;
+  const uint32_t r = rank_of(keys, n, k, k);
+  if (threadIdx.x >= kWave || i >= n) return;
+  const uint32_t v = vals[i];
+  uint2 tr;
+  const uint32_t c = kept_tiles(k, v, trect, tr);
+  keys_out[r] = k;
+  vals_out[r] = v;
+  cnt_sorted[r] = c;
+  trect_sorted[r] = tr;
+}
+
+// The class order.  Lane n stands for the mark: the records whose count lies
+// below 2^(mark - 1) are the ones of a lower class.
+__global__ void __launch_bounds__(kRankWaves* kWave) rank_classes_kernel(
+    const uint32_t* __restrict__ ntiles, uint32_t n, StoreOrder out) {
+  const uint32_t i = blockIdx.x * kWave + (threadIdx.x & (kWave - 1));
+  const uint32_t k = i < n ? ntiles[i] : 0u;
+  // bits of the count set to ones: the largest count of its class
+  uint32_t le = k ? 0xffffffffu >> __clz(k) : 0u;
+  const uint32_t lt = k ? (le >> 1) + 1u : 0u;
+  if (i == n) le = out.mark ? (1u << (out.mark - 1)) - 1u : 0u;
+  const uint32_t r = rank_of(ntiles, n, le, lt);
+  if (threadIdx.x >= kWave) return;
+  if (i < n) out.put(r, 0u, i);
+  if (i == n) out.start(out.mark, r);
 }
 
 // q = floor(a / b), r = a - q b for b >= 1: a float estimate corrected by
@@ -651,52 +881,29 @@ __global__ void __launch_bounds__(256) keygen_kernel(
   }
 }
 
-// [start, end) of every tile's run in the sorted keys (ranges pre-zeroed).
-// Each thread scans 32 consecutive keys (four 16-byte loads of 16-bit keys,
-// eight of 32-bit ones) plus the key just before them; a run boundary writes
-// the start of the new tile and the end of the previous one.
-constexpr int kRangeItems = 32;
-
+// [start, end) of every tile's run in the sorted keys, (0, 0) if it has none.
+// A lane finds its tile's start (the number of keys below it) by binary
+// search, and the next lane's start is its end; a wave covers 63 tiles.
 template <typename KeyT>
 __global__ void __launch_bounds__(256) ranges_kernel(const KeyT* __restrict__ keys,
                                                      const uint64_t* k_dev, uint64_t capacity,
                                                      uint2* __restrict__ ranges,
                                                      uint32_t n_tiles) {
-  constexpr int kPer = 16 / (int)sizeof(KeyT);  // keys per 16-byte load
-  static_assert(kRangeItems % kPer == 0, "whole 16-byte loads");
-  const uint64_t K = *k_dev < capacity ? *k_dev : capacity;
-  const uint64_t i0 = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * kRangeItems;
-  if (i0 >= K) return;
-  uint32_t k[kRangeItems];
-  if (i0 + kRangeItems <= K) {
-#pragma unroll
-    for (int q = 0; q < kRangeItems / kPer; ++q) {
-      union {
-        uint4 v;
-        KeyT k[kPer];
-      } u;
-      u.v = *reinterpret_cast<const uint4*>(keys + i0 + q * kPer);
-#pragma unroll
-      for (int t = 0; t < kPer; ++t) k[q * kPer + t] = u.k[t];
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < kRangeItems; ++j) k[j] = i0 + j < K ? (uint32_t)keys[i0 + j] : 0xffffffffu;
+  const uint32_t K = (uint32_t)(*k_dev < capacity ? *k_dev : capacity);
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint64_t t = ((uint64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave) * (kWave - 1) +
+                     lane;
+  uint32_t lo = 0, len = K;
+  while (len > 0) {  // uniform: len does not depend on the outcomes
+    const uint32_t half = len / 2;
+    // keys[lo + half] is inside [lo, lo + len)
+    const bool right = (uint64_t)keys[lo + half] < t;
+    lo = right ? lo + half + (len & 1 ? 1u : 0u) : lo;
+    len = half;
   }
-  uint32_t prev = i0 == 0 ? 0xffffffffu : (uint32_t)keys[i0 - 1];
-#pragma unroll
-  for (int j = 0; j < kRangeItems; ++j) {
-    const uint64_t i = i0 + j;
-    if (i >= K) break;
-    const uint32_t t = k[j];
-    if (t != prev) {
-      if (t < n_tiles) ranges[t].x = (uint32_t)i;
-      if (prev < n_tiles) ranges[prev].y = (uint32_t)i;
-    }
-    prev = t;
-  }
-  const uint64_t last = i0 + kRangeItems - 1 < K - 1 ? i0 + kRangeItems - 1 : K - 1;
-  if (last == K - 1 && prev < n_tiles) ranges[prev].y = (uint32_t)K;
+  const uint32_t end = __shfl_down(lo, 1, kWave);
+  if (lane < kWave - 1 && t < n_tiles)
+    ranges[t] = end > lo ? make_uint2(lo, end) : make_uint2(0u, 0u);
 }
 
 // Plain copy, one 16-byte element per thread: the reference for the
@@ -776,7 +983,9 @@ size_t radix_hist_elems(uint64_t n_max, int bits) {
   const int wmax = bits > 0 ? max_digit_width(bits) : 8;
   return ((size_t)1 << std::max(wmax, 8)) * blocks_for(n_max, RadixShape<4>::kTile);
 }
-size_t scan_block_elems(uint64_t n_max) { return blocks_for(n_max, kScanTile) + 1; }
+size_t scan_block_elems(uint64_t n_max) {
+  return blocks_for(n_max, (n_max > kGatherBig ? kScanItems : kScanFew) * kScanThreads);
+}
 // u32 elements of the column scan's chunk sums for up to n_max keys (an upper
 // bound for every smaller count as well)
 size_t radix_scan_elems(uint64_t n_max, int bits) {
@@ -800,52 +1009,102 @@ static void radix_offsets(hipStream_t st, uint32_t* hist, unsigned nb, int width
                      scan_tmp, nc);
 }
 
-template <int BINS, int WAVES, typename KeyT>
-static void radix_pass(hipStream_t st, const KeyT* ki, const uint32_t* vi, KeyT* ko,
-                       uint32_t* vo, const uint64_t* n_dev, uint64_t n_max, int shift, int width,
-                       uint32_t* hist, uint32_t* scan_tmp) {
+// Up to this many counts every scatter block walks down the columns itself,
+// which takes the three column kernels out of the pass: with 256 digits, 8
+// blocks 2 + 9 us (histogram + scatter) against 2 + 5 + 8, 32 blocks 5 + 10
+// against 4 + 8 + 8, 125 blocks 5 + 16 against 5 + 13 + 10, and three launches
+// saved; with 1024 digits the walks have overtaken the kernels at a few
+// hundred blocks (4 + 32 against 3 + 9 + 14).
+constexpr uint64_t kFoldCounts = 1u << 16;
+
+template <int BINS, int WAVES, typename Load, typename Store>
+static void radix_pass(hipStream_t st, Load in, Store out, const uint64_t* n_dev, uint64_t n_max,
+                       int shift, int width, uint32_t* hist, uint32_t* scan_tmp) {
   const unsigned nb = blocks_for(n_max, RadixShape<WAVES>::kTile);
   const unsigned per = (nb + kXcds - 1) / kXcds;
-  hipLaunchKernelGGL((radix_hist_kernel<BINS, WAVES, KeyT>), dim3(nb), dim3(256), 0, st, ki,
+  const dim3 grid(per * kXcds), block(RadixShape<WAVES>::kThreads);
+  hipLaunchKernelGGL((radix_hist_kernel<BINS, WAVES, Load>), dim3(nb), dim3(256), 0, st, in,
                      n_dev, n_max, shift, width, hist);
+  if (((uint64_t)nb << width) <= kFoldCounts) {
+    hipLaunchKernelGGL((radix_scatter_kernel<BINS, WAVES, true, Load, Store>), grid, block, 0, st,
+                       in, n_dev, n_max, shift, width, nb, per, hist, out);
+    return;
+  }
   radix_offsets(st, hist, nb, width, scan_tmp);
-  hipLaunchKernelGGL((radix_scatter_kernel<BINS, WAVES, KeyT>), dim3(per * kXcds),
-                     dim3(RadixShape<WAVES>::kThreads), 0, st, ki, vi, n_dev, n_max, shift,
-                     width, nb, per, hist, ko, vo);
+  hipLaunchKernelGGL((radix_scatter_kernel<BINS, WAVES, false, Load, Store>), grid, block, 0, st,
+                     in, n_dev, n_max, shift, width, nb, per, hist, out);
 }
 
 // Large passes take 8-wave blocks (longer digit runs per block); small ones
 // and 10-bit digits (LDS) take 4-wave blocks.
 constexpr uint64_t kBigPass = 1ull << 24;
 
-template <typename KeyT>
-static void radix_pass_any(hipStream_t st, const KeyT* ki, const uint32_t* vi, KeyT* ko,
-                           uint32_t* vo, const uint64_t* n_dev, uint64_t n_max, int shift,
-                           int width, uint32_t* hist, uint32_t* scan_tmp) {
+template <typename Load, typename Store>
+static void radix_pass_any(hipStream_t st, Load in, Store out, const uint64_t* n_dev,
+                           uint64_t n_max, int shift, int width, uint32_t* hist,
+                           uint32_t* scan_tmp) {
   if (width > 8)
-    radix_pass<kMaxBins, 4>(st, ki, vi, ko, vo, n_dev, n_max, shift, width, hist, scan_tmp);
+    radix_pass<kMaxBins, 4>(st, in, out, n_dev, n_max, shift, width, hist, scan_tmp);
   else if (n_max >= kBigPass)
-    radix_pass<256, 8>(st, ki, vi, ko, vo, n_dev, n_max, shift, width, hist, scan_tmp);
+    radix_pass<256, 8>(st, in, out, n_dev, n_max, shift, width, hist, scan_tmp);
   else
-    radix_pass<256, 4>(st, ki, vi, ko, vo, n_dev, n_max, shift, width, hist, scan_tmp);
+    radix_pass<256, 4>(st, in, out, n_dev, n_max, shift, width, hist, scan_tmp);
 }
 
-// Stable sort of (keys, vals) by the key bits [0, bits), 8-bit digits.  The
-// element count is *n_dev (<= n_max).  Result ends in (keys_a, vals_a) if the
-// number of passes is even, else in (keys_b, vals_b); returns true if in b.
-bool launch_radix_sort(hipStream_t st, uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
-                       uint32_t* vals_b, const uint64_t* n_dev, uint64_t n_max, int bits,
-                       uint32_t* hist, uint32_t* scan_tmp) {
-  if (n_max == 0) return false;
-  bool in_b = false;
-  for (int shift = 0; shift < bits; shift += 8) {
-    const int width = std::min(8, bits - shift);
-    radix_pass_any<uint32_t>(st, in_b ? keys_b : keys_a, in_b ? vals_b : vals_a,
-                             in_b ? keys_a : keys_b, in_b ? vals_a : vals_b, n_dev, n_max, shift,
-                             width, hist, scan_tmp);
-    in_b = !in_b;
+// Up to here the order comes from counting pairs.  Its time grows with the
+// square of the count, that of the passes hardly at all below 10^5.  Measured
+// (us of kernel time, counting against the two-launch passes; each launch
+// saved is worth 2 to 3 us more): records 1000: 9 (2 launches) against 50
+// (10), 8000: 23 / 61, 16000: 40 / 61, 32000: 86 / 62; tile keys, two passes
+// of 4 launches, 8000: 10 / 24; size classes 4000: 9 / 15 (2 launches), 8000:
+// 16 / 14, 16000: 27 / 15.
+constexpr uint64_t kRankRecords = 16384;
+constexpr uint64_t kRankKeys = 8192;
+constexpr uint64_t kRankClasses = 8192;
+
+// Stable sort of the records (keys, vals) by their 32 depth bits, 8-bit
+// digits, then launch_offsets_scan over the sorted records.  Ends in
+// (keys_a, vals_a).
+void launch_depth_sort(hipStream_t st, uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
+                       uint32_t* vals_b, uint64_t m, uint32_t* hist, uint32_t* scan_tmp) {
+  if (m == 0) return;
+  for (int shift = 0; shift < 32; shift += 16) {
+    radix_pass_any(st, StoredPairs<uint32_t>{keys_a, vals_a},
+                   StorePairs<uint32_t>{keys_b, vals_b}, nullptr, m, shift, 8, hist, scan_tmp);
+    radix_pass_any(st, StoredPairs<uint32_t>{keys_b, vals_b},
+                   StorePairs<uint32_t>{keys_a, vals_a}, nullptr, m, shift + 8, 8, hist,
+                   scan_tmp);
   }
-  return in_b;
+}
+
+bool rank_records(uint64_t m) { return m > 0 && m <= kRankRecords; }
+
+void launch_rank_records(hipStream_t st, const uint32_t* keys, const uint32_t* vals, uint64_t m,
+                         const uint2* trect, uint32_t* keys_out, uint32_t* vals_out,
+                         uint32_t* cnt_sorted, uint2* trect_sorted, uint64_t* offsets,
+                         uint64_t* total) {
+  hipLaunchKernelGGL(rank_records_kernel, dim3(blocks_for(m, kWave)), dim3(kRankWaves * kWave), 0,
+                     st, keys, vals, (uint32_t)m, trect, keys_out, vals_out, cnt_sorted,
+                     trect_sorted);
+  hipLaunchKernelGGL(scan_few_kernel, dim3(1), dim3(kScanFewThreads), 0, st, cnt_sorted,
+                     (uint32_t)m, offsets, total);
+}
+
+// The records in ascending order of size class; *first (unless NULL)
+// receives the position of the first record of class `mark` or above, m if
+// there is none.
+void launch_class_order(hipStream_t st, uint64_t m, const uint32_t* ntiles, uint32_t* order,
+                        uint32_t mark, uint32_t* first, uint32_t* hist, uint32_t* scan_tmp) {
+  if (m == 0) {
+    if (first) launch_fill_u32(st, first, 1, 0u);
+    return;
+  }
+  const StoreOrder out{order, mark, first};
+  if (m <= kRankClasses)
+    hipLaunchKernelGGL(rank_classes_kernel, dim3(blocks_for(m + 1, kWave)),
+                       dim3(kRankWaves * kWave), 0, st, ntiles, (uint32_t)m, out);
+  else
+    radix_pass_any(st, SizeClasses{ntiles}, out, nullptr, m, 0, kClassBits, hist, scan_tmp);
 }
 
 bool tile_keys_16bit(int bits) { return bits <= 16; }
@@ -869,14 +1128,20 @@ template <typename KeyT>
 static bool tile_sort_t(hipStream_t st, KeyT* keys_a, uint32_t* vals_a, KeyT* keys_b,
                         uint32_t* vals_b, const uint64_t* k_dev, uint64_t k_max, int bits,
                         uint32_t* hist, uint32_t* scan_tmp) {
+  if (k_max <= kRankKeys) {
+    hipLaunchKernelGGL(rank_pairs_kernel<KeyT>, dim3(blocks_for(k_max, kWave)),
+                       dim3(kRankWaves * kWave), 0, st, keys_a, vals_a, k_dev, (uint32_t)k_max,
+                       keys_b, vals_b);
+    return true;
+  }
   int widths[8];
   const int passes = tile_pass_widths(bits, widths);
   bool in_b = false;
   int shift = 0;
   for (int p = 0; p < passes; ++p) {
-    radix_pass_any<KeyT>(st, in_b ? keys_b : keys_a, in_b ? vals_b : vals_a,
-                         in_b ? keys_a : keys_b, in_b ? vals_a : vals_b, k_dev, k_max, shift,
-                         widths[p], hist, scan_tmp);
+    radix_pass_any(st, StoredPairs<KeyT>{in_b ? keys_b : keys_a, in_b ? vals_b : vals_a},
+                   StorePairs<KeyT>{in_b ? keys_a : keys_b, in_b ? vals_a : vals_b}, k_dev, k_max,
+                   shift, widths[p], hist, scan_tmp);
     in_b = !in_b;
     shift += widths[p];
   }
@@ -899,31 +1164,6 @@ bool launch_tile_sort(hipStream_t st, void* keys_a, uint32_t* vals_a, void* keys
                                scan_tmp);
 }
 
-// The tile counts in depth order, cnt_sorted[i] = ntiles[perm[i]], gathered
-// once so that the offsets scan and keygen read them in order, together
-// with the tile rects (keygen's one random read per record happens here, as
-// part of the gather that has to be random anyway).  A record is kept iff its
-// sorted depth key is not the all-ones of a culled record, and a kept
-// record's tile count is the area of its rect (the preprocess writes the two
-// together; a culled record has neither).
-__global__ void __launch_bounds__(256) gather_counts_kernel(uint64_t m,
-                                                            const uint32_t* __restrict__ skey,
-                                                            const uint32_t* __restrict__ perm,
-                                                            const uint2* __restrict__ trect,
-                                                            uint32_t* __restrict__ cnt_sorted,
-                                                            uint2* __restrict__ trect_sorted) {
-  const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= m) return;
-  uint2 tr = make_uint2(0u, 0u);
-  uint32_t c = 0;
-  if (skey[i] != 0xffffffffu) {
-    tr = trect[perm[i]];
-    c = ((tr.x >> 16) - (tr.x & 0xffffu) + 1u) * ((tr.y >> 16) - (tr.y & 0xffffu) + 1u);
-  }
-  cnt_sorted[i] = c;
-  trect_sorted[i] = tr;
-}
-
 // Exclusive scan of the depth-ordered records' tile counts into offsets
 // (u64), total into *total; cnt_sorted[i] and trect_sorted[i] receive the
 // count and the tile rect of record perm[i] (zero for a culled record).
@@ -935,23 +1175,23 @@ void launch_offsets_scan(hipStream_t st, const uint32_t* skey, const uint32_t* p
     launch_fill_u32(st, (uint32_t*)total, 2, 0u);
     return;
   }
-  hipLaunchKernelGGL(gather_counts_kernel, dim3(blocks_for(m, 256)), dim3(256), 0, st, m, skey,
-                     perm, trect, cnt_sorted, trect_sorted);
-  const unsigned sb = blocks_for(m, kScanTile);
-  LoadU32 ld{cnt_sorted};
-  hipLaunchKernelGGL((scan_reduce_kernel<uint64_t, LoadU32>), dim3(sb), dim3(kScanThreads), 0,
-                     st, ld, (const uint64_t*)nullptr, m, block_tmp);
-  hipLaunchKernelGGL((scan_spine_kernel<uint64_t>), dim3(1), dim3(kScanThreads), 0, st,
-                     block_tmp, (int)sb, total);
-  hipLaunchKernelGGL((scan_down_kernel<uint64_t, LoadU32>), dim3(sb), dim3(kScanThreads), 0, st,
-                     ld, (const uint64_t*)nullptr, m, block_tmp, offsets);
+  const bool big = m > kGatherBig;
+  const unsigned items = big ? 16 : kScanFew;
+  const dim3 grid(blocks_for(m, items * kScanThreads)), block(kScanThreads);
+  if (big)
+    hipLaunchKernelGGL(gather_counts_kernel<16>, grid, block, 0, st, m, skey, perm, trect,
+                       cnt_sorted, trect_sorted, block_tmp);
+  else
+    hipLaunchKernelGGL(gather_counts_kernel<kScanFew>, grid, block, 0, st, m, skey, perm, trect,
+                       cnt_sorted, trect_sorted, block_tmp);
+  hipLaunchKernelGGL(scan_down_kernel, dim3(blocks_for(m, kScanTile)), block, 0, st, cnt_sorted,
+                     m, block_tmp, (unsigned)kScanItems / items, offsets, total);
 }
 
 void launch_ranges(hipStream_t st, const void* keys, int bits, const uint64_t* k_dev,
                    uint64_t k_max, uint64_t capacity, uint2* ranges, uint64_t n_tiles) {
-  launch_fill_u32(st, (uint32_t*)ranges, 2 * n_tiles, 0u);
-  if (k_max == 0) return;
-  const dim3 grid(blocks_for(k_max, 256 * kRangeItems));
+  if (n_tiles == 0) return;
+  const dim3 grid(blocks_for(n_tiles, 256 / kWave * (kWave - 1)));
   if (tile_keys_16bit(bits))
     hipLaunchKernelGGL(ranges_kernel<uint16_t>, grid, dim3(256), 0, st,
                        static_cast<const uint16_t*>(keys), k_dev, capacity, ranges,

@@ -1,0 +1,80 @@
+"""The ordering of records and tile keys at the sizes where its method
+changes: counting (up to 16384 records, 8192 tile keys, 8192 records of the
+size classes), passes whose scatter walks the digit columns, and passes with
+column kernels.
+
+- The tile lists are those of a stable sort of the slots by tile in depth
+  order, and the ranges are their bounds.
+- Culled Gaussians appended to a scene take every stage across its line and
+  leave the images and gradients bitwise as they were.
+"""
+import numpy as np
+import pytest
+
+from paper_2411_17660_amd import scenes
+
+pytestmark = pytest.mark.gpu
+
+
+def _scene(n, seed, extra=0, F=1):
+    W, H = 200, 150
+    sc = scenes.tiny_scene(seed=seed, n=n, W=W, H=H, f=160.0, n_frames=F, sh_degree=0, ls_mean=-5.0,
+                           ls_sigma=0.8, opacity_sigma=1.0)
+    if extra:  # not finite: culled in every frame
+        for k in ("means", "log_scales", "quats", "opacity", "sh"):
+            a = getattr(sc, k)
+            pad = np.repeat(a[:1], extra, axis=0)
+            if k == "means":
+                pad = np.full_like(pad, np.nan)
+            setattr(sc, k, np.concatenate([a, pad]))
+    return sc
+
+
+@pytest.fixture(scope="module")
+def rast():
+    from paper_2411_17660_amd.raster import Rasterizer
+    return Rasterizer()
+
+
+@pytest.mark.parametrize("n,F", [(1, 1), (63, 1), (64, 1), (65, 2), (700, 3), (2731, 3),
+                                 (8191, 1), (8193, 1), (16384, 1), (16385, 1), (33000, 2),
+                                 (150000, 2)])
+def test_lists_are_the_stable_order(rast, n, F):
+    from gpu_util import gpu_forward
+    gpu_forward(rast, _scene(n, 5, F=F))
+    L = rast.debug_lists()
+    T = rast.stats()["n_tiles"]
+    keys, vals, nt = L["tile_keys"].astype(np.int64), L["tile_vals"].astype(np.int64), L["ntiles"]
+    assert len(keys) == int(nt.sum())
+    # every record once per tile of its rect
+    np.testing.assert_array_equal(np.bincount(vals, minlength=n * F), nt)
+    # tiles ascend, and inside a tile (depth, record)
+    dk = L["depth_key"].astype(np.int64)[vals]
+    np.testing.assert_array_equal(np.lexsort((vals, dk, keys)), np.arange(len(keys)))
+    want = np.stack([np.searchsorted(keys, np.arange(T)),
+                     np.searchsorted(keys, np.arange(T), side="right")], 1)
+    want[want[:, 0] == want[:, 1]] = 0
+    np.testing.assert_array_equal(L["ranges"].reshape(T, 2), want)
+
+
+@pytest.mark.parametrize("n,extra", [(1, 63), (1, 64), (500, 7692), (500, 7693), (5000, 12000),
+                                     (5000, 300000)])
+def test_culled_records_change_nothing(rast, n, extra):
+    import torch
+    from gpu_util import gpu_forward
+    P = 200 * 150
+    gen = torch.Generator().manual_seed(3)
+    G = [torch.randn(k * P, generator=gen).cuda() for k in (3, 1, 1)]
+    out = []
+    for e in (0, extra):
+        _, *im = gpu_forward(rast, _scene(n, 9, e))
+        g = rast.backward(*G)
+        out.append(([x.clone() for x in im], g))
+    for a, b in zip(out[0][0], out[1][0]):
+        assert torch.equal(a, b)
+    for k, a in out[0][1].items():
+        if k == "twist":  # its sum over the Gaussians runs in waves of their count
+            assert float((a - out[1][1][k]).norm()) <= 1e-6 * float(a.norm())
+        else:
+            assert torch.equal(a, out[1][1][k][:n]), k
+            assert not out[1][1][k][n:].any()
