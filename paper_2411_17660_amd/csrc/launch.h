@@ -118,16 +118,20 @@ void launch_loss_l1(hipStream_t st, int F, int blocks_x, const FrameDesc* frames
                     const float* t_depth, float depth_weight, double* part, float* scale,
                     float* loss, float* g_rgb, float* g_depth, float* g_alpha);
 
-// ssim.hip: rendering loss with SSIM.  tile_sums holds 4 doubles per padded
-// block tile of every plane [F][3][tiles_pad]; part 3 x 3 * total_px doubles
-// (the SSIM map's derivatives A, B, C per colour value); frame_sums [F][4]
-// doubles (gradient scales and loss term per frame).
-int ssim_tiles_pad(int max_w, int max_h);
-void launch_loss_render(hipStream_t st, int F, int tiles_pad, const FrameDesc* frames,
-                        int64_t total_px, const float* rgb, const float* depth,
-                        const float* t_rgb, const float* t_depth, float lambda1, float lambda2,
-                        double* part, double* tile_sums, double* frame_sums, float* loss,
-                        float* ssim, float* g_rgb, float* g_depth, float* g_alpha);
+// ssim.hip: rendering loss with SSIM.  tile_sums holds 4 doubles per pair of
+// waves of every plane [F][3][units]; frame_sums [F][2] doubles (depth
+// gradient scale and loss term per frame).  g_rgb is neither rgb nor t_rgb.
+struct SsimPlan {
+  int chunks;       // rows per pair of waves, in elevens
+  int units;        // blocks per plane of the largest frame
+  int64_t max_px;   // pixels of the largest frame
+};
+SsimPlan ssim_plan(const FrameDesc* host_frames, int F);
+void launch_loss_render(hipStream_t st, int F, const SsimPlan& plan, const FrameDesc* frames,
+                        const float* rgb, const float* depth, const float* t_rgb,
+                        const float* t_depth, float lambda1, float lambda2, double* tile_sums,
+                        double* frame_sums, float* loss, float* ssim, float* g_rgb,
+                        float* g_depth, float* g_alpha);
 
 // densify.hip: ADC statistics of the last backward (grad2d [m][kNG], ntiles
 // [m], record r = f n + g), MCMC position noise and relocation.  src [n]:

@@ -53,7 +53,7 @@ struct gsr_context {
       counters;
   DBuf keys_a, vals_a, keys_b, vals_b, partial, stamp, grad2d;
   DBuf ranges, nproc, t_final, n_last, frames, twist_part, loss_part, loss_scale;
-  DBuf ssim_part, ssim_tiles, ssim_scale;  // rendering loss with SSIM
+  DBuf ssim_rgb, ssim_tiles, ssim_scale;  // rendering loss with SSIM
   DBuf med_pos;                     // per pixel: list position of the median-depth entry
   DBuf dist_aux, spart, sgrad;      // surfels: distortion sums per pixel, per-key and
                                     // per-record gradient sums
@@ -230,7 +230,7 @@ gsr_status gsr_destroy(gsr_context* ctx) {
                   &ctx->grad2d,
                   &ctx->stamp, &ctx->ranges, &ctx->nproc, &ctx->t_final, &ctx->n_last,
                   &ctx->frames, &ctx->twist_part, &ctx->loss_part, &ctx->loss_scale,
-                  &ctx->ssim_part, &ctx->ssim_tiles, &ctx->ssim_scale, &ctx->med_pos,
+                  &ctx->ssim_rgb, &ctx->ssim_tiles, &ctx->ssim_scale, &ctx->med_pos,
                   &ctx->reloc_cnt, &ctx->reloc_rule,
                   &ctx->up_rgb, &ctx->up_depth, &ctx->up_alpha, &ctx->tune_out,
                   &ctx->order_f, &ctx->order_b, &ctx->cls_order, &ctx->dist_aux, &ctx->spart,
@@ -773,23 +773,25 @@ gsr_status gsr_loss_render(gsr_context* ctx, const float* rgb, const float* dept
     if (((uintptr_t)p) & 3u) return fail(ctx, GSR_ERR_INVALID_ARGUMENT, "pointer not 4-aligned");
   hipStream_t st = (hipStream_t)stream;
   GSR_HIP(hipSetDevice(ctx->device));
-  int max_w = 1, max_h = 1;
-  for (const FrameDesc& fd : ctx->last_frames) {
-    max_w = std::max(max_w, (int)fd.width);
-    max_h = std::max(max_h, (int)fd.height);
-  }
-  const int tiles_pad = ssim_tiles_pad(max_w, max_h);
+  const SsimPlan plan = ssim_plan(ctx->last_frames.data(), sv.F);
   if (sv.F > 65535) return fail(ctx, GSR_ERR_UNSUPPORTED, "more than 65535 frames");
   gsr_status rc;
-  if ((rc = ensure(ctx, ctx->ssim_part, (size_t)sv.P * 9 * 8, st))) return rc;
-  if ((rc = ensure(ctx, ctx->ssim_tiles, (size_t)sv.F * 3 * tiles_pad * 4 * 8, st))) return rc;
-  if ((rc = ensure(ctx, ctx->ssim_scale, (size_t)sv.F * 4 * 8, st))) return rc;
+  // the gradient of one pixel needs its neighbours' colours: a g_rgb in the
+  // place of an image is written beside it first
+  const bool in_place = g_rgb == rgb || g_rgb == target_rgb;
+  if (in_place && (rc = ensure(ctx, ctx->ssim_rgb, (size_t)sv.P * 3 * 4, st))) return rc;
+  if ((rc = ensure(ctx, ctx->ssim_tiles, (size_t)sv.F * 3 * plan.units * 4 * 8, st)))
+    return rc;
+  if ((rc = ensure(ctx, ctx->ssim_scale, (size_t)sv.F * 2 * 8, st))) return rc;
   {
     StageTimer t(ctx, st, (sv.set.flags & GSR_FLAG_TIMING) != 0, GSR_STAGE_LOSS);
-    launch_loss_render(st, sv.F, tiles_pad, P<FrameDesc>(ctx->frames), sv.P, rgb, depth,
-                       target_rgb, target_depth, lambda1, lambda2, P<double>(ctx->ssim_part),
-                       P<double>(ctx->ssim_tiles), P<double>(ctx->ssim_scale), loss, ssim,
-                       g_rgb, g_depth, g_alpha);
+    launch_loss_render(st, sv.F, plan, P<FrameDesc>(ctx->frames), rgb, depth, target_rgb,
+                       target_depth, lambda1, lambda2, P<double>(ctx->ssim_tiles),
+                       P<double>(ctx->ssim_scale), loss, ssim,
+                       in_place ? P<float>(ctx->ssim_rgb) : g_rgb, g_depth, g_alpha);
+    if (in_place)
+      GSR_HIP(hipMemcpyAsync(g_rgb, ctx->ssim_rgb.p, (size_t)sv.P * 3 * 4,
+                             hipMemcpyDeviceToDevice, st));
   }
   GSR_HIP(hipGetLastError());
   return GSR_OK;
