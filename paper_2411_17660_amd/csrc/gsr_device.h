@@ -53,6 +53,13 @@ static_assert(sizeof(Record) == 64, "record layout");
 // dopacity, dc0..2, dz.
 constexpr int kNG = 10;
 
+// Where value j of record r of m lies: the centre's gradients (du, dv) of all
+// records first, which the densification statistics read alone, then the
+// other eight of each (64 bytes, aligned).
+__host__ __device__ inline uint64_t grad2d_at(uint64_t r, int j, uint64_t m) {
+  return j < 2 ? 2 * r + j : 2 * m + (kNG - 2) * r + (j - 2);
+}
+
 // The frame of a global tile id: the last frame whose first tile is <= tile
 // (every frame has at least one tile, so the first tiles increase), by
 // binary search over the frame table.

@@ -133,7 +133,7 @@ void launch_loss_render(hipStream_t st, int F, const SsimPlan& plan, const Frame
                         double* frame_sums, float* loss, float* ssim, float* g_rgb,
                         float* g_depth, float* g_alpha);
 
-// densify.hip: ADC statistics of the last backward (grad2d [m][kNG], ntiles
+// densify.hip: ADC statistics of the last backward (grad2d_at, ntiles
 // [m], record r = f n + g), MCMC position noise and relocation.  src [n]:
 // the live source of each dead Gaussian, -1 (or out of range) otherwise;
 // cnt [n] (uint32) and rule [n][4] (double) are scratch.

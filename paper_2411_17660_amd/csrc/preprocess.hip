@@ -362,7 +362,7 @@ __device__ __forceinline__ void slot_reduce_wide(
     double t[kNG];
     for (int j = 0; j < kNG; ++j) t[j] = my[j];
     screen_gradient(rec[r], t);
-    for (int j = 0; j < kNG; ++j) grad2d[r * kNG + j] = t[j];
+    for (int j = 0; j < kNG; ++j) grad2d[grad2d_at(r, j, m)] = t[j];
   }
   }
 }
@@ -374,7 +374,7 @@ __device__ __forceinline__ void slot_reduce_groups(
     const uint32_t* __restrict__ keyoff, const uint32_t* __restrict__ ntiles,
     const float* __restrict__ partial, const uint32_t* __restrict__ stamp, uint32_t epoch,
     uint64_t key_capacity, const uint32_t* __restrict__ first_wide, uint64_t wide_max,
-    const Record* __restrict__ rec, double* __restrict__ grad2d /* [m][kNG] */) {
+    const Record* __restrict__ rec, double* __restrict__ grad2d /* grad2d_at */) {
   const uint64_t gid = (uint64_t)block * blockDim.x + threadIdx.x;
   const uint64_t k = gid / kSlotGroup + min(m - *first_wide, wide_max);
   const int sub = threadIdx.x & (kSlotGroup - 1);
@@ -386,6 +386,7 @@ __device__ __forceinline__ void slot_reduce_groups(
   uint32_t cnt = active ? ntiles[r] : 0u;
   const uint32_t off = cnt ? keyoff[r] : 0u;
   if (cnt && (uint64_t)off + cnt > key_capacity) cnt = 0;  // overflowed the key capacity
+  bool live = false;
   double acc[kNG];
 #pragma unroll
   for (int j = 0; j < kNG; ++j) acc[j] = 0.0;
@@ -409,6 +410,7 @@ __device__ __forceinline__ void slot_reduce_groups(
       // by the lanes whose slot is stamped
       if (s < cnt && st[u] == epoch) {
         const float2* pp = reinterpret_cast<const float2*>(partial + (size_t)(off + s) * kNG);
+        live = true;
 #pragma unroll
         for (int j = 0; j < kNG / 2; ++j) v[u][j] = pp[j];
       }
@@ -421,6 +423,9 @@ __device__ __forceinline__ void slot_reduce_groups(
         acc[2 * j + 1] += v[u][j].y;
       }
   }
+  // no slot stamped: nothing to add up, and no record to read
+  const uint64_t lives = __ballot(live);
+  if (((lives >> (threadIdx.x & (kWave - kSlotGroup))) & ((1u << kSlotGroup) - 1u)) == 0) cnt = 0;
   // sum over the group's 4 lanes: quad DPP moves (partners l ^ 2, l ^ 1),
   // the butterfly order of a shuffle reduction without its LDS round trips
 #pragma unroll
@@ -430,7 +435,7 @@ __device__ __forceinline__ void slot_reduce_groups(
   static_assert(kSlotGroup == 4, "the group reduction is a quad permute");
   if (!active) return;
   if (cnt == 0) {
-    for (int j = sub; j < kNG; j += kSlotGroup) grad2d[r * kNG + j] = 0.0;
+    for (int j = sub; j < kNG; j += kSlotGroup) grad2d[grad2d_at(r, j, m)] = 0.0;
     return;
   }
   screen_gradient(rec[r], acc);
@@ -441,7 +446,7 @@ __device__ __forceinline__ void slot_reduce_groups(
 #pragma unroll
     for (int t = 1; t < kSlotGroup; ++t)
       if (j0 + t < kNG) v = sub == t ? acc[j0 + t] : v;
-    if (j0 + sub < kNG) grad2d[r * kNG + j0 + sub] = v;
+    if (j0 + sub < kNG) grad2d[grad2d_at(r, j0 + sub, m)] = v;
   }
 }
 
@@ -502,7 +507,7 @@ __global__ void __launch_bounds__(256) preprocess_bwd_kernel(
     if (cnt > 0) {
       kept = true;
       double gr[kNG];
-      for (int j = 0; j < kNG; ++j) gr[j] = grad2d[r * kNG + j];
+      for (int j = 0; j < kNG; ++j) gr[j] = grad2d[grad2d_at(r, j, (uint64_t)n * n_frames)];
       const FrameDesc fr = frames[f];
       double W[9], tf[3];
       load_pose(poses, f, W, tf);

@@ -1103,7 +1103,11 @@ gsr_status gsr_debug_grad2d(gsr_context* ctx, double* out, void* stream) {
   if (ctx->grad2d.bytes < bytes) return fail(ctx, GSR_ERR_STATE, "no backward");
   GSR_HIP(hipSetDevice(ctx->device));
   GSR_HIP(hipStreamSynchronize((hipStream_t)stream));
-  GSR_HIP(hipMemcpy(out, ctx->grad2d.p, bytes, hipMemcpyDeviceToHost));
+  std::vector<double> parts(bytes / 8);
+  GSR_HIP(hipMemcpy(parts.data(), ctx->grad2d.p, bytes, hipMemcpyDeviceToHost));
+  const uint64_t m = (uint64_t)sv.n * sv.F;
+  for (uint64_t r = 0; r < m; ++r)
+    for (int j = 0; j < kNG; ++j) out[r * kNG + j] = parts[grad2d_at(r, j, m)];
   return GSR_OK;
 }
 
