@@ -245,10 +245,10 @@ __device__ __forceinline__ unsigned xcd_block(unsigned bid, unsigned per) {
   return (bid % kXcds) * per + bid / kXcds;
 }
 
-template <int WAVES>
+template <int WAVES, int R>
 struct RadixShape {
   static constexpr int kThreads = WAVES * kWave;
-  static constexpr int kTile = kThreads * kSortRounds;  // keys per block
+  static constexpr int kTile = kThreads * R;  // keys per block
 };
 
 // Where a pass reads its (key, value) pairs.  kPer: keys per 16-byte load.
@@ -314,13 +314,14 @@ struct StoreOrder {
 // Digit counts of one block's keys.  A count does not depend on the order,
 // so each thread loads 16 bytes of keys at once and bumps its wave's LDS
 // counters with atomics; the wave histograms are summed.
-template <int BINS, int WAVES, typename Load>
+template <int BINS, int WAVES, int R, typename Load>
 __global__ void __launch_bounds__(256) radix_hist_kernel(
     Load in, const uint64_t* n_dev, uint64_t n_host, int shift,
     int width, uint32_t* __restrict__ hist /* [nblocks][2^width] */) {
-  constexpr int kTile = RadixShape<WAVES>::kTile;
+  constexpr int kTile = RadixShape<WAVES, R>::kTile;
   constexpr int kHW = 256 / kWave;  // waves of this kernel
   constexpr int kPer = Load::kPer;
+  static_assert(kTile % (kPer * 256) == 0, "whole 16-byte loads");
   __shared__ uint32_t wcnt[kHW][BINS];
   const uint64_t n = n_dev ? min(*n_dev, n_host) : n_host;
   const int bins = 1 << width;
@@ -443,12 +444,12 @@ __global__ void __launch_bounds__(kMaxBins) radix_coldown_kernel(
   }
 }
 
-template <int BINS, int WAVES>
+template <int BINS, int WAVES, int R>
 struct ScatterLds {
   uint32_t wcnt[WAVES][BINS];  // counts, then each wave's block-local start in digit
   uint32_t gofs[BINS];         // global start of digit d minus its block-local start
   uint32_t wsum[WAVES];
-  uint32_t sk[RadixShape<WAVES>::kTile], sv[RadixShape<WAVES>::kTile];
+  uint32_t sk[RadixShape<WAVES, R>::kTile], sv[RadixShape<WAVES, R>::kTile];
 };
 
 // Ranks the block's keys (lane's round-k key is block-local index
@@ -459,25 +460,25 @@ struct ScatterLds {
 // the global offsets, so that each key reads one LDS word on its way into
 // the staging rows and one on its way out.  offs: the global starts of the
 // DPT digits that this thread combines.
-template <int BINS, int WAVES, int DPT, typename Store>
-__device__ __forceinline__ void rank_and_scatter(ScatterLds<BINS, WAVES>& L,
-                                                 const uint32_t (&key)[kSortRounds],
-                                                 const uint32_t (&val)[kSortRounds],
+template <int BINS, int WAVES, int R, int DPT, typename Store>
+__device__ __forceinline__ void rank_and_scatter(ScatterLds<BINS, WAVES, R>& L,
+                                                 const uint32_t (&key)[R],
+                                                 const uint32_t (&val)[R],
                                                  uint32_t nkeys, int shift, int width,
                                                  const uint32_t (&offs)[DPT],
                                                  const Store& out) {
-  constexpr int kThreads = RadixShape<WAVES>::kThreads;
+  constexpr int kThreads = RadixShape<WAVES, R>::kThreads;
   static_assert(BINS == 256 || BINS == kMaxBins, "8- or 10-bit digit counters");
   constexpr int kBinBits = BINS == 256 ? 8 : kMaxDigitBits;
   const int bins = 1 << width;
   const uint32_t mask = (uint32_t)bins - 1u;
   const int lane = threadIdx.x & (kWave - 1);
   const int w = threadIdx.x / kWave;
-  const uint32_t wbase = (uint32_t)w * (kWave * kSortRounds);
+  const uint32_t wbase = (uint32_t)w * (kWave * R);
   const uint32_t wbase_s = __builtin_amdgcn_readfirstlane(wbase);  // wave-uniform
-  uint32_t rank[kSortRounds];
+  uint32_t rank[R];
 #pragma unroll
-  for (int k = 0; k < kSortRounds; ++k) {
+  for (int k = 0; k < R; ++k) {
     const uint32_t i = wbase + (uint32_t)k * kWave + lane;
     const bool valid = i < nkeys;
     const uint32_t d = (key[k] >> shift) & mask;
@@ -528,17 +529,17 @@ __device__ __forceinline__ void rank_and_scatter(ScatterLds<BINS, WAVES>& L,
   // A full block (all but the last) takes the loops without a per-key test,
   // so that the unrolled rounds' LDS reads are all in flight before the
   // dependent writes and stores; the test made each round wait for its own.
-  const bool full = nkeys == (uint32_t)RadixShape<WAVES>::kTile;  // block-uniform
+  const bool full = nkeys == (uint32_t)RadixShape<WAVES, R>::kTile;  // block-uniform
   if (full) {
 #pragma unroll
-    for (int k = 0; k < kSortRounds; ++k) {
+    for (int k = 0; k < R; ++k) {
       const uint32_t lp = L.wcnt[w][__builtin_amdgcn_ubfe(key[k], shift, width)] + rank[k];
       L.sk[lp] = key[k];
       L.sv[lp] = val[k];
     }
   } else {
 #pragma unroll
-    for (int k = 0; k < kSortRounds; ++k) {
+    for (int k = 0; k < R; ++k) {
       const uint32_t i = wbase + (uint32_t)k * kWave + lane;
       if (i < nkeys) {
         const uint32_t lp = L.wcnt[w][__builtin_amdgcn_ubfe(key[k], shift, width)] + rank[k];
@@ -548,25 +549,25 @@ __device__ __forceinline__ void rank_and_scatter(ScatterLds<BINS, WAVES>& L,
     }
   }
   __syncthreads();
-  // kSortRounds slots per thread: consecutive threads take consecutive
+  // R slots per thread: consecutive threads take consecutive
   // slots, so each digit's run leaves as consecutive stores
   if (full) {
-    uint32_t kk[kSortRounds], vv[kSortRounds];
+    uint32_t kk[R], vv[R];
 #pragma unroll
-    for (int k = 0; k < kSortRounds; ++k) {
+    for (int k = 0; k < R; ++k) {
       const uint32_t idx = threadIdx.x + (uint32_t)k * kThreads;
       kk[k] = L.sk[idx];
       vv[k] = L.sv[idx];
     }
 #pragma unroll
-    for (int k = 0; k < kSortRounds; ++k) {
+    for (int k = 0; k < R; ++k) {
       const uint32_t idx = threadIdx.x + (uint32_t)k * kThreads;
       const uint32_t dst = L.gofs[__builtin_amdgcn_ubfe(kk[k], shift, width)] + idx;
       out.put(dst, kk[k], vv[k]);
     }
   } else {
 #pragma unroll
-    for (int k = 0; k < kSortRounds; ++k) {
+    for (int k = 0; k < R; ++k) {
       const uint32_t idx = threadIdx.x + (uint32_t)k * kThreads;
       if (idx < nkeys) {
         const uint32_t kk = L.sk[idx];
@@ -581,14 +582,14 @@ __device__ __forceinline__ void rank_and_scatter(ScatterLds<BINS, WAVES>& L,
 // (FOLD) as the histogram left them.  With FOLD a block walks down the whole
 // columns itself: the counts in front of it and the digit totals, whose scan
 // over the digits completes the starts.
-template <int BINS, int WAVES, bool FOLD, typename Load, typename Store>
+template <int BINS, int WAVES, int R, bool FOLD, typename Load, typename Store>
 __global__ void __launch_bounds__(WAVES * kWave) radix_scatter_kernel(
     Load in, const uint64_t* n_dev, uint64_t n_host, int shift, int width, unsigned nb,
     unsigned per, const uint32_t* __restrict__ offsets /* [nblocks][2^width] */, Store out) {
-  constexpr int kThreads = RadixShape<WAVES>::kThreads;
-  constexpr int kTile = RadixShape<WAVES>::kTile;
+  constexpr int kThreads = RadixShape<WAVES, R>::kThreads;
+  constexpr int kTile = RadixShape<WAVES, R>::kTile;
   constexpr int DPT = (BINS + kThreads - 1) / kThreads;  // digits per thread in the combine
-  __shared__ ScatterLds<BINS, WAVES> L;
+  __shared__ ScatterLds<BINS, WAVES, R> L;
   const unsigned b = xcd_block(blockIdx.x, per);
   if (b >= nb) return;  // padding workgroup: before any barrier
   const uint64_t n = n_dev ? min(*n_dev, n_host) : n_host;
@@ -596,10 +597,10 @@ __global__ void __launch_bounds__(WAVES * kWave) radix_scatter_kernel(
   const uint32_t nkeys = (uint32_t)(n > bbase ? min((uint64_t)kTile, n - bbase) : 0);
   for (int i = threadIdx.x; i < WAVES * BINS; i += kThreads) (&L.wcnt[0][0])[i] = 0;
   const int lane = threadIdx.x & (kWave - 1);
-  const uint32_t wbase = (uint32_t)(threadIdx.x / kWave) * (kWave * kSortRounds);
-  uint32_t key[kSortRounds], val[kSortRounds];
+  const uint32_t wbase = (uint32_t)(threadIdx.x / kWave) * (kWave * R);
+  uint32_t key[R], val[R];
 #pragma unroll
-  for (int k = 0; k < kSortRounds; ++k) {
+  for (int k = 0; k < R; ++k) {
     const uint32_t i = wbase + (uint32_t)k * kWave + lane;
     key[k] = i < nkeys ? in.key(bbase + i) : 0u;
     val[k] = i < nkeys ? in.val(bbase + i) : 0u;
@@ -647,7 +648,7 @@ __global__ void __launch_bounds__(WAVES * kWave) radix_scatter_kernel(
 #pragma unroll
     for (int j = 0; j < DPT; ++j) out.start(d0 + j, offs[j]);
   __syncthreads();
-  rank_and_scatter<BINS, WAVES, DPT, Store>(L, key, val, nkeys, shift, width, offs, out);
+  rank_and_scatter<BINS, WAVES, R, DPT, Store>(L, key, val, nkeys, shift, width, offs, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -978,10 +979,20 @@ static int max_digit_width(int bits) {
   return mx;
 }
 
-// Workspace bounds use the smallest block (4 waves, 4096 keys).
+// Up to this many counts every scatter block walks down the columns itself,
+// which takes the three column kernels out of the pass: with 256 digits, 8
+// blocks 2 + 9 us (histogram + scatter) against 2 + 5 + 8, 32 blocks 5 + 10
+// against 4 + 8 + 8, 125 blocks 5 + 16 against 5 + 13 + 10, and three launches
+// saved; with 1024 digits the walks have overtaken the kernels at a few
+// hundred blocks (4 + 32 against 3 + 9 + 14).
+constexpr uint64_t kFoldCounts = 1u << 16;
+
+// Workspace bounds use the smallest block of a pass with column kernels (4
+// waves, 4096 keys); the others have at most kFoldCounts counts.
 size_t radix_hist_elems(uint64_t n_max, int bits) {
   const int wmax = bits > 0 ? max_digit_width(bits) : 8;
-  return ((size_t)1 << std::max(wmax, 8)) * blocks_for(n_max, RadixShape<4>::kTile);
+  const size_t blocks = blocks_for(n_max, RadixShape<4, kSortRounds>::kTile);
+  return std::max<size_t>(kFoldCounts, blocks << std::max(wmax, 8));
 }
 size_t scan_block_elems(uint64_t n_max) {
   return blocks_for(n_max, (n_max > kGatherBig ? kScanItems : kScanFew) * kScanThreads);
@@ -990,7 +1001,7 @@ size_t scan_block_elems(uint64_t n_max) {
 // bound for every smaller count as well)
 size_t radix_scan_elems(uint64_t n_max, int bits) {
   const int wmax = bits > 0 ? max_digit_width(bits) : 8;
-  const uint64_t nb = blocks_for(n_max, RadixShape<4>::kTile);
+  const uint64_t nb = blocks_for(n_max, RadixShape<4, kSortRounds>::kTile);
   const uint64_t nc = std::min<uint64_t>(isqrt_ceil(nb), kColMaxChunks);
   return (size_t)(nc + 1) << std::max(wmax, 8);
 }
@@ -1009,46 +1020,47 @@ static void radix_offsets(hipStream_t st, uint32_t* hist, unsigned nb, int width
                      scan_tmp, nc);
 }
 
-// Up to this many counts every scatter block walks down the columns itself,
-// which takes the three column kernels out of the pass: with 256 digits, 8
-// blocks 2 + 9 us (histogram + scatter) against 2 + 5 + 8, 32 blocks 5 + 10
-// against 4 + 8 + 8, 125 blocks 5 + 16 against 5 + 13 + 10, and three launches
-// saved; with 1024 digits the walks have overtaken the kernels at a few
-// hundred blocks (4 + 32 against 3 + 9 + 14).
-constexpr uint64_t kFoldCounts = 1u << 16;
-
-template <int BINS, int WAVES, typename Load, typename Store>
+template <int BINS, int WAVES, int R, typename Load, typename Store>
 static void radix_pass(hipStream_t st, Load in, Store out, const uint64_t* n_dev, uint64_t n_max,
                        int shift, int width, uint32_t* hist, uint32_t* scan_tmp) {
-  const unsigned nb = blocks_for(n_max, RadixShape<WAVES>::kTile);
+  const unsigned nb = blocks_for(n_max, RadixShape<WAVES, R>::kTile);
   const unsigned per = (nb + kXcds - 1) / kXcds;
-  const dim3 grid(per * kXcds), block(RadixShape<WAVES>::kThreads);
-  hipLaunchKernelGGL((radix_hist_kernel<BINS, WAVES, Load>), dim3(nb), dim3(256), 0, st, in,
+  const dim3 grid(per * kXcds), block(RadixShape<WAVES, R>::kThreads);
+  hipLaunchKernelGGL((radix_hist_kernel<BINS, WAVES, R, Load>), dim3(nb), dim3(256), 0, st, in,
                      n_dev, n_max, shift, width, hist);
   if (((uint64_t)nb << width) <= kFoldCounts) {
-    hipLaunchKernelGGL((radix_scatter_kernel<BINS, WAVES, true, Load, Store>), grid, block, 0, st,
-                       in, n_dev, n_max, shift, width, nb, per, hist, out);
+    hipLaunchKernelGGL((radix_scatter_kernel<BINS, WAVES, R, true, Load, Store>), grid, block, 0,
+                       st, in, n_dev, n_max, shift, width, nb, per, hist, out);
     return;
   }
   radix_offsets(st, hist, nb, width, scan_tmp);
-  hipLaunchKernelGGL((radix_scatter_kernel<BINS, WAVES, false, Load, Store>), grid, block, 0, st,
+  hipLaunchKernelGGL((radix_scatter_kernel<BINS, WAVES, R, false, Load, Store>), grid, block, 0, st,
                      in, n_dev, n_max, shift, width, nb, per, hist, out);
 }
 
 // Large passes take 8-wave blocks (longer digit runs per block); small ones
 // and 10-bit digits (LDS) take 4-wave blocks.
 constexpr uint64_t kBigPass = 1ull << 24;
+// Few keys: half the rounds, and so of a block's serial chain, and twice the
+// blocks.  The depth order of 20000 records takes 51 us (68 with 16 rounds, 49
+// with 4), 50000: 56 (68, 57), 100000: 66 (71, 71), 260000: 83 (80, 109; the
+// column walks have grown past the gain).
+constexpr int kFewRounds = 8;
+constexpr uint64_t kFewPass = 1u << 17;
+static_assert(kFewPass / RadixShape<4, kFewRounds>::kTile * 256 <= kFoldCounts, "columns walked");
 
 template <typename Load, typename Store>
 static void radix_pass_any(hipStream_t st, Load in, Store out, const uint64_t* n_dev,
                            uint64_t n_max, int shift, int width, uint32_t* hist,
                            uint32_t* scan_tmp) {
   if (width > 8)
-    radix_pass<kMaxBins, 4>(st, in, out, n_dev, n_max, shift, width, hist, scan_tmp);
+    radix_pass<kMaxBins, 4, kSortRounds>(st, in, out, n_dev, n_max, shift, width, hist, scan_tmp);
   else if (n_max >= kBigPass)
-    radix_pass<256, 8>(st, in, out, n_dev, n_max, shift, width, hist, scan_tmp);
+    radix_pass<256, 8, kSortRounds>(st, in, out, n_dev, n_max, shift, width, hist, scan_tmp);
+  else if (n_max <= kFewPass)
+    radix_pass<256, 4, kFewRounds>(st, in, out, n_dev, n_max, shift, width, hist, scan_tmp);
   else
-    radix_pass<256, 4>(st, in, out, n_dev, n_max, shift, width, hist, scan_tmp);
+    radix_pass<256, 4, kSortRounds>(st, in, out, n_dev, n_max, shift, width, hist, scan_tmp);
 }
 
 // Up to here the order comes from counting pairs.  Its time grows with the
