@@ -98,6 +98,10 @@ void launch_composite_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           float* alpha, float* t_final, int32_t* n_last, uint32_t* nproc,
                           const uint32_t* prev_nproc, uint32_t* order, bool xcd_groups,
                           unsigned long long* pairs, int32_t* med_pos);
+// The segments that the backward cuts every tile's list into (1: none), and
+// the bytes of each pixel's state change over them (`maps`).
+int bwd_segments(uint64_t keys, int64_t n_tiles, int tw, int th);
+size_t bwd_map_bytes(int segments, int64_t n_tiles, int tw, int th);
 void launch_composite_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
                           const Record* rec, const uint32_t* keyoff, const uint32_t* nproc,
@@ -105,7 +109,7 @@ void launch_composite_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           const float* g_alpha, const float* t_final, const int32_t* n_last,
                           float* partial, uint32_t* stamp,
                           const uint32_t* epoch, uint32_t* order, bool xcd_groups,
-                          const int32_t* med_pos);
+                          const int32_t* med_pos, int segments, double2* maps);
 
 // loss.hip
 int loss_blocks_x(int64_t max_hw);
@@ -186,7 +190,8 @@ void launch_surfel_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                        const float* g_alpha, const float* g_normal, const float* g_dist,
                        const float* t_final, const int32_t* n_last, const float* dist_aux,
                        float* partial, uint32_t* stamp, const uint32_t* epoch,
-                       const uint32_t* nproc, uint32_t* order, bool xcd_groups);
+                       const uint32_t* nproc, uint32_t* order, bool xcd_groups, int segments,
+                       double2* maps);
 // Per-record sums of the stamped key partials, records in `order` (sorted by
 // tile count so that a wave's groups do similar work): sgrad [m][values].
 void launch_surfel_slot_reduce(hipStream_t st, uint64_t m, const uint32_t* order,

@@ -298,9 +298,9 @@ struct BwdLds {
   uint64_t summed[WAVES];                       // the batch's entries the wave has sums for
 };
 
-template <int TW, int TH, int PIX, bool MEDIAN>
+template <int TW, int TH, int PIX, bool MEDIAN, BwdPass PASS>
 __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_kernel(
-    int n_tiles, int groups, const uint32_t* __restrict__ order, int n_frames,
+    double2* __restrict__ maps, int n_tiles, int groups, const uint32_t* __restrict__ order, int n_frames,
     const FrameDesc* __restrict__ frames, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ vals, const Record* __restrict__ rec,
     const uint32_t* __restrict__ keyoff, const uint32_t* __restrict__ tile_nproc, float bg0,
@@ -318,8 +318,16 @@ __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_
   __shared__ BwdLds<WAVES, MEDIAN> L;
   const int tile = tile_of_block(blockIdx.x, n_tiles, groups, order);
   if (tile < 0) return;
-  const uint32_t nproc = tile_nproc[tile];
-  if (nproc == 0) return;  // uniform over the workgroup
+  uint32_t nproc = tile_nproc[tile];
+  // the segment's entries, from now on positions 0 .. nproc of a list of its own
+  uint32_t seg0 = 0;
+  const int seg = PASS == kBwdMaps ? blockIdx.y + 1 : blockIdx.y;
+  if (PASS != kBwdWhole) {
+    const uint32_t len = segment_len(nproc, kBatchB, PASS == kBwdMaps ? gridDim.y + 1 : gridDim.y);
+    seg0 = min(nproc, seg * len);
+    nproc = min(nproc - seg0, len);
+  }
+  if (nproc == 0 && PASS != kBwdMaps) return;  // uniform over the workgroup
   const uint32_t epoch = *epoch_dev;
   const int f = frame_of_tile(frames, n_frames, tile);
   const FrameDesc fr = frames[f];
@@ -330,8 +338,14 @@ __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_
   const int blk0 = wave * PIX;
   const int bx0 = tx * TW + (blk0 % TB::kX) * kBlk, by0 = ty * TH + (blk0 / TB::kX) * kBlk;
   const int px0 = bx0 + (lane & 7), py0 = by0 + (lane >> 3);
-  const uint2 rg = ranges[tile];
+  uint2 rg = ranges[tile];
+  rg.x += seg0;
   const int64_t plane = (int64_t)fr.width * fr.height;
+  // the maps of the tile's pixels, segment after segment from the second
+  double2* my_maps = nullptr;
+  if (PASS != kBwdWhole)
+    my_maps = maps + (int64_t)tile * (PASS == kBwdMaps ? gridDim.y : gridDim.y - 1) * (TW * TH) +
+              wave * kWave + lane;
 
   // per pixel: T_{i+1} and the upstream gradients G.  dL/da_i = T_i G . (c_i -
   // B_i), the upstream-weighted difference between the entry's colour, depth
@@ -356,8 +370,8 @@ __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_
     if (px < fr.width && py < fr.height) {
       const int64_t p = (int64_t)py * fr.width + px, q = fr.pixel_offset + p;
       const float* gi = g_rgb + 3 * fr.pixel_offset;
-      last[k] = n_last[q];
-      if (MEDIAN) mp[k] = med_pos[q];
+      last[k] = n_last[q] - (int)seg0;
+      if (MEDIAN) mp[k] = med_pos[q] - (int)seg0;
       T[k] = t_final[q];
       H0[k] = gi[p];
       H1[k] = gi[plane + p];
@@ -368,12 +382,26 @@ __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_
                            __builtin_fma(H1[k], (double)bg1, H0[k] * (double)bg0)) -
              (double)g_alpha[q];
     }
+    if (PASS == kBwdMaps) {
+      T[k] = 1.0f;
+      E[k] = 0.0;
+    } else if (PASS == kBwdSegments) {
+      // from behind the list to behind the segment
+      double t = T[k];
+      for (int s = (int)gridDim.y - 2; s >= seg; --s) {
+        const double2 m = my_maps[s * (TW * TH)];
+        E[k] = __builtin_fma(m.x, E[k], m.y);
+        t /= m.x;
+      }
+      T[k] = (float)t;
+    }
     odd |= !isfinite(H0[k] + H1[k] + H2[k] + HZ[k]);
-    int mx = last[k];
+    int mx = max(last[k], 0);
     for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, kWave));
     most[k] = __builtin_amdgcn_readfirstlane((uint32_t)mx);
   }
   odd = __ballot(odd) != 0;  // (wave-uniform)
+  double through = 1.0;  // kBwdMaps: the product of 1 - alpha
   // right operands: powers of Y by block row (k the row pair) and of X by
   // block column, unit columns for the colours
   double wy[kRows], wx[kCols], unit[4];
@@ -470,6 +498,17 @@ __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_
                              readlane64(in[k], j);
         hit |= act;
         float p = 0.0f;
+        if (PASS == kBwdMaps) {
+          if (__builtin_amdgcn_inverse_ballot_w64(act)) {
+            through *= (double)(1.0f - a);
+            double diff = __builtin_fma(H0[k], En.c0, -E[k]);
+            diff = __builtin_fma(H1[k], En.c1, diff);
+            diff = __builtin_fma(H2[k], En.c2, diff);
+            if (!MEDIAN) diff = __builtin_fma(HZ[k], En.z, diff);
+            E[k] = __builtin_fma((double)a, diff, E[k]);
+          }
+          continue;
+        }
         if (__builtin_amdgcn_inverse_ballot_w64(act)) {
           const float om = 1.0f - a;
           const float inv = __builtin_amdgcn_rcpf(om);
@@ -498,7 +537,7 @@ __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_
         my[k % kCols] =
             __builtin_amdgcn_mfma_f64_4x4x4f64((double)p, wy[k / kCols], my[k % kCols], 0, 0, 0);
       }
-      if (hit == 0) continue;
+      if (PASS == kBwdMaps || hit == 0) continue;
       double tot = __builtin_amdgcn_mfma_f64_4x4x4f64(my[0], wx[0], 0.0, 0, 0, 0);
 #pragma unroll
       for (int c = 1; c < kCols; ++c)
@@ -529,6 +568,10 @@ __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_
       tot += dpp<kDppRowRor4>(tot);
       if (out_v >= 0) L.tot[wave][j][out_v] = tot;
       summed |= 1ull << j;
+    }
+    if (PASS == kBwdMaps) {
+      __syncthreads();
+      continue;
     }
     if (lane == 0) L.summed[wave] = summed;
     __syncthreads();
@@ -571,6 +614,7 @@ __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_
     }
     if (WAVES == 1) __syncthreads();
   }
+  if (PASS == kBwdMaps) my_maps[(seg - 1) * (TW * TH)] = make_double2(through, E[0]);
 }
 
 static void launch_order(hipStream_t st, int n_tiles, int groups, const uint32_t* nproc,
@@ -615,23 +659,36 @@ static void launch_bwd_t(hipStream_t st, int pix, int n_tiles, int groups, const
                          const uint32_t* nproc, const float* bg, const float* g_rgb,
                          const float* g_depth, const float* g_alpha, const float* t_final,
                          const int32_t* n_last, float* partial, uint32_t* stamp,
-                         const uint32_t* epoch, const int32_t* med_pos) {
+                         const uint32_t* epoch, const int32_t* med_pos, int segments,
+                         double2* maps) {
   if constexpr (PIX > 1) {
     if (pix < PIX) {
       launch_bwd_t<TW, TH, PIX / 2>(st, pix, n_tiles, groups, order, F, frames, ranges, vals, rec,
                                     keyoff, nproc, bg, g_rgb, g_depth, g_alpha, t_final, n_last,
-                                    partial, stamp, epoch, med_pos);
+                                    partial, stamp, epoch, med_pos, segments, maps);
       return;
     }
   }
-  const auto go = [&](auto* k) {
-    hipLaunchKernelGGL(k, dim3(grid_of(n_tiles, groups)), dim3(TW * TH / PIX), 0, st, n_tiles,
-                       groups, order, F, frames, ranges, vals, rec, keyoff, nproc, bg[0], bg[1],
+  const auto go = [&](auto* k, int parts) {
+    hipLaunchKernelGGL(k, dim3(grid_of(n_tiles, groups), (unsigned)parts), dim3(TW * TH / PIX), 0,
+                       st, maps, n_tiles, groups, order, F, frames, ranges, vals, rec, keyoff, nproc, bg[0], bg[1],
                        bg[2], g_rgb, g_depth, g_alpha, t_final, n_last, partial, stamp, epoch,
                        med_pos);
   };
-  if (med_pos) go(composite_bwd_kernel<TW, TH, PIX, true>);
-  else go(composite_bwd_kernel<TW, TH, PIX, false>);
+  if constexpr (PIX == 1) {
+    if (segments > 1) {
+      if (med_pos) {
+        go(composite_bwd_kernel<TW, TH, 1, true, kBwdMaps>, segments - 1);
+        go(composite_bwd_kernel<TW, TH, 1, true, kBwdSegments>, segments);
+      } else {
+        go(composite_bwd_kernel<TW, TH, 1, false, kBwdMaps>, segments - 1);
+        go(composite_bwd_kernel<TW, TH, 1, false, kBwdSegments>, segments);
+      }
+      return;
+    }
+  }
+  if (med_pos) go(composite_bwd_kernel<TW, TH, PIX, true, kBwdWhole>, 1);
+  else go(composite_bwd_kernel<TW, TH, PIX, false, kBwdWhole>, 1);
 }
 
 void launch_composite_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
@@ -654,6 +711,22 @@ void launch_composite_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
 #undef GSR_FWD
 }
 
+// Below 1.5 waves per SIMD, and with lists of two batches and more on average,
+// the lists are worked on in segments.  Whole against eight segments (both
+// launches), us: 2 x 131x97 (504 waves, 209 keys per tile) 83 / 46; 321x243
+// (1,344 waves, 235) 80 / 62; but 400x300 (1,900, 210) 71 / 73 and 640x480
+// (4,800, 965) 229 / 294, where the state pass costs more than the idle SIMDs,
+// and 97x81 (168, 59), whose lists are one batch, 24 / 28.
+int bwd_segments(uint64_t keys, int64_t n_tiles, int tw, int th) {
+  constexpr int64_t kFewWaves = 1536;
+  const bool few = n_tiles * (tw * th / kWave) <= kFewWaves;
+  return few && keys >= 2 * kBatchB * (uint64_t)n_tiles ? 8 : 1;
+}
+
+size_t bwd_map_bytes(int segments, int64_t n_tiles, int tw, int th) {
+  return (size_t)n_tiles * tw * th * (segments - 1) * sizeof(double2);
+}
+
 void launch_composite_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
                           const Record* rec, const uint32_t* keyoff, const uint32_t* nproc,
@@ -661,7 +734,7 @@ void launch_composite_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           const float* g_depth, const float* g_alpha, const float* t_final,
                           const int32_t* n_last, float* partial, uint32_t* stamp,
                           const uint32_t* epoch, uint32_t* order, bool xcd_groups,
-                          const int32_t* med_pos) {
+                          const int32_t* med_pos, int segments, double2* maps) {
   if (n_tiles <= 0) return;
   const int groups = xcd_groups ? kQueues : 1;
   launch_order(st, n_tiles, groups, nproc, order);
@@ -677,7 +750,8 @@ void launch_composite_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
 #define GSR_BWD(W, H)                                                                            \
   launch_bwd_t<W, H, std::min(4, TileBlocks<W, H>::kN)>(                                         \
       st, pix, n_tiles, groups, order, F, frames, ranges, vals, rec, keyoff, nproc, bg, g_rgb,    \
-      g_depth, g_alpha, t_final, n_last, partial, stamp, epoch, med_pos)
+      g_depth, g_alpha, t_final, n_last, partial, stamp, epoch, med_pos,                        \
+      segments, maps)
   if (tw == 16 && th == 16) GSR_BWD(16, 16);
   else if (tw == 8 && th == 8) GSR_BWD(8, 8);
   else if (tw == 32 && th == 8) GSR_BWD(32, 8);

@@ -62,6 +62,7 @@ struct gsr_context {
   DBuf up_rgb, up_depth, up_alpha;  // upstream gradients for gsr_step_l1
   DBuf tune_out;                    // scratch outputs of the autotuner
   DBuf order_f, order_b;            // compositing tile schedules (forward, backward)
+  DBuf bwd_maps;   // compositing backward in segments: state changes per pixel
   DBuf cls_order;  // records ordered by key count (per-record reduction)
   // layout (tile shape and frame sizes) whose processed-entry counts nproc
   // holds, so that the next forward over the same tiles can order its queue
@@ -233,7 +234,7 @@ gsr_status gsr_destroy(gsr_context* ctx) {
                   &ctx->ssim_rgb, &ctx->ssim_tiles, &ctx->ssim_scale, &ctx->med_pos,
                   &ctx->reloc_cnt, &ctx->reloc_rule,
                   &ctx->up_rgb, &ctx->up_depth, &ctx->up_alpha, &ctx->tune_out,
-                  &ctx->order_f, &ctx->order_b, &ctx->cls_order, &ctx->dist_aux, &ctx->spart,
+                  &ctx->order_f, &ctx->order_b, &ctx->bwd_maps, &ctx->cls_order, &ctx->dist_aux, &ctx->spart,
                   &ctx->sgrad, &ctx->nc_part};
   for (DBuf* b : bufs)
     if (b->p) (void)hipFree(b->p);
@@ -547,6 +548,9 @@ gsr_status gsr_backward_surfel(gsr_context* ctx, const float* g_rgb, const float
   if ((rc = ensure(ctx, ctx->spart, std::max<uint64_t>(kcap, 1) * ng * 4, st))) return rc;
   if ((rc = ensure(ctx, ctx->sgrad, std::max<uint64_t>(M, 1) * ng * 8, st))) return rc;
   if ((rc = ensure(ctx, ctx->cls_order, M * 4, st))) return rc;
+  const int segments = bwd_segments(sv.K, sv.T, s.tile_w, s.tile_h);
+  if ((rc = ensure(ctx, ctx->bwd_maps, bwd_map_bytes(segments, sv.T, s.tile_w, s.tile_h), st)))
+    return rc;
   const int64_t waves = sv.n > 0 ? surfel_preprocess_bwd_waves(sv.n) : 0;
   if ((rc = ensure(ctx, ctx->twist_part, (size_t)std::max<int64_t>(waves, 1) * sv.F * 6 * 8, st)))
     return rc;
@@ -563,7 +567,7 @@ gsr_status gsr_backward_surfel(gsr_context* ctx, const float* g_rgb, const float
                       g_dist, P<float>(ctx->t_final), P<int32_t>(ctx->n_last),
                       P<float>(ctx->dist_aux), P<float>(ctx->spart), P<uint32_t>(ctx->stamp),
                       d_epoch, P<uint32_t>(ctx->nproc), P<uint32_t>(ctx->order_b),
-                      !(s.flags & GSR_FLAG_NO_XCD_REMAP));
+                      !(s.flags & GSR_FLAG_NO_XCD_REMAP), segments, P<double2>(ctx->bwd_maps));
   }
   {
     StageTimer t(ctx, st, timing, GSR_STAGE_PREPROCESS_BWD);
@@ -610,6 +614,9 @@ gsr_status gsr_backward(gsr_context* ctx, const float* g_rgb, const float* g_dep
   const bool remap = !(s.flags & GSR_FLAG_NO_XCD_REMAP);
   const bool timing = (s.flags & GSR_FLAG_TIMING) != 0;
   // A8 reverse compositing -> per-key partials
+  const int segments = bwd_segments(sv.K, sv.T, s.tile_w, s.tile_h);
+  if ((rc = ensure(ctx, ctx->bwd_maps, bwd_map_bytes(segments, sv.T, s.tile_w, s.tile_h), st)))
+    return rc;
   {
     StageTimer t(ctx, st, timing, GSR_STAGE_COMPOSITE_BWD);
     launch_composite_bwd(st, s.tile_w, s.tile_h, (int)sv.T, sv.F,
@@ -620,7 +627,8 @@ gsr_status gsr_backward(gsr_context* ctx, const float* g_rgb, const float* g_dep
                          P<float>(ctx->t_final), P<int32_t>(ctx->n_last),
                          P<float>(ctx->partial), P<uint32_t>(ctx->stamp), d_epoch,
                          P<uint32_t>(ctx->order_b), remap,
-                         (s.flags & GSR_FLAG_MEDIAN_DEPTH) ? P<int32_t>(ctx->med_pos) : nullptr);
+                         (s.flags & GSR_FLAG_MEDIAN_DEPTH) ? P<int32_t>(ctx->med_pos) : nullptr,
+                         segments, P<double2>(ctx->bwd_maps));
   }
   // A9-A11 per-record reduce, chain rule, twist
   const int64_t waves = sv.n > 0 ? preprocess_bwd_waves(sv.n) : 0;

@@ -492,7 +492,8 @@ constexpr int kSG = 16;
 // another, two row rotations for the remaining bits.  What bounds it: VALU
 // issue (~190 instructions a visit, half of them FP64).  One wave per tile and
 // a reduction through LDS took 3810 us on 250k surfels over 4 x 1200x680 and
-// 843 us on 20k over one 321x243 frame; this takes 3436 and 316 us.
+// 843 us on 20k over one 321x243 frame; this takes 3436 and 316, the latter 220
+// us in eight segments (both launches).
 constexpr int kBatchB = 64;          // list entries per batch
 constexpr int kBwdMinWaves = 4096;  // four waves on each of the 1,024 SIMDs
 
@@ -504,9 +505,9 @@ struct BwdLds {
   uint64_t summed[WAVES];  // the batch's entries the wave has sums for
 };
 
-template <int TW, int TH, int PIX>
+template <int TW, int TH, int PIX, BwdPass PASS>
 __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
-    int n_tiles, int groups, const uint32_t* __restrict__ order,
+    double2* __restrict__ maps, int n_tiles, int groups, const uint32_t* __restrict__ order,
     const uint32_t* __restrict__ tile_nproc,
     int n_frames, const FrameDesc* __restrict__ frames, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ vals, const Surfel* __restrict__ rec,
@@ -524,8 +525,17 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
   __shared__ BwdLds<WAVES> L;
   const int tile = tile_of_block(blockIdx.x, n_tiles, groups, order);
   if (tile < 0) return;
-  const int nproc = (int)tile_nproc[tile];
-  if (nproc == 0) return;  // uniform over the workgroup
+  int nproc = (int)tile_nproc[tile];
+  // the segment's entries, from now on positions 0 .. nproc of a list of its own
+  int seg0 = 0;
+  const int seg = PASS == kBwdMaps ? blockIdx.y + 1 : blockIdx.y;
+  if (PASS != kBwdWhole) {
+    const int len =
+        (int)segment_len(nproc, kBatchB, PASS == kBwdMaps ? gridDim.y + 1 : gridDim.y);
+    seg0 = min(nproc, seg * len);
+    nproc = min(nproc - seg0, len);
+  }
+  if (nproc == 0 && PASS != kBwdMaps) return;  // uniform over the workgroup
   const uint32_t epoch = *epoch_dev;
   const int f = frame_of_tile(frames, n_frames, tile);
   const FrameDesc fr = frames[f];
@@ -535,7 +545,13 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
   const int wave = WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int blk0 = wave * PIX;
   const int bx0 = tx * TW + (blk0 % TB::kX) * kBlk, by0 = ty * TH + (blk0 / TB::kX) * kBlk;
-  const uint2 rg = ranges[tile];
+  uint2 rg = ranges[tile];
+  rg.x += seg0;
+  // the maps of the tile's pixels, segment after segment from the second
+  double2* my_maps = nullptr;
+  if (PASS != kBwdWhole)
+    my_maps = maps + (int64_t)tile * (PASS == kBwdMaps ? gridDim.y : gridDim.y - 1) * (TW * TH) +
+              wave * kWave + lane;
   const int64_t plane = (int64_t)fr.width * fr.height;
   // per pixel: T_{i+1} and the totals of the distortion sums.  dL/da_i takes
   // the upstream-weighted difference G . (v_i - B_i) between the entry's
@@ -556,7 +572,7 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
     const bool valid = px < fr.width && py < fr.height;
     const int64_t p = (int64_t)py * fr.width + px;
     const int64_t q = fr.pixel_offset + p;
-    last[k] = valid ? n_last[q] : 0;
+    last[k] = valid ? n_last[q] - seg0 : 0;
     T[k] = valid ? t_final[q] : 1.0f;
     const float4 ax = valid ? reinterpret_cast<const float4*>(dist_aux)[q]
                             : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -581,10 +597,24 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
     E[k] = __builtin_fma(H2[k], (double)bg2,
                          __builtin_fma(H1[k], (double)bg1, H0[k] * (double)bg0)) -
            ha;
-    int mx = last[k];
+    if (PASS == kBwdMaps) {
+      T[k] = 1.0f;
+      E[k] = 0.0;
+    } else if (PASS == kBwdSegments) {
+      // from behind the list to behind the segment
+      double t = T[k];
+      for (int s = (int)gridDim.y - 2; s >= seg; --s) {
+        const double2 m = my_maps[s * (TW * TH)];
+        E[k] = __builtin_fma(m.x, E[k], m.y);
+        t /= m.x;
+      }
+      T[k] = (float)t;
+    }
+    int mx = max(last[k], 0);
     for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, kWave));
     most[k] = __builtin_amdgcn_readfirstlane(mx);
   }
+  double through = 1.0;  // kBwdMaps: the product of 1 - alpha
   odd = __ballot(odd) != 0;  // (wave-uniform)
   double unit[4];  // right operands: unit columns
 #pragma unroll
@@ -651,12 +681,6 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
         hit |= act;
         if (!__builtin_amdgcn_inverse_ballot_w64(act)) continue;
         const float om = 1.0f - a;
-        const float inv = __builtin_amdgcn_rcpf(om);
-        float Ti = T[k] * inv;
-        Ti = __builtin_fmaf(__builtin_fmaf(-Ti, om, T[k]), inv, Ti);  // Newton step
-        const float w = a * Ti;
-        const double wd = w;
-        T[k] = Ti;
         const double zp = h.z - ZR[k];
         // dDist/dw_i: sum over the other entries m of w_m (z_i - z_m)^2
         const double e = AT[k] * zp * zp - 2.0 * zp * S1[k] + S2[k];
@@ -669,8 +693,18 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
         diff = __builtin_fma(HN1[k], (double)S.n1, diff);
         diff = __builtin_fma(HN2[k], (double)S.n2, diff);
         diff = __builtin_fma(HE[k], e, diff);
-        const float dLda = Ti * (float)diff;
         E[k] = __builtin_fma((double)a, diff, E[k]);
+        if (PASS == kBwdMaps) {
+          through *= (double)om;
+          continue;
+        }
+        const float inv = __builtin_amdgcn_rcpf(om);
+        float Ti = T[k] * inv;
+        Ti = __builtin_fmaf(__builtin_fmaf(-Ti, om, T[k]), inv, Ti);  // Newton step
+        const float w = a * Ti;
+        const double wd = w;
+        T[k] = Ti;
+        const float dLda = Ti * (float)diff;
         acc[10] = __builtin_fma(H0[k], wd, acc[10]);
         acc[11] = __builtin_fma(H1[k], wd, acc[11]);
         acc[12] = __builtin_fma(H2[k], wd, acc[12]);
@@ -732,7 +766,7 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
           acc[8] += dzd - (gx * ocx + gy * ocy);
         }
       }
-      if (hit == 0) continue;
+      if (PASS == kBwdMaps || hit == 0) continue;
       double tot = 0.0;
       if (!odd) {
 #pragma unroll
@@ -775,7 +809,9 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
         summed |= 1ull << j;
       }
     }
-    if constexpr (WAVES > 1) {
+    if constexpr (PASS == kBwdMaps) {
+      __syncthreads();
+    } else if constexpr (WAVES > 1) {
       if (lane == 0) L.summed[wave] = summed;
       __syncthreads();
       uint64_t sw[WAVES], all = 0;
@@ -797,6 +833,7 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
       __syncthreads();
     }
   }
+  if (PASS == kBwdMaps) my_maps[(seg - 1) * (TW * TH)] = make_double2(through, E[0]);
 }
 
 // Per record (surfel, frame): the sum of its keys' partials that this
@@ -1066,19 +1103,30 @@ static void launch_bwd_t(hipStream_t st, int pix, int n_tiles, int groups, const
                          const float* g_alpha, const float* g_normal, const float* g_dist,
                          const float* t_final, const int32_t* n_last, const float* dist_aux,
                          float* partial, uint32_t* stamp, const uint32_t* epoch,
-                         const uint32_t* nproc) {
+                         const uint32_t* nproc, int segments, double2* maps) {
   if constexpr (PIX > 1) {
     if (pix < PIX) {
       launch_bwd_t<TW, TH, PIX / 2>(st, pix, n_tiles, groups, order, F, frames, ranges, vals, rec,
                                     keyoff, bg, g_rgb, g_depth, g_alpha, g_normal, g_dist,
-                                    t_final, n_last, dist_aux, partial, stamp, epoch, nproc);
+                                    t_final, n_last, dist_aux, partial, stamp, epoch, nproc, segments,
+                                    maps);
       return;
     }
   }
-  hipLaunchKernelGGL((surfel_bwd_kernel<TW, TH, PIX>), dim3(tile_schedule_grid(n_tiles, groups)),
-                     dim3(TW * TH / PIX), 0, st, n_tiles, groups, order, nproc, F, frames, ranges,
-                     vals, rec, keyoff, bg[0], bg[1], bg[2], g_rgb, g_depth, g_alpha, g_normal,
-                     g_dist, t_final, n_last, dist_aux, partial, stamp, epoch);
+  const auto go = [&](auto* k, int parts) {
+    hipLaunchKernelGGL(k, dim3(tile_schedule_grid(n_tiles, groups), (unsigned)parts),
+                       dim3(TW * TH / PIX), 0, st, maps, n_tiles, groups, order, nproc, F, frames,
+                       ranges, vals, rec, keyoff, bg[0], bg[1], bg[2], g_rgb, g_depth, g_alpha,
+                       g_normal, g_dist, t_final, n_last, dist_aux, partial, stamp, epoch);
+  };
+  if constexpr (PIX == 1) {
+    if (segments > 1) {
+      go(surfel_bwd_kernel<TW, TH, 1, kBwdMaps>, segments - 1);
+      go(surfel_bwd_kernel<TW, TH, 1, kBwdSegments>, segments);
+      return;
+    }
+  }
+  go(surfel_bwd_kernel<TW, TH, PIX, kBwdWhole>, 1);
 }
 
 void launch_surfel_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
@@ -1088,7 +1136,8 @@ void launch_surfel_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                        const float* g_alpha, const float* g_normal, const float* g_dist,
                        const float* t_final, const int32_t* n_last, const float* dist_aux,
                        float* partial, uint32_t* stamp, const uint32_t* epoch,
-                       const uint32_t* nproc, uint32_t* order, bool xcd_groups) {
+                       const uint32_t* nproc, uint32_t* order, bool xcd_groups, int segments,
+                       double2* maps) {
   if (n_tiles <= 0) return;
   const int groups = tile_schedule_groups(xcd_groups);
   launch_tile_order(st, n_tiles, groups, nproc, order);
@@ -1102,7 +1151,7 @@ void launch_surfel_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
   launch_bwd_t<W, H, std::min(4, TileBlocks<W, H>::kN)>(                                      \
       st, pix, n_tiles, groups, order, F, frames, ranges, vals, (const Surfel*)rec, keyoff, bg, \
       g_rgb, g_depth, g_alpha, g_normal, g_dist, t_final, n_last, dist_aux, partial, stamp,    \
-      epoch, nproc)
+      epoch, nproc, segments, maps)
   if (tw == 16 && th == 16) GSR_SURF_BWD(16, 16);
   else if (tw == 8 && th == 8) GSR_SURF_BWD(8, 8);
   else if (tw == 32 && th == 8) GSR_SURF_BWD(32, 8);

@@ -188,4 +188,18 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, int j) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+// What a launch does: all of a tile's list per workgroup; or, where that leaves
+// SIMDs without work, a segment of it (blockIdx.y), for which the state behind
+// the segment has to be known: an entry maps the pixel's (T, E) behind it to
+// those in front by T / (1 - a) and (1 - a) E + a G . c, so a segment is the
+// product of its 1 - a and the E it makes of 0.  One launch computes these for
+// all segments but the first, the other starts each segment behind the later
+// ones' maps.
+enum BwdPass { kBwdWhole, kBwdMaps, kBwdSegments };
+
+__device__ __forceinline__ uint32_t segment_len(uint32_t nproc, uint32_t batch,
+                                               uint32_t segments) {
+  return ((nproc + segments - 1) / segments + batch - 1) / batch * batch;
+}
+
 }  // namespace gsr

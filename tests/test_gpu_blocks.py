@@ -105,3 +105,52 @@ def test_surfel_blocks_do_not_depend_on_the_path(rast, size, tile, tilt):
         b = out[1][1][k]
         err = float((a.double() - b.double()).norm() / a.double().norm())
         assert err <= 2e-5, (k, err)
+
+
+# Lists worked on in segments (few tiles, lists of two batches and more) against
+# the same image inside a batch of frames, which takes them whole: lists shorter
+# and longer than the eight segments' batches, and pixels that stop in each of them.
+@pytest.mark.parametrize("surfel", [False, True])
+@pytest.mark.parametrize("tile", [(8, 8), (16, 16), (32, 16)])
+@pytest.mark.parametrize("n,ls_mean,sigma", [(400, -1.2, 0.2), (3000, -1.5, 3.0),
+                                             (3000, -1.0, -2.5)])
+def test_segments_do_not_change_the_gradients(rast, n, ls_mean, sigma, tile, surfel):
+    import torch
+    from gpu_util import to_dev
+    W, H, F = 85, 61, 28
+    sc = scenes.tiny_scene(seed=8, n=n, W=W, H=H, f=0.8 * W, sh_degree=0, ls_mean=ls_mean,
+                           ls_sigma=0.3, opacity_sigma=0.5)
+    d = to_dev(sc)
+    d["opacity"] += sigma
+    if surfel:
+        d["log_scales"] = d["log_scales"][:, :2].contiguous()
+    P = W * H
+    gen = torch.Generator().manual_seed(5)
+    G = [torch.randn(k * P, generator=gen).cuda() for k in ((3, 1, 1, 3, 1) if surfel
+                                                            else (3, 1, 1))]
+    out = []
+    for frames in (1, F):
+        poses = d["poses"].expand(frames, 3, 4).contiguous()
+        cams = [sc.cams[0]] * frames
+        args = [d[k] for k in ("means", "log_scales", "quats", "opacity", "sh")] + [poses, cams]
+        # the first frame carries the gradient, the others none
+        Gs = [torch.cat([g, g.new_zeros(g.numel() * (frames - 1))]) for g in G]
+        if surfel:
+            rast.forward_surfel(*args, sc.sh_degree, sc.background, tile=tile)
+            g = rast.backward_surfel(*Gs)
+        else:
+            rast.forward(*args, sc.sh_degree, sc.background, tile=tile)
+            g = rast.backward(*Gs)
+        st = rast.stats()
+        assert st["n_keys"] >= 128 * st["n_tiles"]
+        waves = st["n_tiles"] * tile[0] * tile[1] // 64
+        assert (waves <= 1536) == (frames == 1)
+        out.append(g)
+    out[1]["twist"] = out[1]["twist"][:1]
+    # T and E reach a segment through FP64 products instead of FP32 steps: 2^-24
+    # per entry in front of the stop, which is at most ln(1e-4) / ln(1 - 1/255)
+    # = 2350 entries deep, random in sign: 3e-6 of a term; terms cancel tenfold
+    for k, a in out[0].items():
+        b = out[1][k]
+        err = float((a.double() - b.double()).norm() / b.double().norm())
+        assert err <= 3e-5, (k, err)
