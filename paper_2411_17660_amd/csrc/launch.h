@@ -49,17 +49,18 @@ size_t radix_scan_elems(uint64_t n_max, int bits);
 void launch_depth_sort(hipStream_t st, uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
                        uint32_t* vals_b, uint64_t m, uint32_t* hist, uint32_t* scan_tmp);
 // skey: the sorted depth keys (all ones: culled); trect_sorted[i] and
-// cnt_sorted[i]: the tile rect and tile count of record perm[i].
+// cnt_sorted[i]: the tile rect and tile count of record perm[i].  mailbox
+// (unless NULL, and unless m = 0): host memory that receives the total too.
 void launch_offsets_scan(hipStream_t st, const uint32_t* skey, const uint32_t* perm,
                          const uint2* trect, uint64_t m, uint32_t* cnt_sorted,
                          uint2* trect_sorted, uint64_t* offsets, uint64_t* block_tmp,
-                         uint64_t* total);
+                         uint64_t* total, uint64_t* mailbox);
 // Few records: both of the above in two launches, from (keys, vals).
 bool rank_records(uint64_t m);
 void launch_rank_records(hipStream_t st, const uint32_t* keys, const uint32_t* vals, uint64_t m,
                          const uint2* trect, uint32_t* keys_out, uint32_t* vals_out,
                          uint32_t* cnt_sorted, uint2* trect_sorted, uint64_t* offsets,
-                         uint64_t* total);
+                         uint64_t* total, uint64_t* mailbox);
 // order: the records 0..m-1 in ascending order of size class (0: no key, else
 // 1 + floor(log2 of the key count)); *first (unless NULL) receives the
 // position of the first one of class `mark` or above (m if none).

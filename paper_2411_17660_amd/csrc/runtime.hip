@@ -254,6 +254,30 @@ const char* gsr_last_error(const gsr_context* ctx) { return ctx ? ctx->err.c_str
 
 namespace {
 
+// h_count[kMailbox]: the key count posted by the forward's scan.  Watching it
+// saves the copy behind the scan and the runtime's wait (about 10 us per
+// forward); the stream is asked now and then, so that an error ends the wait.
+constexpr int kMailbox = 7;
+constexpr uint64_t kNoCount = ~0ull;
+
+gsr_status await_count(gsr_context* ctx, hipStream_t st, uint64_t* out) {
+  GSR_HIP(hipGetLastError());
+  const uint64_t* box = ctx->h_count + kMailbox;
+  uint64_t v;
+  for (uint32_t i = 1; (v = __atomic_load_n(box, __ATOMIC_ACQUIRE)) == kNoCount; ++i) {
+    if (i % 4096 != 0) continue;
+    const hipError_t e = hipStreamQuery(st);
+    (void)hipGetLastError();  // ("not ready" is no error of this call)
+    if (e == hipErrorNotReady) continue;
+    GSR_HIP(hipStreamSynchronize(st));
+    v = __atomic_load_n(box, __ATOMIC_ACQUIRE);
+    if (v == kNoCount) return fail(ctx, GSR_ERR_HIP, "the key count did not arrive");
+    break;
+  }
+  *out = v;
+  return GSR_OK;
+}
+
 // The forward of either primitive: 3D Gaussians (normal == NULL) or 2D
 // surfels (log_scales [n,2], normal [sum 3HW], dist [sum HW]); they differ
 // in the preprocess and the compositing kernels only.
@@ -319,6 +343,12 @@ gsr_status forward_impl(gsr_context* ctx, const gsr_settings* s, int64_t n, cons
   uint64_t* d_count = P<uint64_t>(ctx->counters);               // [0] = K
   uint32_t* d_overflow = (uint32_t*)(P<uint64_t>(ctx->counters) + 1);
   const bool timing = (s->flags & GSR_FLAG_TIMING) != 0;
+  // grow mode: the host waits for the key count, which the scan posts to it
+  uint64_t* mailbox = nullptr;
+  if (s->key_capacity == 0) {
+    mailbox = ctx->h_count + kMailbox;
+    __atomic_store_n(mailbox, kNoCount, __ATOMIC_SEQ_CST);
+  }
   // A1 preprocess: the keys go where the depth sort ends in (.._a) after it
   const bool few = rank_records(M);
   uint32_t* dkey = P<uint32_t>(few ? ctx->dkey_b : ctx->dkey_a);
@@ -351,7 +381,7 @@ gsr_status forward_impl(gsr_context* ctx, const gsr_settings* s, int64_t n, cons
     if (few)
       launch_rank_records(st, dkey, dval, M, P<uint2>(ctx->trect), P<uint32_t>(ctx->dkey_a),
                           P<uint32_t>(ctx->dval_a), P<uint32_t>(ctx->cnt_sorted),
-                          P<uint2>(ctx->trect_s), P<uint64_t>(ctx->offsets), d_count);
+                          P<uint2>(ctx->trect_s), P<uint64_t>(ctx->offsets), d_count, mailbox);
     else
       launch_depth_sort(st, P<uint32_t>(ctx->dkey_a), P<uint32_t>(ctx->dval_a),
                         P<uint32_t>(ctx->dkey_b), P<uint32_t>(ctx->dval_b), M,
@@ -363,15 +393,13 @@ gsr_status forward_impl(gsr_context* ctx, const gsr_settings* s, int64_t n, cons
     StageTimer t(ctx, st, timing, GSR_STAGE_OFFSETS);
     launch_offsets_scan(st, P<uint32_t>(ctx->dkey_a), perm, P<uint2>(ctx->trect), M,
                         P<uint32_t>(ctx->cnt_sorted), P<uint2>(ctx->trect_s),
-                        P<uint64_t>(ctx->offsets), P<uint64_t>(ctx->scan_tmp), d_count);
+                        P<uint64_t>(ctx->offsets), P<uint64_t>(ctx->scan_tmp), d_count, mailbox);
   }
   // key capacity
   uint64_t K = 0, cap = 0;
   bool k_known = false;
   if (s->key_capacity == 0) {
-    GSR_HIP(hipMemcpyAsync(ctx->h_count, d_count, 8, hipMemcpyDeviceToHost, st));
-    GSR_HIP(hipStreamSynchronize(st));
-    K = ctx->h_count[0];
+    if (M > 0 && (rc = await_count(ctx, st, &K))) return rc;
     if (K >= (1ull << 32) - 1) return fail(ctx, GSR_ERR_CAPACITY, "%llu keys exceed 2^32",
                                            (unsigned long long)K);
     cap = K;

@@ -118,6 +118,13 @@ __global__ void __launch_bounds__(kScanThreads) gather_counts_kernel(
   }
 }
 
+// The total for the kernels that follow, and (unless NULL) for the host that
+// waits for it.
+__device__ __forceinline__ void post_total(uint64_t v, uint64_t* total, uint64_t* mailbox) {
+  *total = v;
+  if (mailbox) __hip_atomic_store(mailbox, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Exclusive scan of cnt into out.  A block adds up the sums (`per` of them for
 // each scan block) in front of it by itself, which costs less than a launch
 // between the two kernels.  Its kScanTile elements
@@ -126,7 +133,8 @@ __global__ void __launch_bounds__(kScanThreads) gather_counts_kernel(
 // kScanItems consecutive elements.
 __global__ void __launch_bounds__(kScanThreads) scan_down_kernel(
     const uint32_t* __restrict__ cnt, uint64_t n, const uint64_t* __restrict__ block_sums,
-    unsigned per, uint64_t* __restrict__ out, uint64_t* __restrict__ total) {
+    unsigned per, uint64_t* __restrict__ out, uint64_t* __restrict__ total,
+    uint64_t* __restrict__ mailbox) {
   constexpr int kRow = kScanItems + 1;
   __shared__ uint64_t wsum[kScanThreads / kWave];
   __shared__ uint64_t stage[kScanThreads * kRow];
@@ -158,7 +166,7 @@ __global__ void __launch_bounds__(kScanThreads) scan_down_kernel(
     const uint64_t i = b0 + (uint64_t)e;
     if (i < n) out[i] = stage[(e / kScanItems) * kRow + e % kScanItems];
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = base + all;
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) post_total(base + all, total, mailbox);
 }
 
 // One workgroup: the scan of up to kScanFewThreads * 16 counts, 16 or fewer
@@ -166,7 +174,7 @@ __global__ void __launch_bounds__(kScanThreads) scan_down_kernel(
 constexpr int kScanFewThreads = 1024;
 __global__ void __launch_bounds__(kScanFewThreads) scan_few_kernel(
     const uint32_t* __restrict__ cnt, uint32_t n, uint64_t* __restrict__ out,
-    uint64_t* __restrict__ total) {
+    uint64_t* __restrict__ total, uint64_t* __restrict__ mailbox) {
   __shared__ uint64_t wsum[kScanFewThreads / kWave];
   const uint32_t per = ((n + kScanFewThreads - 1) / kScanFewThreads + 3) & ~3u;
   const uint32_t i0 = threadIdx.x * per;
@@ -195,7 +203,7 @@ __global__ void __launch_bounds__(kScanFewThreads) scan_few_kernel(
     if (k < per && i0 + k < n) out[i0 + k] = run;
     run += v[k];
   }
-  if (threadIdx.x == 0) *total = all;
+  if (threadIdx.x == 0) post_total(all, total, mailbox);
 }
 
 // ---------------------------------------------------------------------------
@@ -1094,12 +1102,12 @@ bool rank_records(uint64_t m) { return m > 0 && m <= kRankRecords; }
 void launch_rank_records(hipStream_t st, const uint32_t* keys, const uint32_t* vals, uint64_t m,
                          const uint2* trect, uint32_t* keys_out, uint32_t* vals_out,
                          uint32_t* cnt_sorted, uint2* trect_sorted, uint64_t* offsets,
-                         uint64_t* total) {
+                         uint64_t* total, uint64_t* mailbox) {
   hipLaunchKernelGGL(rank_records_kernel, dim3(blocks_for(m, kWave)), dim3(kRankWaves * kWave), 0,
                      st, keys, vals, (uint32_t)m, trect, keys_out, vals_out, cnt_sorted,
                      trect_sorted);
   hipLaunchKernelGGL(scan_few_kernel, dim3(1), dim3(kScanFewThreads), 0, st, cnt_sorted,
-                     (uint32_t)m, offsets, total);
+                     (uint32_t)m, offsets, total, mailbox);
 }
 
 // The records in ascending order of size class; *first (unless NULL)
@@ -1182,7 +1190,7 @@ bool launch_tile_sort(hipStream_t st, void* keys_a, uint32_t* vals_a, void* keys
 void launch_offsets_scan(hipStream_t st, const uint32_t* skey, const uint32_t* perm,
                          const uint2* trect, uint64_t m, uint32_t* cnt_sorted,
                          uint2* trect_sorted, uint64_t* offsets, uint64_t* block_tmp,
-                         uint64_t* total) {
+                         uint64_t* total, uint64_t* mailbox) {
   if (m == 0) {
     launch_fill_u32(st, (uint32_t*)total, 2, 0u);
     return;
@@ -1197,7 +1205,7 @@ void launch_offsets_scan(hipStream_t st, const uint32_t* skey, const uint32_t* p
     hipLaunchKernelGGL(gather_counts_kernel<kScanFew>, grid, block, 0, st, m, skey, perm, trect,
                        cnt_sorted, trect_sorted, block_tmp);
   hipLaunchKernelGGL(scan_down_kernel, dim3(blocks_for(m, kScanTile)), block, 0, st, cnt_sorted,
-                     m, block_tmp, (unsigned)kScanItems / items, offsets, total);
+                     m, block_tmp, (unsigned)kScanItems / items, offsets, total, mailbox);
 }
 
 void launch_ranges(hipStream_t st, const void* keys, int bits, const uint64_t* k_dev,
