@@ -300,8 +300,8 @@ struct BwdLds {
 
 template <int TW, int TH, int PIX, bool MEDIAN, BwdPass PASS>
 __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_kernel(
-    double2* __restrict__ maps, int n_tiles, int groups, const uint32_t* __restrict__ order, int n_frames,
-    const FrameDesc* __restrict__ frames, const uint2* __restrict__ ranges,
+    double2* __restrict__ maps, int n_tiles, int groups, const uint32_t* __restrict__ order,
+    int n_frames, const FrameDesc* __restrict__ frames, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ vals, const Record* __restrict__ rec,
     const uint32_t* __restrict__ keyoff, const uint32_t* __restrict__ tile_nproc, float bg0,
     float bg1, float bg2, const float* __restrict__ g_rgb, const float* __restrict__ g_depth,
@@ -671,9 +671,9 @@ static void launch_bwd_t(hipStream_t st, int pix, int n_tiles, int groups, const
   }
   const auto go = [&](auto* k, int parts) {
     hipLaunchKernelGGL(k, dim3(grid_of(n_tiles, groups), (unsigned)parts), dim3(TW * TH / PIX), 0,
-                       st, maps, n_tiles, groups, order, F, frames, ranges, vals, rec, keyoff, nproc, bg[0], bg[1],
-                       bg[2], g_rgb, g_depth, g_alpha, t_final, n_last, partial, stamp, epoch,
-                       med_pos);
+                       st, maps, n_tiles, groups, order, F, frames, ranges, vals, rec, keyoff,
+                       nproc, bg[0], bg[1], bg[2], g_rgb, g_depth, g_alpha, t_final, n_last,
+                       partial, stamp, epoch, med_pos);
   };
   if constexpr (PIX == 1) {
     if (segments > 1) {

@@ -621,22 +621,39 @@ __global__ void __launch_bounds__(WAVES * kWave) radix_scatter_kernel(
     uint32_t tot[DPT], mine = 0;
 #pragma unroll
     for (int j = 0; j < DPT; ++j) offs[j] = tot[j] = 0;
-    if (d0 < bins) {  // bins % DPT == 0: DPT is 1, or 4 with 512 digits or more
-      for (unsigned r0 = 0; r0 < nb; r0 += kBatch) {
+    // fewer digits than threads: every parts-th row each, so that the threads
+    // read whole lines; bins % DPT == 0 (DPT is 1, or 4 with 512 digits or more)
+    const unsigned parts = DPT == 1 ? max((unsigned)kThreads >> width, 1u) : 1u;
+    const unsigned part = DPT == 1 ? threadIdx.x >> width : 0u;
+    const unsigned dw = DPT == 1 ? threadIdx.x & (bins - 1) : d0;
+    if (part < parts && dw < bins) {
+      for (unsigned r0 = part; r0 < nb; r0 += kBatch * parts) {
         uint32_t v[kBatch][DPT];
 #pragma unroll
         for (int r = 0; r < kBatch; ++r)
 #pragma unroll
           for (int j = 0; j < DPT; ++j)
-            v[r][j] = r0 + r < nb ? offsets[(uint64_t)(r0 + r) * bins + d0 + j] : 0u;
+            v[r][j] = r0 + r * parts < nb ? offsets[(uint64_t)(r0 + r * parts) * bins + dw + j]
+                                          : 0u;
 #pragma unroll
         for (int r = 0; r < kBatch; ++r)
 #pragma unroll
           for (int j = 0; j < DPT; ++j) {
             tot[j] += v[r][j];
-            offs[j] += r0 + r < b ? v[r][j] : 0u;
+            offs[j] += r0 + r * parts < b ? v[r][j] : 0u;
           }
       }
+    }
+    if (DPT == 1 && parts > 1) {  // uniform
+      L.sk[threadIdx.x] = tot[0];
+      L.sv[threadIdx.x] = offs[0];
+      __syncthreads();
+      tot[0] = offs[0] = 0;
+      if (threadIdx.x < bins)
+        for (unsigned q = 0; q < parts; ++q) {
+          tot[0] += L.sk[q * bins + threadIdx.x];
+          offs[0] += L.sv[q * bins + threadIdx.x];
+        }
     }
 #pragma unroll
     for (int j = 0; j < DPT; ++j) mine += tot[j];
@@ -871,7 +888,8 @@ __global__ void __launch_bounds__(256) keygen_kernel(
     __builtin_amdgcn_wave_barrier();
     const uint64_t sm = __ballot(s_mark[w][lane] == round);
     const uint32_t upto =
-        __builtin_amdgcn_mbcnt_hi((uint32_t)(sm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)sm, 0u)) +
+        __builtin_amdgcn_mbcnt_hi((uint32_t)(sm >> 32),
+                                  __builtin_amdgcn_mbcnt_lo((uint32_t)sm, 0u)) +
         (uint32_t)((sm >> lane) & 1ull);
     const uint32_t owner = (before + upto - 1u) & (kWave - 1);
     before += (uint32_t)__popcll(sm);
@@ -988,11 +1006,11 @@ static int max_digit_width(int bits) {
 }
 
 // Up to this many counts every scatter block walks down the columns itself,
-// which takes the three column kernels out of the pass: with 256 digits, 8
-// blocks 2 + 9 us (histogram + scatter) against 2 + 5 + 8, 32 blocks 5 + 10
-// against 4 + 8 + 8, 125 blocks 5 + 16 against 5 + 13 + 10, and three launches
-// saved; with 1024 digits the walks have overtaken the kernels at a few
-// hundred blocks (4 + 32 against 3 + 9 + 14).
+// which takes the three column kernels out of the pass.  Scatter alone against
+// column kernels + scatter (us; three launches saved are worth 6 more): 256
+// digits, 32 blocks 10 / 8 + 8, 147 blocks 18 / 14 + 10, 244 blocks 25 / 14 +
+// 12; 32 and 64 digits, 290 blocks 11 and 14 / 8 + 9, 1,200 blocks 25 and 33 /
+// 14 + 17.
 constexpr uint64_t kFoldCounts = 1u << 16;
 
 // Workspace bounds use the smallest block of a pass with column kernels (4

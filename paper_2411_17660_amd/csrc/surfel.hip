@@ -1108,8 +1108,8 @@ static void launch_bwd_t(hipStream_t st, int pix, int n_tiles, int groups, const
     if (pix < PIX) {
       launch_bwd_t<TW, TH, PIX / 2>(st, pix, n_tiles, groups, order, F, frames, ranges, vals, rec,
                                     keyoff, bg, g_rgb, g_depth, g_alpha, g_normal, g_dist,
-                                    t_final, n_last, dist_aux, partial, stamp, epoch, nproc, segments,
-                                    maps);
+                                    t_final, n_last, dist_aux, partial, stamp, epoch, nproc,
+                                    segments, maps);
       return;
     }
   }
