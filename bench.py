@@ -760,11 +760,11 @@ def measured_traffic(kernel, tile):
     taken."""
     import re
     path = os.path.join(ROOT, "profiles", "c3_hbm_traffic_pmc.md")
-    if not os.path.exists(path) or tuple(tile) != (16, 16):
+    if not os.path.exists(path):
         return None
     sha = compositing_sources_sha256(ROOT)
     for line in open(path):
-        m = re.search(r"traffic (\w+)<16, 16> bytes_per_launch=(\d+) "
+        m = re.search(r"traffic (\w+)<%d, %d> bytes_per_launch=(\d+) " % tuple(tile) +
                       r"compositing_sources_sha256=(\w+)", line)
         if m and m.group(1) == kernel + "_kernel" and m.group(3) == sha:
             return int(m.group(2))
