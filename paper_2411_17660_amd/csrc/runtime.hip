@@ -211,8 +211,9 @@ gsr_status gsr_create(gsr_context** out, int32_t device) {
   if (!ctx) return GSR_ERR_OUT_OF_MEMORY;
   ctx->device = device;
   if (loss_scratch_init(device, &ctx->loss_scratch) != hipSuccess ||
-      hipHostMalloc((void**)&ctx->h_count, sizeof(uint64_t) * 8, hipHostMallocDefault) !=
-          hipSuccess) {
+      // (coherent: the host watches a kernel's store)
+      hipHostMalloc((void**)&ctx->h_count, sizeof(uint64_t) * 8,
+                    hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
     delete ctx;
     return GSR_ERR_HIP;
   }
