@@ -320,8 +320,12 @@ struct StoreOrder {
 };
 
 // Digit counts of one block's keys.  A count does not depend on the order,
-// so each thread loads 16 bytes of keys at once and bumps its wave's LDS
-// counters with atomics; the wave histograms are summed.
+// so each thread loads 16 bytes of keys at once and bumps LDS counters with
+// atomics.  The rate of these bounds the kernel (about 23 clocks per wave and
+// key), and lanes of one wave that meet in a counter are served one after the
+// other: with up to 256 digits a wave has four copies of its counters, 16
+// banks apart, for the lanes mod 4.  All are summed at the end.  111M 16-bit
+// keys: 77 us with one copy, 67 with four (2M 32-bit keys, 256 digits: 6.4 / 4.9).
 template <int BINS, int WAVES, int R, typename Load>
 __global__ void __launch_bounds__(256) radix_hist_kernel(
     Load in, const uint64_t* n_dev, uint64_t n_host, int shift,
@@ -330,15 +334,17 @@ __global__ void __launch_bounds__(256) radix_hist_kernel(
   constexpr int kHW = 256 / kWave;  // waves of this kernel
   constexpr int kPer = Load::kPer;
   static_assert(kTile % (kPer * 256) == 0, "whole 16-byte loads");
-  __shared__ uint32_t wcnt[kHW][BINS];
+  constexpr int kCopies = BINS == 256 ? 4 : 1;
+  constexpr int kStride = BINS + (kCopies > 1 ? 16 : 0);
+  __shared__ uint32_t wcnt[kHW * kCopies][kStride];
   const uint64_t n = n_dev ? min(*n_dev, n_host) : n_host;
   const int bins = 1 << width;
   const uint32_t mask = (uint32_t)bins - 1u;
   const int w = threadIdx.x / kWave;
-  for (int i = threadIdx.x; i < kHW * BINS; i += 256) (&wcnt[0][0])[i] = 0;
+  for (int i = threadIdx.x; i < kHW * kCopies * kStride; i += 256) (&wcnt[0][0])[i] = 0;
   __syncthreads();
   const uint64_t bbase = (uint64_t)blockIdx.x * kTile;
-  uint32_t* cw = wcnt[w];
+  uint32_t* cw = wcnt[w * kCopies + (threadIdx.x & (kCopies - 1))];
 #pragma unroll
   for (int j = 0; j < kTile / (kPer * 256); ++j) {
     const uint64_t i = bbase + kPer * ((uint64_t)threadIdx.x + (uint64_t)j * 256);
@@ -355,7 +361,7 @@ __global__ void __launch_bounds__(256) radix_hist_kernel(
   __syncthreads();
   for (int d = threadIdx.x; d < bins; d += 256) {
     uint32_t c = 0;
-    for (int ww = 0; ww < kHW; ++ww) c += wcnt[ww][d];
+    for (int ww = 0; ww < kHW * kCopies; ++ww) c += wcnt[ww][d];
     hist[(uint64_t)blockIdx.x * bins + d] = c;
   }
 }
