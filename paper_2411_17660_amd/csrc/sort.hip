@@ -1098,13 +1098,13 @@ static void radix_pass_any(hipStream_t st, Load in, Store out, const uint64_t* n
 // Up to here the order comes from counting pairs.  Its time grows with the
 // square of the count, that of the passes hardly at all below 10^5.  Measured
 // (us of kernel time, counting against the two-launch passes; each launch
-// saved is worth 2 to 3 us more): records 1000: 9 (2 launches) against 50
-// (10), 8000: 23 / 61, 16000: 40 / 61, 32000: 86 / 62; tile keys, two passes
-// of 4 launches, 8000: 10 / 24; size classes 4000: 9 / 15 (2 launches), 8000:
-// 16 / 14, 16000: 27 / 15.
+// saved is worth 2 to 5 us more): records (with the offsets) 1000: 10 (2
+// launches) / 37 (10), 8000: 23 / 48, 16000: 40 / 53, 32000: 86 / 60; tile
+// keys of two passes, 8000: 10 / 17 (4 launches); size classes 4000: 10 / 13 (2
+// launches), 8000: 17 / 11.
 constexpr uint64_t kRankRecords = 16384;
 constexpr uint64_t kRankKeys = 8192;
-constexpr uint64_t kRankClasses = 8192;
+constexpr uint64_t kRankClasses = 4096;
 
 // Stable sort of the records (keys, vals) by their 32 depth bits, 8-bit
 // digits, then launch_offsets_scan over the sorted records.  Ends in
