@@ -232,10 +232,9 @@ struct SurfelHit {
 // alpha < 1/255 either way).
 constexpr float kLowpassReach = 5.6f;
 
-// The fields of an entry that every pixel strip reads, and the part of the
+// The fields of an entry that a pixel's row reads, and the part of the
 // intersection fixed by the lane's pixel column (h_u = (x - c_x) M2 + k_u
-// does not depend on the row): formed once per entry, in registers, instead
-// of once per strip from LDS.
+// does not depend on the row).
 struct SurfelEntry {
   float cyh, cyl, m2x, m2y, kvx, kvy, zc, opacity;  // the record's row fields
   float ex, hux, huy, huz;                          // the column's part
