@@ -359,7 +359,6 @@ __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_
   double E[PIX], H0[PIX], H1[PIX], H2[PIX], HZ[PIX];
   int last[PIX], mp[PIX];  // mp: MEDIAN, the list position of the pixel's depth
   uint32_t most[PIX];      // the block's longest walk (wave-uniform)
-  bool odd = false;        // a pixel's upstream gradient is not finite
 #pragma unroll
   for (int k = 0; k < PIX; ++k) {
     const int px = px0 + (k % kCols) * kBlk, py = py0 + (k / kCols) * kBlk;
@@ -395,12 +394,10 @@ __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_
       }
       T[k] = (float)t;
     }
-    odd |= !isfinite(H0[k] + H1[k] + H2[k] + HZ[k]);
     int mx = max(last[k], 0);
     for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, kWave));
     most[k] = __builtin_amdgcn_readfirstlane((uint32_t)mx);
   }
-  odd = __ballot(odd) != 0;  // (wave-uniform)
   double through = 1.0;  // kBwdMaps: the product of 1 - alpha
   // right operands: powers of Y by block row (k the row pair) and of X by
   // block column, unit columns for the colours
@@ -538,29 +535,30 @@ __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_
             __builtin_amdgcn_mfma_f64_4x4x4f64((double)p, wy[k / kCols], my[k % kCols], 0, 0, 0);
       }
       if (PASS == kBwdMaps || hit == 0) continue;
-      double tot = __builtin_amdgcn_mfma_f64_4x4x4f64(my[0], wx[0], 0.0, 0, 0, 0);
+      double mom = __builtin_amdgcn_mfma_f64_4x4x4f64(my[0], wx[0], 0.0, 0, 0, 0);
 #pragma unroll
       for (int c = 1; c < kCols; ++c)
-        tot = __builtin_amdgcn_mfma_f64_4x4x4f64(my[c], wx[c], tot, 0, 0, 0);
-      if (!odd) {
-        double cs = __builtin_amdgcn_mfma_f64_4x4x4f64(gc0, unit[0], 0.0, 0, 0, 0);
-        cs = __builtin_amdgcn_mfma_f64_4x4x4f64(gc1, unit[1], cs, 0, 0, 0);
-        cs = __builtin_amdgcn_mfma_f64_4x4x4f64(gc2, unit[2], cs, 0, 0, 0);
-        cs = __builtin_amdgcn_mfma_f64_4x4x4f64(gz, unit[3], cs, 0, 0, 0);
-        tot = __builtin_amdgcn_mfma_f64_4x4x4f64(cs, unit[3], tot, 0, 0, 0);
-      } else {
-        // zeros times a value that is not finite would spread it over the
-        // other sums: sum each colour by itself and select
+        mom = __builtin_amdgcn_mfma_f64_4x4x4f64(my[c], wx[c], mom, 0, 0, 0);
+      double cs = __builtin_amdgcn_mfma_f64_4x4x4f64(gc0, unit[0], 0.0, 0, 0, 0);
+      cs = __builtin_amdgcn_mfma_f64_4x4x4f64(gc1, unit[1], cs, 0, 0, 0);
+      cs = __builtin_amdgcn_mfma_f64_4x4x4f64(gc2, unit[2], cs, 0, 0, 0);
+      cs = __builtin_amdgcn_mfma_f64_4x4x4f64(gz, unit[3], cs, 0, 0, 0);
+      double tot = __builtin_amdgcn_mfma_f64_4x4x4f64(cs, unit[3], mom, 0, 0, 0);
+      if (__builtin_expect(__ballot(!isfinite(tot)) != 0, 0)) {
+        // A p or colour sum that is not finite (an upstream gradient or a
+        // colour that is not, a p that overflows) has met the zeros of the
+        // others' columns: sum each colour by itself and select.  Every such
+        // value is seen here, as each also meets a one.
         const int col = lane & 3;
         const double v[4] = {gc0, gc1, gc2, gz};
-        double cs = 0.0;
+        cs = 0.0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           const double d = __builtin_amdgcn_mfma_f64_4x4x4f64(v[c], 1.0, 0.0, 0, 0, 0);
           if (col == c) cs = d;
         }
         cs = __builtin_amdgcn_mfma_f64_4x4x4f64(cs, 1.0, 0.0, 0, 0, 0);
-        if (col == 3) tot = cs;
+        tot = col == 3 ? cs : mom;
       }
       gc0 = gc1 = gc2 = gz = 0.0;
       asm volatile("" : "+v"(gc0), "+v"(gc1), "+v"(gc2), "+v"(gz));

@@ -563,7 +563,6 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
   double E[PIX], H0[PIX], H1[PIX], H2[PIX], HD[PIX], HN0[PIX], HN1[PIX], HN2[PIX], HE[PIX];
   int last[PIX];
   int most[PIX];     // the block's longest walk (wave-uniform)
-  bool odd = false;  // a pixel's upstream gradient is not finite
 #pragma unroll
   for (int k = 0; k < PIX; ++k) {
     const int px = bx0 + (k % kCols) * kBlk + (lane & 7);
@@ -590,7 +589,6 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
     HD[k] = valid ? g_depth[q] : 0.0f;
     HE[k] = valid ? g_dist[q] : 0.0f;
     const double ha = valid ? g_alpha[q] : 0.0f;
-    odd |= !isfinite(H0[k] + H1[k] + H2[k] + HN0[k] + HN1[k] + HN2[k] + HD[k] + HE[k]);
     // behind the last entry: the background colour, zero depth, normal, e and
     // alpha (less G_A, the share of every entry's alpha of 1 in G . v_i)
     E[k] = __builtin_fma(H2[k], (double)bg2,
@@ -614,7 +612,6 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
     most[k] = __builtin_amdgcn_readfirstlane(mx);
   }
   double through = 1.0;  // kBwdMaps: the product of 1 - alpha
-  odd = __ballot(odd) != 0;  // (wave-uniform)
   double unit[4];  // right operands: unit columns
 #pragma unroll
   for (int c = 0; c < 4; ++c) unit[c] = (lane & 3) == c ? 1.0 : 0.0;
@@ -767,18 +764,17 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
       }
       if (PASS == kBwdMaps || hit == 0) continue;
       double tot = 0.0;
-      if (!odd) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          double d = 0.0;
+      for (int g = 0; g < 4; ++g) {
+        double d = 0.0;
 #pragma unroll
-          for (int c = 0; c < 4; ++c)
-            d = __builtin_amdgcn_mfma_f64_4x4x4f64(acc[4 * g + c], unit[c], d, 0, 0, 0);
-          tot = __builtin_amdgcn_mfma_f64_4x4x4f64(d, unit[g], tot, 0, 0, 0);
-        }
-      } else {
-        // zeros times a value that is not finite would spread it over the
-        // other sums: sum each value by itself and select
+        for (int c = 0; c < 4; ++c)
+          d = __builtin_amdgcn_mfma_f64_4x4x4f64(acc[4 * g + c], unit[c], d, 0, 0, 0);
+        tot = __builtin_amdgcn_mfma_f64_4x4x4f64(d, unit[g], tot, 0, 0, 0);
+      }
+      if (__builtin_expect(__ballot(!isfinite(tot)) != 0, 0)) {
+        // a value that is not finite has met the zeros of the others' columns:
+        // sum each value by itself and select
         const int col = lane & 3;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
