@@ -258,11 +258,13 @@ namespace {
 // h_count[kMailbox]: the key count posted by the forward's scan.  Watching it
 // saves the copy behind the scan and the runtime's wait (about 10 us per
 // forward); the stream is asked now and then, so that an error ends the wait.
+// Every return comes after the post, or once the stream has nothing left that
+// could post: a count that arrived later would be taken for the next forward's.
 constexpr int kMailbox = 7;
 constexpr uint64_t kNoCount = ~0ull;
 
 gsr_status await_count(gsr_context* ctx, hipStream_t st, uint64_t* out) {
-  GSR_HIP(hipGetLastError());
+  const hipError_t before = hipGetLastError();  // of the launches, or of an earlier call
   const uint64_t* box = ctx->h_count + kMailbox;
   uint64_t v;
   for (uint32_t i = 1; (v = __atomic_load_n(box, __ATOMIC_ACQUIRE)) == kNoCount; ++i) {
@@ -272,9 +274,11 @@ gsr_status await_count(gsr_context* ctx, hipStream_t st, uint64_t* out) {
     if (e == hipErrorNotReady) continue;
     GSR_HIP(hipStreamSynchronize(st));
     v = __atomic_load_n(box, __ATOMIC_ACQUIRE);
+    GSR_HIP(before);
     if (v == kNoCount) return fail(ctx, GSR_ERR_HIP, "the key count did not arrive");
     break;
   }
+  GSR_HIP(before);
   *out = v;
   return GSR_OK;
 }
