@@ -100,9 +100,9 @@ void launch_composite_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           const uint32_t* prev_nproc, uint32_t* order, bool xcd_groups,
                           unsigned long long* pairs, int32_t* med_pos);
 // The segments that the backward cuts every tile's list into (1: none), and
-// the bytes of each pixel's state change over them (`maps`).
+// the bytes that the pixels' state changes over them (`maps`) may need.
 int bwd_segments(uint64_t keys, int64_t n_tiles, int tw, int th);
-size_t bwd_map_bytes(int segments, int64_t n_tiles, int tw, int th);
+size_t bwd_map_bytes(int64_t n_tiles, int tw, int th);
 void launch_composite_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
                           const Record* rec, const uint32_t* keyoff, const uint32_t* nproc,

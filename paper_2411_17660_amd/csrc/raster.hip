@@ -715,14 +715,20 @@ void launch_composite_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
 // (1,344 waves, 235) 80 / 62; but 400x300 (1,900, 210) 71 / 73 and 640x480
 // (4,800, 965) 229 / 294, where the state pass costs more than the idle SIMDs,
 // and 97x81 (168, 59), whose lists are one batch, 24 / 28.
+constexpr int64_t kFewWaves = 1536;
+constexpr int kSegments = 8;
+
 int bwd_segments(uint64_t keys, int64_t n_tiles, int tw, int th) {
-  constexpr int64_t kFewWaves = 1536;
   const bool few = n_tiles * (tw * th / kWave) <= kFewWaves;
-  return few && keys >= 2 * kBatchB * (uint64_t)n_tiles ? 8 : 1;
+  return few && keys >= 2 * kBatchB * (uint64_t)n_tiles ? kSegments : 1;
 }
 
-size_t bwd_map_bytes(int segments, int64_t n_tiles, int tw, int th) {
-  return (size_t)n_tiles * tw * th * (segments - 1) * sizeof(double2);
+// For every key count and every smaller number of tiles (11 MB at most), so
+// that a call which takes segments needs no more than a larger one before it
+// that took none: a capture may follow with fewer frames or another capacity.
+size_t bwd_map_bytes(int64_t n_tiles, int tw, int th) {
+  const int64_t waves = std::min(n_tiles * (tw * th / kWave), kFewWaves);
+  return (size_t)waves * kWave * (kSegments - 1) * sizeof(double2);
 }
 
 void launch_composite_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,

@@ -1,0 +1,89 @@
+"""A captured call needs no more workspace than an uncaptured one of the same
+or larger sizes before it, whatever way of working its sizes choose."""
+import numpy as np
+import pytest
+
+from paper_2411_17660_amd import scenes
+
+pytestmark = pytest.mark.gpu
+
+
+def _check_capture(r, outputs, call, ref_outputs, ref_call):
+    """Captures call() without an uncaptured one before it, replays it with
+    other work between the replays and compares its outputs with those of an
+    eager call on a context of its own."""
+    import torch
+    ref_call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for _ in range(3):
+        for x in outputs:
+            x.fill_(float("nan"))
+        torch.randn(1000, device="cuda").cumsum(0)
+        g.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(outputs, ref_outputs):
+            assert torch.equal(a, b)
+    r.check_overflow()
+
+
+def _fit(r, sc, surfel, n=None):
+    """(outputs, call(key_capacity)): a forward and its backward into fixed
+    buffers."""
+    import torch
+    from gpu_util import to_dev
+    d = to_dev(sc)
+    if surfel:
+        d["log_scales"] = d["log_scales"][:, :2].contiguous()
+    d = {k: v if k == "poses" or n is None else v[:n].contiguous() for k, v in d.items()}
+    n, F, P = d["means"].shape[0], len(sc.cams), sc.n_pixels
+    ks = (3, 1, 1, 3, 1) if surfel else (3, 1, 1)
+    im = tuple(torch.empty(k * P, device="cuda") for k in ks)
+    gen = torch.Generator().manual_seed(1)
+    G = [torch.randn(k * P, generator=gen).cuda() for k in ks]
+    g = {k: torch.empty_like(d[k]) for k in ("means", "log_scales", "quats", "opacity", "sh")}
+    g["twist"] = torch.empty(F, 6, device="cuda")
+    args = [d[k] for k in ("means", "log_scales", "quats", "opacity", "sh", "poses")]
+
+    def call(cap):
+        (r.forward_surfel if surfel else r.forward)(*args, sc.cams, sc.sh_degree, sc.background,
+                                                    key_capacity=cap, out=im)
+        (r.backward_surfel if surfel else r.backward)(*G, out=g)
+    return list(im) + list(g.values()), call
+
+
+@pytest.mark.parametrize("surfel", [False, True])
+def test_capture_with_headroom_after_a_growing_step(surfel):
+    """A growing step just under 128 keys per tile, then a capture whose fixed
+    capacity, inside what that step allocated, lies above."""
+    from paper_2411_17660_amd.raster import Rasterizer
+    sc = scenes.tiny_scene(seed=7, n=2000, W=96, H=80, f=80.0, sh_degree=1, ls_mean=-2.6)
+    r = Rasterizer(0)
+    _fit(r, sc, surfel)[1](0)
+    T = r.stats()["n_tiles"]
+    keys = np.cumsum(r.debug_lists()["ntiles"])
+    n = int(np.searchsorted(keys, 126 * T))
+    assert 122 * T < keys[n - 1] < 128 * T
+    r = Rasterizer(0)
+    outputs, call = _fit(r, sc, surfel, n)
+    call(0)
+    cap = 132 * T
+    assert keys[n - 1] < 128 * T < cap <= r.stats()["key_capacity"]
+    ref_outputs, ref_call = _fit(Rasterizer(0), sc, surfel, n)
+    _check_capture(r, outputs, lambda: call(cap), ref_outputs, lambda: ref_call(cap))
+
+
+@pytest.mark.parametrize("surfel", [False, True])
+def test_capture_of_fewer_frames_after_a_larger_step(surfel):
+    """Many tiles, whose lists are taken whole, then one small frame."""
+    from paper_2411_17660_amd.raster import Rasterizer
+    large, small = (scenes.tiny_scene(seed=7, n=500, W=w, H=h, f=0.8 * w, n_frames=f, sh_degree=0,
+                                      ls_mean=-2.6) for w, h, f in ((640, 480, 2), (131, 97, 1)))
+    cap = 200000
+    r = Rasterizer(0)
+    _fit(r, large, surfel)[1](cap)
+    outputs, call = _fit(r, small, surfel)
+    ref_outputs, ref_call = _fit(Rasterizer(0), small, surfel)
+    _check_capture(r, outputs, lambda: call(cap), ref_outputs, lambda: ref_call(cap))
