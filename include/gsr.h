@@ -270,7 +270,8 @@ gsr_status gsr_step_l1(gsr_context* ctx, const gsr_settings* settings, int64_t n
  * not NULL, receives SSIM_f [n_frames] (device floats).  lambda1 and
  * lambda2 must lie in [0, 1] (GSR_ERR_INVALID_ARGUMENT otherwise);
  * GSR_ERR_STATE if no forward preceded.  The SSIM map is evaluated in FP64;
- * the workspace grows by 72 bytes per pixel. */
+ * the workspace grows by 12 bytes per pixel (g_rgb may be rgb or target_rgb
+ * itself and is then written there first). */
 gsr_status gsr_loss_render(gsr_context* ctx, const float* rgb, const float* depth,
                            const float* target_rgb, const float* target_depth, float lambda1,
                            float lambda2, float* loss, float* ssim, float* g_rgb,

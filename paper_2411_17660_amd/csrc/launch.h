@@ -130,6 +130,9 @@ struct SsimPlan {
   int chunks;       // rows per pair of waves, in elevens
   int units;        // blocks per plane of the largest frame
   int64_t max_px;   // pixels of the largest frame
+  // units of any plan for no more and no larger frames (fewer frames are cut
+  // finer), by which workspace is sized
+  int64_t units_max;
 };
 SsimPlan ssim_plan(const FrameDesc* host_frames, int F);
 void launch_loss_render(hipStream_t st, int F, const SsimPlan& plan, const FrameDesc* frames,

@@ -816,10 +816,11 @@ gsr_status gsr_loss_render(gsr_context* ctx, const float* rgb, const float* dept
   if (sv.F > 65535) return fail(ctx, GSR_ERR_UNSUPPORTED, "more than 65535 frames");
   gsr_status rc;
   // the gradient of one pixel needs its neighbours' colours: a g_rgb in the
-  // place of an image is written beside it first
+  // place of an image is written beside it first (a buffer that every call
+  // reserves: a capture in place may follow a call that was not)
   const bool in_place = g_rgb == rgb || g_rgb == target_rgb;
-  if (in_place && (rc = ensure(ctx, ctx->ssim_rgb, (size_t)sv.P * 3 * 4, st))) return rc;
-  if ((rc = ensure(ctx, ctx->ssim_tiles, (size_t)sv.F * 3 * plan.units * 4 * 8, st)))
+  if ((rc = ensure(ctx, ctx->ssim_rgb, (size_t)sv.P * 3 * 4, st))) return rc;
+  if ((rc = ensure(ctx, ctx->ssim_tiles, (size_t)sv.F * 3 * plan.units_max * 4 * 8, st)))
     return rc;
   if ((rc = ensure(ctx, ctx->ssim_scale, (size_t)sv.F * 2 * 8, st))) return rc;
   {

@@ -531,8 +531,16 @@ Window make_window() {
 // segment, fewer fill the last round better.
 SsimPlan ssim_plan(const FrameDesc* frames, int F) {
   constexpr int64_t kSimds = 1024;
-  SsimPlan best{0, 0, 0};
+  constexpr int kMinSeg = kTaps * kMinChunks - kLag;
+  SsimPlan best{0, 0, 0, 0};
   int64_t cost = 0;
+  int max_w = 1, max_h = 1;
+  for (int f = 0; f < F; ++f) {
+    max_w = std::max(max_w, (int)frames[f].width);
+    max_h = std::max(max_h, (int)frames[f].height);
+  }
+  const int64_t units_max =
+      (int64_t)((max_w + kOutCols - 1) / kOutCols) * ((max_h + kMinSeg - 1) / kMinSeg);
   for (int c = kMinChunks; c <= kMaxChunks; ++c) {
     const int seg = kTaps * c - kLag;
     int64_t pairs = 0, most = 0, px = 0;
@@ -546,7 +554,7 @@ SsimPlan ssim_plan(const FrameDesc* frames, int F) {
     const int64_t rounds = (pairs + kSimds - 1) / kSimds;
     if (best.chunks == 0 || rounds * c <= cost) {
       cost = rounds * c;
-      best = SsimPlan{c, (int)most, px};
+      best = SsimPlan{c, (int)most, px, units_max};
     }
   }
   return best;

@@ -87,3 +87,36 @@ def test_capture_of_fewer_frames_after_a_larger_step(surfel):
     outputs, call = _fit(r, small, surfel)
     ref_outputs, ref_call = _fit(Rasterizer(0), small, surfel)
     _check_capture(r, outputs, lambda: call(cap), ref_outputs, lambda: ref_call(cap))
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("frames", [6, 5])
+def test_capture_of_the_rendering_loss(frames, in_place):
+    """The SSIM of six frames, uncaptured into a buffer of its own; then a
+    capture of as many or of five, whose rows are cut finer, or with the colour
+    gradient over the image."""
+    import torch
+    from gpu_util import to_dev
+    from paper_2411_17660_amd.raster import Rasterizer
+    W, H = 320, 240
+
+    def fit(r, F, over):
+        sc = scenes.tiny_scene(seed=7, n=300, W=W, H=H, f=200.0, n_frames=F, sh_degree=0,
+                               ls_mean=-2.6)
+        d, P = to_dev(sc), sc.n_pixels
+        target = [torch.from_numpy(np.ascontiguousarray(x, np.float32)).cuda()
+                  for x in scenes.loss_images(3, [(W, H)] * F, depth_invalid=0.2)[2:]]
+        im = tuple(torch.empty(k * P, device="cuda") for k in (3, 1, 1))
+        out = dict(loss=torch.empty(1, device="cuda"), ssim=torch.empty(F, device="cuda"),
+                   g_rgb=im[0] if over else torch.empty(3 * P, device="cuda"),
+                   g_depth=torch.empty(P, device="cuda"), g_alpha=torch.empty(P, device="cuda"))
+
+        def call():
+            r.forward(*[d[k] for k in ("means", "log_scales", "quats", "opacity", "sh", "poses")],
+                      sc.cams, 0, sc.background, key_capacity=100000, out=im)
+            r.loss_render(im[0], im[1], *target, out=out)
+        return list(out.values()), call
+    r = Rasterizer(0)
+    fit(r, 6, False)[1]()
+    outputs, call = fit(r, frames, in_place)
+    _check_capture(r, outputs, call, *fit(Rasterizer(0), frames, False))
