@@ -1026,8 +1026,10 @@ size_t radix_hist_elems(uint64_t n_max, int bits) {
   const size_t blocks = blocks_for(n_max, RadixShape<4, kSortRounds>::kTile);
   return std::max<size_t>(kFoldCounts, blocks << std::max(wmax, 8));
 }
+// (not fewer for a larger count)
 size_t scan_block_elems(uint64_t n_max) {
-  return blocks_for(n_max, (n_max > kGatherBig ? kScanItems : kScanFew) * kScanThreads);
+  return std::max(blocks_for(std::min(n_max, kGatherBig), kScanFew * kScanThreads),
+                  blocks_for(n_max, kScanTile));
 }
 // u32 elements of the column scan's chunk sums for up to n_max keys (an upper
 // bound for every smaller count as well)
