@@ -125,12 +125,26 @@ __device__ __forceinline__ void post_total(uint64_t v, uint64_t* total, uint64_t
   if (mailbox) __hip_atomic_store(mailbox, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// One workgroup: the sums of nb blocks become the sums in front of each.
+constexpr int kSpineThreads = 1024;
+__global__ void __launch_bounds__(kSpineThreads) scan_spine_kernel(uint64_t* __restrict__ sums,
+                                                                   unsigned nb) {
+  __shared__ uint64_t wsum[kSpineThreads / kWave];
+  uint64_t run = 0, all;
+  for (unsigned b0 = 0; b0 < nb; b0 += kSpineThreads) {
+    const unsigned b = b0 + threadIdx.x;
+    const uint64_t front = run + block_scan_excl<uint64_t>(b < nb ? sums[b] : 0u, wsum, all);
+    if (b < nb) sums[b] = front;
+    run += all;
+  }
+}
+
 // Exclusive scan of cnt into out.  A block adds up the sums (`per` of them for
 // each scan block) in front of it by itself, which costs less than a launch
-// between the two kernels.  Its kScanTile elements
-// pass through LDS rows of kScanItems + 1 (padded against bank conflicts) so
-// that global loads and stores are coalesced while each thread scans
-// kScanItems consecutive elements.
+// between the two kernels, or (per = 0) finds that in block_sums.  Its kScanTile
+// elements pass through LDS rows of kScanItems + 1 (padded against bank
+// conflicts) so that global loads and stores are coalesced while each thread
+// scans kScanItems consecutive elements.
 __global__ void __launch_bounds__(kScanThreads) scan_down_kernel(
     const uint32_t* __restrict__ cnt, uint64_t n, const uint64_t* __restrict__ block_sums,
     unsigned per, uint64_t* __restrict__ out, uint64_t* __restrict__ total,
@@ -146,6 +160,7 @@ __global__ void __launch_bounds__(kScanThreads) scan_down_kernel(
     stage[(e / kScanItems) * kRow + e % kScanItems] = i < n ? (uint64_t)cnt[i] : 0u;
   }
   uint64_t front = 0, base, all;
+  if (per == 0 && threadIdx.x == 0) front = block_sums[blockIdx.x];
   for (unsigned b = threadIdx.x; b < blockIdx.x * per; b += kScanThreads) front += block_sums[b];
   block_scan_excl<uint64_t>(front, wsum, base);  // (its barriers also cover stage)
   uint64_t v[kScanItems];
@@ -1210,6 +1225,14 @@ bool launch_tile_sort(hipStream_t st, void* keys_a, uint32_t* vals_a, void* keys
                                scan_tmp);
 }
 
+// Beyond this many scan blocks the sums in front of them come from a kernel of
+// their own: adding them up in every block grows with the square of the count.
+// Without / with it (us, the scan, and with it the sums' kernel too): 1,280
+// blocks 19 / 19 + 5, 4,096 (17M records) 66 / 54 + 8, 8,192 160 / 138 + 15,
+// 32,768 (134M) 988 / 525 + 60.
+constexpr unsigned kSpineBlocks = 4096;
+static_assert(kSpineBlocks >= kGatherBig / kScanTile, "one sum per scan block");
+
 // Exclusive scan of the depth-ordered records' tile counts into offsets
 // (u64), total into *total; cnt_sorted[i] and trect_sorted[i] receive the
 // count and the tile rect of record perm[i] (zero for a culled record).
@@ -1230,8 +1253,11 @@ void launch_offsets_scan(hipStream_t st, const uint32_t* skey, const uint32_t* p
   else
     hipLaunchKernelGGL(gather_counts_kernel<kScanFew>, grid, block, 0, st, m, skey, perm, trect,
                        cnt_sorted, trect_sorted, block_tmp);
-  hipLaunchKernelGGL(scan_down_kernel, dim3(blocks_for(m, kScanTile)), block, 0, st, cnt_sorted,
-                     m, block_tmp, (unsigned)kScanItems / items, offsets, total, mailbox);
+  const unsigned nb = blocks_for(m, kScanTile);
+  const bool spine = nb > kSpineBlocks;
+  if (spine) hipLaunchKernelGGL(scan_spine_kernel, dim3(1), dim3(kSpineThreads), 0, st, block_tmp, nb);
+  hipLaunchKernelGGL(scan_down_kernel, dim3(nb), block, 0, st, cnt_sorted, m, block_tmp,
+                     spine ? 0u : kScanItems / items, offsets, total, mailbox);
 }
 
 void launch_ranges(hipStream_t st, const void* keys, int bits, const uint64_t* k_dev,
