@@ -1026,13 +1026,21 @@ static int max_digit_width(int bits) {
   return mx;
 }
 
-// Up to this many counts every scatter block walks down the columns itself,
-// which takes the three column kernels out of the pass.  Scatter alone against
+// Up to this many counts, and this many read by all blocks together, every
+// scatter block walks down the columns itself, which takes the three column
+// kernels out of the pass.  The first bounds a block's own serial walk, the
+// second what the walks of many blocks cost in all.  Scatter alone against
 // column kernels + scatter (us; three launches saved are worth 6 more): 256
 // digits, 32 blocks 10 / 8 + 8, 147 blocks 18 / 14 + 10, 244 blocks 25 / 14 +
-// 12; 32 and 64 digits, 290 blocks 11 and 14 / 8 + 9, 1,200 blocks 25 and 33 /
-// 14 + 17.
+// 12; 64 digits, 512 blocks 18 / 14 + 11, 1,024 blocks 36 / 14 + 16; 32 digits,
+// 1,200 blocks 35 / 13 + 18, 1,536 blocks 43 / 11 + 20, 2,048 blocks 63 / 12 +
+// 25; 8 digits, 2,048 blocks 38 / 14 + 26, 4,096 blocks 83 / 14 + 47.
 constexpr uint64_t kFoldCounts = 1u << 16;
+constexpr uint64_t kFoldReads = 3u << 24;
+
+constexpr bool walk_columns(uint64_t nb, int width) {
+  return (nb << width) <= kFoldCounts && ((nb * nb) << width) <= kFoldReads;
+}
 
 // Workspace bounds use the smallest block of a pass with column kernels (4
 // waves, 4096 keys); the others have at most kFoldCounts counts.
@@ -1077,7 +1085,7 @@ static void radix_pass(hipStream_t st, Load in, Store out, const uint64_t* n_dev
   const dim3 grid(per * kXcds), block(RadixShape<WAVES, R>::kThreads);
   hipLaunchKernelGGL((radix_hist_kernel<BINS, WAVES, R, Load>), dim3(nb), dim3(256), 0, st, in,
                      n_dev, n_max, shift, width, hist);
-  if (((uint64_t)nb << width) <= kFoldCounts) {
+  if (walk_columns(nb, width)) {
     hipLaunchKernelGGL((radix_scatter_kernel<BINS, WAVES, R, true, Load, Store>), grid, block, 0,
                        st, in, n_dev, n_max, shift, width, nb, per, hist, out);
     return;
@@ -1096,7 +1104,7 @@ constexpr uint64_t kBigPass = 1ull << 24;
 // column walks have grown past the gain).
 constexpr int kFewRounds = 8;
 constexpr uint64_t kFewPass = 1u << 17;
-static_assert(kFewPass / RadixShape<4, kFewRounds>::kTile * 256 <= kFoldCounts, "columns walked");
+static_assert(walk_columns(kFewPass / RadixShape<4, kFewRounds>::kTile, 8), "columns walked");
 
 template <typename Load, typename Store>
 static void radix_pass_any(hipStream_t st, Load in, Store out, const uint64_t* n_dev,

@@ -78,3 +78,25 @@ def test_culled_records_change_nothing(rast, n, extra):
         else:
             assert torch.equal(a, out[1][1][k][:n]), k
             assert not out[1][1][k][n:].any()
+
+
+@pytest.mark.parametrize("blocks", [1254, 1255])
+def test_digit_columns_of_many_blocks(rast, blocks):
+    """5 digit bits (30 tiles, every one under every Gaussian), blocks of 4096
+    keys: the last count of blocks whose scatter walks the columns, and the
+    first whose columns have kernels."""
+    from gpu_util import gpu_forward
+    n = (blocks * 4096) // 30
+    assert -(-n * 30 // 4096) == blocks
+    sc = scenes.tiny_scene(seed=2, n=n, W=96, H=80, f=80.0, sh_degree=0, ls_mean=2.0, ls_sigma=0.1)
+    sc.opacity = np.full_like(sc.opacity, -3.0)
+    gpu_forward(rast, sc)
+    L = rast.debug_lists()
+    keys, vals, nt = L["tile_keys"].astype(np.int64), L["tile_vals"].astype(np.int64), L["ntiles"]
+    dk = L["depth_key"].astype(np.int64)
+    kept = nt > 0
+    assert (nt[kept] == 30).all() and -(-len(keys) // 4096) == blocks
+    # each tile's list: the kept records by (depth, index)
+    order = np.lexsort((np.arange(n), dk))[:kept.sum()]
+    np.testing.assert_array_equal(keys, np.repeat(np.arange(30), kept.sum()))
+    np.testing.assert_array_equal(vals.reshape(30, -1), np.broadcast_to(order, (30, len(order))))
