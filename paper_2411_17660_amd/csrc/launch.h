@@ -55,12 +55,14 @@ void launch_offsets_scan(hipStream_t st, const uint32_t* skey, const uint32_t* p
                          const uint2* trect, uint64_t m, uint32_t* cnt_sorted,
                          uint2* trect_sorted, uint64_t* offsets, uint64_t* block_tmp,
                          uint64_t* total, uint64_t* mailbox);
-// Few records: both of the above in two launches, from (keys, vals).
+// Few records: both of the above in a launch each, the sort from (keys, vals)
+// and with the records' tile rects and counts.
 bool rank_records(uint64_t m);
 void launch_rank_records(hipStream_t st, const uint32_t* keys, const uint32_t* vals, uint64_t m,
                          const uint2* trect, uint32_t* keys_out, uint32_t* vals_out,
-                         uint32_t* cnt_sorted, uint2* trect_sorted, uint64_t* offsets,
-                         uint64_t* total, uint64_t* mailbox);
+                         uint32_t* cnt_sorted, uint2* trect_sorted);
+void launch_ranked_scan(hipStream_t st, const uint32_t* cnt_sorted, uint64_t m, uint64_t* offsets,
+                        uint64_t* total, uint64_t* mailbox);
 // order: the records 0..m-1 in ascending order of size class (0: no key, else
 // 1 + floor(log2 of the key count)); *first (unless NULL) receives the
 // position of the first one of class `mark` or above (m if none).

@@ -386,7 +386,7 @@ gsr_status forward_impl(gsr_context* ctx, const gsr_settings* s, int64_t n, cons
     if (few)
       launch_rank_records(st, dkey, dval, M, P<uint2>(ctx->trect), P<uint32_t>(ctx->dkey_a),
                           P<uint32_t>(ctx->dval_a), P<uint32_t>(ctx->cnt_sorted),
-                          P<uint2>(ctx->trect_s), P<uint64_t>(ctx->offsets), d_count, mailbox);
+                          P<uint2>(ctx->trect_s));
     else
       launch_depth_sort(st, P<uint32_t>(ctx->dkey_a), P<uint32_t>(ctx->dval_a),
                         P<uint32_t>(ctx->dkey_b), P<uint32_t>(ctx->dval_b), M,
@@ -394,11 +394,15 @@ gsr_status forward_impl(gsr_context* ctx, const gsr_settings* s, int64_t n, cons
   }
   const uint32_t* perm = P<uint32_t>(ctx->dval_a);
   // A2 offsets over the depth-ordered records, K on the device
-  if (!few) {
+  {
     StageTimer t(ctx, st, timing, GSR_STAGE_OFFSETS);
-    launch_offsets_scan(st, P<uint32_t>(ctx->dkey_a), perm, P<uint2>(ctx->trect), M,
-                        P<uint32_t>(ctx->cnt_sorted), P<uint2>(ctx->trect_s),
-                        P<uint64_t>(ctx->offsets), P<uint64_t>(ctx->scan_tmp), d_count, mailbox);
+    if (few)
+      launch_ranked_scan(st, P<uint32_t>(ctx->cnt_sorted), M, P<uint64_t>(ctx->offsets), d_count,
+                         mailbox);
+    else
+      launch_offsets_scan(st, P<uint32_t>(ctx->dkey_a), perm, P<uint2>(ctx->trect), M,
+                          P<uint32_t>(ctx->cnt_sorted), P<uint2>(ctx->trect_s),
+                          P<uint64_t>(ctx->offsets), P<uint64_t>(ctx->scan_tmp), d_count, mailbox);
   }
   // key capacity
   uint64_t K = 0, cap = 0;

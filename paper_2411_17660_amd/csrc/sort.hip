@@ -1150,11 +1150,14 @@ bool rank_records(uint64_t m) { return m > 0 && m <= kRankRecords; }
 
 void launch_rank_records(hipStream_t st, const uint32_t* keys, const uint32_t* vals, uint64_t m,
                          const uint2* trect, uint32_t* keys_out, uint32_t* vals_out,
-                         uint32_t* cnt_sorted, uint2* trect_sorted, uint64_t* offsets,
-                         uint64_t* total, uint64_t* mailbox) {
+                         uint32_t* cnt_sorted, uint2* trect_sorted) {
   hipLaunchKernelGGL(rank_records_kernel, dim3(blocks_for(m, kWave)), dim3(kRankWaves * kWave), 0,
                      st, keys, vals, (uint32_t)m, trect, keys_out, vals_out, cnt_sorted,
                      trect_sorted);
+}
+
+void launch_ranked_scan(hipStream_t st, const uint32_t* cnt_sorted, uint64_t m, uint64_t* offsets,
+                        uint64_t* total, uint64_t* mailbox) {
   hipLaunchKernelGGL(scan_few_kernel, dim3(1), dim3(kScanFewThreads), 0, st, cnt_sorted,
                      (uint32_t)m, offsets, total, mailbox);
 }

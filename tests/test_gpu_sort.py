@@ -100,3 +100,14 @@ def test_digit_columns_of_many_blocks(rast, blocks):
     order = np.lexsort((np.arange(n), dk))[:kept.sum()]
     np.testing.assert_array_equal(keys, np.repeat(np.arange(30), kept.sum()))
     np.testing.assert_array_equal(vals.reshape(30, -1), np.broadcast_to(order, (30, len(order))))
+
+
+@pytest.mark.parametrize("n", [0, 100, 16384, 16385])
+def test_every_stage_of_a_forward_is_timed(rast, n):
+    from gpu_util import gpu_forward
+    rast.timings()
+    gpu_forward(rast, _scene(n, 5), timing=True)
+    t = rast.timings()
+    for stage in ("preprocess", "depth_sort", "offsets", "keygen", "tile_sort", "ranges",
+                  "composite_fwd"):
+        assert t[stage][1] == 1, stage
