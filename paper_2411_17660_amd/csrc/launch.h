@@ -2,6 +2,8 @@
 // define them and by runtime.hip, which sequences them.  Internal to
 // libgsr.so; every launcher enqueues on `st` and returns without waiting.
 #pragma once
+#include <algorithm>
+
 #include "gsr.h"
 #include "gsr_device.h"
 
@@ -163,6 +165,17 @@ void launch_tile_order(hipStream_t st, int n_tiles, int groups, const uint32_t* 
                        uint32_t* order, uint32_t* clear = nullptr);
 unsigned tile_schedule_grid(int n_tiles, int groups);
 int tile_schedule_groups(bool xcd_groups);
+// The forward's workgroups, a wave per 8 x 8 block (`per_tile` of a tile): go(first,
+// count) launches `count` workgroups, whose (blockIdx.x / groups) counts from
+// `first` in their group.  One launch, unless it would have 2^32 threads, which
+// the runtime refuses (images of 2^32 pixels).
+template <typename Go>
+void for_block_runs(int n_tiles, int groups, int per_tile, Go go) {
+  constexpr uint64_t kMostBlocks = 1u << 25;  // a multiple of the groups
+  const uint64_t all = (uint64_t)tile_schedule_grid(n_tiles, groups) * per_tile;
+  for (uint64_t b = 0; b < all; b += kMostBlocks)
+    go((int)(b / groups), (unsigned)std::min(all - b, kMostBlocks));
+}
 
 // Sum of the per-wave twist partials [F][n_waves][6] into g_twist [F][6].
 void launch_twist_reduce(hipStream_t st, int F, const double* twist_partial, int64_t n_waves,

@@ -151,7 +151,7 @@ struct alignas(16) FwdEntry {
 // take part is kept as wave-uniform lane masks.
 template <int TW, int TH, bool COUNT, bool MEDIAN>
 __global__ void __launch_bounds__(kWave) composite_fwd_kernel(
-    int n_tiles, int groups, const uint32_t* __restrict__ order, int n_frames,
+    int first, int n_tiles, int groups, const uint32_t* __restrict__ order, int n_frames,
     const FrameDesc* __restrict__ frames, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ vals, const Record* __restrict__ rec, float bg0, float bg1,
     float bg2, float* __restrict__ rgb, float* __restrict__ depth, float* __restrict__ alpha,
@@ -161,7 +161,7 @@ __global__ void __launch_bounds__(kWave) composite_fwd_kernel(
   __shared__ FwdEntry sm[kWave + 2];
   // workgroup i of a group takes block i % kN of its (i / kN)-th tile, so that
   // a tile's blocks share the XCD of its group (and the records in its L2)
-  const int group = blockIdx.x % groups, i_wg = blockIdx.x / groups;
+  const int group = blockIdx.x % groups, i_wg = first + blockIdx.x / groups;
   const int tile = tile_of_block((i_wg / TB::kN) * groups + group, n_tiles, groups, order);
   if (tile < 0) return;
   const int blk = i_wg % TB::kN;
@@ -640,9 +640,11 @@ static void launch_fwd_t(hipStream_t st, int n_tiles, int groups, const uint32_t
                          float* alpha, float* t_final, int32_t* n_last, uint32_t* nproc,
                          unsigned long long* pairs, int32_t* med_pos) {
   const auto go = [&](auto* k) {
-    hipLaunchKernelGGL(k, dim3(grid_of(n_tiles, groups) * TileBlocks<TW, TH>::kN), dim3(kWave), 0,
-                       st, n_tiles, groups, order, F, frames, ranges, vals, rec, bg[0], bg[1],
-                       bg[2], rgb, depth, alpha, t_final, n_last, nproc, pairs, med_pos);
+    for_block_runs(n_tiles, groups, TileBlocks<TW, TH>::kN, [&](int first, unsigned blocks) {
+      hipLaunchKernelGGL(k, dim3(blocks), dim3(kWave), 0, st, first, n_tiles, groups, order, F,
+                         frames, ranges, vals, rec, bg[0], bg[1], bg[2], rgb, depth, alpha, t_final,
+                         n_last, nproc, pairs, med_pos);
+    });
   };
   if (pairs && med_pos) go(composite_fwd_kernel<TW, TH, true, true>);
   else if (pairs) go(composite_fwd_kernel<TW, TH, true, false>);

@@ -348,7 +348,7 @@ struct alignas(16) FwdSurfel {
 // (one atomic add per block).
 template <int TW, int TH, bool COUNT>
 __global__ void __launch_bounds__(kWave) surfel_fwd_kernel(
-    int n_tiles, int groups, const uint32_t* __restrict__ order, uint32_t* __restrict__ tile_nproc,
+    int first, int n_tiles, int groups, const uint32_t* __restrict__ order, uint32_t* __restrict__ tile_nproc,
     unsigned long long* __restrict__ pair_count,
     int n_frames, const FrameDesc* __restrict__ frames, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ vals, const Surfel* __restrict__ rec, float bg0, float bg1,
@@ -357,7 +357,7 @@ __global__ void __launch_bounds__(kWave) surfel_fwd_kernel(
     int32_t* __restrict__ n_last, float* __restrict__ dist_aux /* [P][4]: z_ref, A, D_1, D_2 */) {
   using TB = TileBlocks<TW, TH>;
   __shared__ FwdSurfel sm[kWave + 2];
-  const int group = blockIdx.x % groups, i_wg = blockIdx.x / groups;
+  const int group = blockIdx.x % groups, i_wg = first + blockIdx.x / groups;
   const int tile = tile_of_block((i_wg / TB::kN) * groups + group, n_tiles, groups, order);
   if (tile < 0) return;
   const int blk = i_wg % TB::kN;
@@ -1071,13 +1071,13 @@ void launch_surfel_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
   if (n_tiles <= 0) return;
   const int groups = tile_schedule_groups(xcd_groups);
   launch_tile_order(st, n_tiles, groups, prev_nproc, order, nproc);
-  const unsigned grid = tile_schedule_grid(n_tiles, groups);
-#define GSR_SURF_FWD_C(W, H, C)                                                             \
-  hipLaunchKernelGGL((surfel_fwd_kernel<W, H, C>), dim3(grid * TileBlocks<W, H>::kN),        \
-                     dim3(kWave), 0, st, n_tiles,                                          \
-                     groups, order, nproc, pairs, F, frames, ranges, vals, (const Surfel*)rec, \
-                     bg[0], bg[1], bg[2], rgb, depth, alpha, normal, dist, t_final, n_last,  \
-                     dist_aux)
+#define GSR_SURF_FWD_C(W, H, C)                                                               \
+  for_block_runs(n_tiles, groups, TileBlocks<W, H>::kN, [&](int first, unsigned blocks) {     \
+    hipLaunchKernelGGL((surfel_fwd_kernel<W, H, C>), dim3(blocks), dim3(kWave), 0, st, first, \
+                       n_tiles, groups, order, nproc, pairs, F, frames, ranges, vals,         \
+                       (const Surfel*)rec, bg[0], bg[1], bg[2], rgb, depth, alpha, normal,    \
+                       dist, t_final, n_last, dist_aux);                                      \
+  })
 #define GSR_SURF_FWD(W, H)                 \
   if (pairs) GSR_SURF_FWD_C(W, H, true);   \
   else GSR_SURF_FWD_C(W, H, false)
