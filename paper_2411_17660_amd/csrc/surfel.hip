@@ -567,28 +567,34 @@ __global__ void __launch_bounds__(TW* TH / PIX) surfel_bwd_kernel(
   for (int k = 0; k < PIX; ++k) {
     const int px = bx0 + (k % kCols) * kBlk + (lane & 7);
     const int py = by0 + (k / kCols) * kBlk + (lane >> 3);
+    // pixels outside read the nearest one inside, and its values are dropped:
+    // the loads need no branch each, so that all are in flight together
     const bool valid = px < fr.width && py < fr.height;
-    const int64_t p = (int64_t)py * fr.width + px;
+    const int64_t p = (int64_t)min(py, fr.height - 1) * fr.width + min(px, fr.width - 1);
     const int64_t q = fr.pixel_offset + p;
-    last[k] = valid ? n_last[q] - seg0 : 0;
-    T[k] = valid ? t_final[q] : 1.0f;
-    const float4 ax = valid ? reinterpret_cast<const float4*>(dist_aux)[q]
-                            : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    ZR[k] = ax.x;
-    AT[k] = ax.y;
-    S1[k] = ax.z;
-    S2[k] = ax.w;
+    const int nl = n_last[q];
+    const float tf = t_final[q];
+    const float4 ax = reinterpret_cast<const float4*>(dist_aux)[q];
     const float* gi = g_rgb + 3 * fr.pixel_offset;
     const float* gn = g_normal + 3 * fr.pixel_offset;
-    H0[k] = valid ? gi[p] : 0.0f;
-    H1[k] = valid ? gi[plane + p] : 0.0f;
-    H2[k] = valid ? gi[2 * plane + p] : 0.0f;
-    HN0[k] = valid ? gn[p] : 0.0f;
-    HN1[k] = valid ? gn[plane + p] : 0.0f;
-    HN2[k] = valid ? gn[2 * plane + p] : 0.0f;
-    HD[k] = valid ? g_depth[q] : 0.0f;
-    HE[k] = valid ? g_dist[q] : 0.0f;
-    const double ha = valid ? g_alpha[q] : 0.0f;
+    const float g0 = gi[p], g1 = gi[plane + p], g2 = gi[2 * plane + p];
+    const float gn0 = gn[p], gn1 = gn[plane + p], gn2 = gn[2 * plane + p];
+    const float gd = g_depth[q], ge = g_dist[q], ga = g_alpha[q];
+    last[k] = valid ? nl - seg0 : 0;
+    T[k] = valid ? tf : 1.0f;
+    ZR[k] = valid ? ax.x : 0.0f;
+    AT[k] = valid ? ax.y : 0.0f;
+    S1[k] = valid ? ax.z : 0.0f;
+    S2[k] = valid ? ax.w : 0.0f;
+    H0[k] = valid ? g0 : 0.0f;
+    H1[k] = valid ? g1 : 0.0f;
+    H2[k] = valid ? g2 : 0.0f;
+    HN0[k] = valid ? gn0 : 0.0f;
+    HN1[k] = valid ? gn1 : 0.0f;
+    HN2[k] = valid ? gn2 : 0.0f;
+    HD[k] = valid ? gd : 0.0f;
+    HE[k] = valid ? ge : 0.0f;
+    const double ha = valid ? ga : 0.0f;
     // behind the last entry: the background colour, zero depth, normal, e and
     // alpha (less G_A, the share of every entry's alpha of 1 in G . v_i)
     E[k] = __builtin_fma(H2[k], (double)bg2,
