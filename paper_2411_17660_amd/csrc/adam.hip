@@ -65,10 +65,10 @@ __global__ void __launch_bounds__(256) adam_gauss_kernel(uint64_t n3, uint64_t n
   const uint64_t v3 = n3 / V, vsh = nsh / V;
   for (uint64_t i = first; i < v3 + vsh; i += stride) {
     const bool is_mean = i < v3;
-    const AdamGroup& a = is_mean ? means : sh;
-    const float lr = is_mean ? h.lr_means : h.lr_sh;
-    const uint64_t j = is_mean ? i : i - v3;
     if constexpr (V == 4) {
+      const AdamGroup& a = is_mean ? means : sh;
+      const float lr = is_mean ? h.lr_means : h.lr_sh;
+      const uint64_t j = is_mean ? i : i - v3;
       float4 p = reinterpret_cast<float4*>(a.p)[j];
       const float4 g = reinterpret_cast<const float4*>(a.g)[j];
       float4 m = reinterpret_cast<float4*>(a.m)[j], v = reinterpret_cast<float4*>(a.v)[j];
@@ -79,8 +79,10 @@ __global__ void __launch_bounds__(256) adam_gauss_kernel(uint64_t n3, uint64_t n
       reinterpret_cast<float4*>(a.p)[j] = p;
       reinterpret_cast<float4*>(a.m)[j] = m;
       reinterpret_cast<float4*>(a.v)[j] = v;
+    } else if (is_mean) {  // (a branch: addresses by selection take a seventh longer here)
+      adam_one(means, i, h.lr_means, h, c1, c2);
     } else {
-      adam_one(a, j, lr, h, c1, c2);
+      adam_one(sh, i - v3, h.lr_sh, h, c1, c2);
     }
   }
   if (first < n3 % V) adam_one(means, n3 - 1 - first, h.lr_means, h, c1, c2);
