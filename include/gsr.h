@@ -85,9 +85,10 @@ typedef struct {
   int32_t lds_batch;      /* 0, 32, 64 or 128: accepted, without effect on results or
                              speed (the compositing kernels stage 64 entries per round) */
   int64_t key_capacity;   /* 0: the library sizes the key buffers from the
-                             exact count (one 8-byte device->host read per
-                             forward); > 0: fixed capacity, no host read, and
-                             an overflow is reported by gsr_check_overflow */
+                             exact count (each forward waits for it; a kernel
+                             writes it to host memory that the call watches);
+                             > 0: fixed capacity, no wait, and an overflow is
+                             reported by gsr_check_overflow */
   uint32_t flags;         /* GSR_FLAG_* */
 } gsr_settings;
 

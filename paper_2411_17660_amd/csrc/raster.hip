@@ -290,7 +290,7 @@ struct alignas(16) BwdEntry {  // as Entry, the colour and depth already FP64
   double c0, c1, c2, z;
 };
 
-template <int WAVES, bool MEDIAN>
+template <int WAVES>
 struct BwdLds {
   BwdEntry sm[WAVES > 1 ? 2 : 1][kBatchB];
   uint32_t slot[WAVES > 1 ? 2 : 1][kBatchB];
@@ -315,7 +315,7 @@ __global__ void __launch_bounds__(TW* TH / PIX, PIX == 4 ? 3 : 4) composite_bwd_
   // or a part of one row)
   constexpr int kCols = PIX < TB::kX ? PIX : TB::kX, kRows = PIX / kCols;
   static_assert(TB::kX % kCols == 0, "blocks of a wave form a rectangle");
-  __shared__ BwdLds<WAVES, MEDIAN> L;
+  __shared__ BwdLds<WAVES> L;
   const int tile = tile_of_block(blockIdx.x, n_tiles, groups, order);
   if (tile < 0) return;
   uint32_t nproc = tile_nproc[tile];

@@ -12,8 +12,8 @@
 //      (up to 65,535 tiles), else 32; a stable LSD radix over only the
 //      tile-id bits (two passes of <= 10 bits up to 2^20 tiles) then groups
 //      the keys by tile while keeping the depth order inside each tile.
-// With 16-bit keys, keygen, the two passes and the ranges move 36 bytes per
-// key, instead of 6-7 passes over 12-byte (tile | depth, value) pairs.
+// With 16-bit keys, keygen and the two passes move 34 bytes per key, instead of
+// 6-7 passes over 12-byte (tile | depth, value) pairs; the ranges search.
 //
 // The radix passes use a hand-written LDS multi-split: each wave ranks its
 // 64 keys per round with one ballot per digit bit (lanes with equal digits
@@ -224,10 +224,10 @@ __global__ void __launch_bounds__(kScanFewThreads) scan_few_kernel(
 // ---------------------------------------------------------------------------
 // Stable LSD radix pass over the digit of `width` <= 10 bits at `shift`.
 //
-// A block of WAVES waves owns WAVES * 1024 consecutive keys, wave w the
-// contiguous 1024 keys from w * 1024 as 16 rounds of 64.  Each lane loads
-// its 16 keys and values straight into registers (fully unrolled, so all the
-// loads are in flight at once).  Per round a wave ranks its 64 keys by digit
+// A block of WAVES waves owns WAVES * 64 R consecutive keys, wave w the
+// contiguous 64 R keys from w * 64 R as R rounds of 64 (16, or 8 where there
+// are few keys).  Each lane loads its R keys and values straight into registers
+// (fully unrolled, so all the loads are in flight at once).  Per round a wave ranks its 64 keys by digit
 // with one ballot per digit bit, 8 or 10 whatever the width (lanes with
 // equal digits form one mask); the lowest lane of each group bumps the
 // wave's LDS counter.  No atomics there, so the
@@ -482,7 +482,7 @@ struct ScatterLds {
 };
 
 // Ranks the block's keys (lane's round-k key is block-local index
-// w 1024 + 64 k + lane; L.wcnt zeroed and the zeroing visible to all waves),
+// w 64 R + 64 k + lane; L.wcnt zeroed and the zeroing visible to all waves),
 // moves them into digit order through L.sk / L.sv and writes them to
 // (global start of digit d) + (position inside the block's run of digit d).
 // The combine folds the block-local digit starts into the waves' bases and

@@ -491,7 +491,7 @@ constexpr int kSG = 16;
 // another, two row rotations for the remaining bits.  What bounds it: VALU
 // issue (~190 instructions a visit, half of them FP64).  One wave per tile and
 // a reduction through LDS took 3810 us on 250k surfels over 4 x 1200x680 and
-// 843 us on 20k over one 321x243 frame; this takes 3436 and 316, the latter 220
+// 843 us on 20k over one 321x243 frame; this takes 3340 and 319, the latter 207
 // us in eight segments (both launches).
 constexpr int kBatchB = 64;          // list entries per batch
 constexpr int kBwdMinWaves = 4096;  // four waves on each of the 1,024 SIMDs
@@ -1144,7 +1144,7 @@ void launch_surfel_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
   launch_tile_order(st, n_tiles, groups, nproc, order);
   // Blocks per wave: as many as leave kBwdMinWaves waves, as in the 3D
   // backward.  Measured with 1 / 2 / 4 blocks (us): 4 x 1200x680 (12,900 tiles
-  // of 16x16) 4445 / 4142 / 3436; 1 x 321x243 (336 tiles) 316 / 474 / 708.
+  // of 16x16) 4417 / 4079 / 3325; 1 x 321x243 (336 tiles) 319 / 455 / 713.
   const int blocks = tw * th / kWave;
   int pix = 4;
   while (pix > 1 && (int64_t)n_tiles * blocks / pix < kBwdMinWaves) pix /= 2;
