@@ -585,7 +585,7 @@ def measure_render_loss(rast, sc, dev, bb, t_rgb, t_dep, tile, cap, steps):
     return {"lambda1": 0.9, "lambda2": 0.2, "ms_per_call": round(ms, 4),
             "ssim_per_frame": [round(float(v), 6) for v in out["ssim"].cpu()],
             "loss": float(out["loss"].item()),
-            "bound": "hbm", "hbm_bytes_per_call": nbytes, "achieved_GBps": round(gbs, 1),
+            "bound": "alu", "hbm_bytes_per_call": nbytes, "achieved_GBps": round(gbs, 1),
             "peak_GBps": PEAK_HBM_GBS, "frac": round(gbs / PEAK_HBM_GBS, 4),
             "fp64_flops_per_call": flops, "achieved_fp64_TFLOPs": round(tfl, 3),
             "frac_fp64_peak": round(tfl / PEAK_FP64_VECTOR_TFLOPS, 4),
