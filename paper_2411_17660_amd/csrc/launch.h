@@ -106,7 +106,7 @@ void launch_composite_fwd(hipStream_t st, int tw, int th, int n_tiles, int F,
 // The segments that the backward cuts every tile's list into (1: none), and
 // the bytes that the pixels' state changes over them (`maps`) may need.
 int bwd_segments(uint64_t keys, int64_t n_tiles, int tw, int th);
-size_t bwd_map_bytes(int64_t n_tiles, int tw, int th);
+size_t bwd_map_bytes();
 void launch_composite_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,
                           const Record* rec, const uint32_t* keyoff, const uint32_t* nproc,

@@ -725,13 +725,9 @@ int bwd_segments(uint64_t keys, int64_t n_tiles, int tw, int th) {
   return few && keys >= 2 * kBatchB * (uint64_t)n_tiles ? kSegments : 1;
 }
 
-// For every key count and every smaller number of tiles (11 MB at most), so
-// that a call which takes segments needs no more than a larger one before it
-// that took none: a capture may follow with fewer frames or another capacity.
-size_t bwd_map_bytes(int64_t n_tiles, int tw, int th) {
-  const int64_t waves = std::min(n_tiles * (tw * th / kWave), kFewWaves);
-  return (size_t)waves * kWave * (kSegments - 1) * sizeof(double2);
-}
+// For every call that takes segments (11 MB), whatever the one before it took:
+// a capture may follow with fewer frames, another tile shape or capacity.
+size_t bwd_map_bytes() { return (size_t)kFewWaves * kWave * (kSegments - 1) * sizeof(double2); }
 
 void launch_composite_bwd(hipStream_t st, int tw, int th, int n_tiles, int F,
                           const FrameDesc* frames, const uint2* ranges, const uint32_t* vals,

@@ -586,7 +586,7 @@ gsr_status gsr_backward_surfel(gsr_context* ctx, const float* g_rgb, const float
   if ((rc = ensure(ctx, ctx->sgrad, std::max<uint64_t>(M, 1) * ng * 8, st))) return rc;
   if ((rc = ensure(ctx, ctx->cls_order, M * 4, st))) return rc;
   const int segments = bwd_segments(sv.K, sv.T, s.tile_w, s.tile_h);
-  if ((rc = ensure(ctx, ctx->bwd_maps, bwd_map_bytes(sv.T, s.tile_w, s.tile_h), st))) return rc;
+  if ((rc = ensure(ctx, ctx->bwd_maps, bwd_map_bytes(), st))) return rc;
   const int64_t waves = sv.n > 0 ? surfel_preprocess_bwd_waves(sv.n) : 0;
   if ((rc = ensure(ctx, ctx->twist_part, (size_t)std::max<int64_t>(waves, 1) * sv.F * 6 * 8, st)))
     return rc;
@@ -651,7 +651,7 @@ gsr_status gsr_backward(gsr_context* ctx, const float* g_rgb, const float* g_dep
   const bool timing = (s.flags & GSR_FLAG_TIMING) != 0;
   // A8 reverse compositing -> per-key partials
   const int segments = bwd_segments(sv.K, sv.T, s.tile_w, s.tile_h);
-  if ((rc = ensure(ctx, ctx->bwd_maps, bwd_map_bytes(sv.T, s.tile_w, s.tile_h), st))) return rc;
+  if ((rc = ensure(ctx, ctx->bwd_maps, bwd_map_bytes(), st))) return rc;
   {
     StageTimer t(ctx, st, timing, GSR_STAGE_COMPOSITE_BWD);
     launch_composite_bwd(st, s.tile_w, s.tile_h, (int)sv.T, sv.F,

@@ -29,7 +29,7 @@ def _check_capture(r, outputs, call, ref_outputs, ref_call):
     r.check_overflow()
 
 
-def _fit(r, sc, surfel, n=None):
+def _fit(r, sc, surfel, n=None, tile=(16, 16)):
     """(outputs, call(key_capacity)): a forward and its backward into fixed
     buffers."""
     import torch
@@ -49,7 +49,7 @@ def _fit(r, sc, surfel, n=None):
 
     def call(cap):
         (r.forward_surfel if surfel else r.forward)(*args, sc.cams, sc.sh_degree, sc.background,
-                                                    key_capacity=cap, out=im)
+                                                    key_capacity=cap, out=im, tile=tile)
         (r.backward_surfel if surfel else r.backward)(*G, out=g)
     return list(im) + list(g.values()), call
 
@@ -120,3 +120,17 @@ def test_capture_of_the_rendering_loss(frames, in_place):
     fit(r, 6, False)[1]()
     outputs, call = fit(r, frames, in_place)
     _check_capture(r, outputs, call, *fit(Rasterizer(0), frames, False))
+
+
+@pytest.mark.parametrize("surfel", [False, True])
+def test_capture_with_another_tile_shape(surfel):
+    """Few 8x8 tiles, then one large tile whose blocks beyond the image count as
+    well."""
+    from paper_2411_17660_amd.raster import Rasterizer
+    sc = scenes.tiny_scene(seed=7, n=600, W=40, H=24, f=32.0, sh_degree=0, ls_mean=-2.0)
+    cap = 20000
+    r = Rasterizer(0)
+    _fit(r, sc, surfel, tile=(8, 8))[1](cap)
+    outputs, call = _fit(r, sc, surfel, tile=(32, 16))
+    ref_outputs, ref_call = _fit(Rasterizer(0), sc, surfel, tile=(32, 16))
+    _check_capture(r, outputs, lambda: call(cap), ref_outputs, lambda: ref_call(cap))
