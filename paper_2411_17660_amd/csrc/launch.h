@@ -135,7 +135,7 @@ struct SsimPlan {
   int units;        // blocks per plane of the largest frame
   int64_t max_px;   // pixels of the largest frame
   // units of any plan for no more and no larger frames (fewer frames are cut
-  // finer), by which workspace is sized
+  // finer) and more, without the steps of whole units: workspace is sized by it
   int64_t units_max;
 };
 SsimPlan ssim_plan(const FrameDesc* host_frames, int F);

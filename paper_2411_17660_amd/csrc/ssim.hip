@@ -540,7 +540,7 @@ SsimPlan ssim_plan(const FrameDesc* frames, int F) {
     max_h = std::max(max_h, (int)frames[f].height);
   }
   const int64_t units_max =
-      (int64_t)((max_w + kOutCols - 1) / kOutCols) * ((max_h + kMinSeg - 1) / kMinSeg);
+      (int64_t)((max_w / (double)kOutCols + 1.0) * (max_h / (double)kMinSeg + 1.0));
   for (int c = kMinChunks; c <= kMaxChunks; ++c) {
     const int seg = kTaps * c - kLag;
     int64_t pairs = 0, most = 0, px = 0;

@@ -134,3 +134,29 @@ def test_capture_with_another_tile_shape(surfel):
     outputs, call = _fit(r, sc, surfel, tile=(32, 16))
     ref_outputs, ref_call = _fit(Rasterizer(0), sc, surfel, tile=(32, 16))
     _check_capture(r, outputs, lambda: call(cap), ref_outputs, lambda: ref_call(cap))
+
+
+def test_capture_of_a_slightly_larger_loss():
+    """One column more, inside the workspaces' headroom, and a second strip."""
+    import torch
+    from gpu_util import to_dev
+    from paper_2411_17660_amd.raster import Rasterizer
+
+    def fit(r, W):
+        sc = scenes.tiny_scene(seed=7, n=50, W=W, H=220, f=100.0, sh_degree=0, ls_mean=-2.6)
+        d, P = to_dev(sc), sc.n_pixels
+        im = tuple(torch.rand(k * P, generator=torch.Generator().manual_seed(1)).cuda()
+                   for k in (3, 1, 3, 1))
+        out = dict(loss=torch.empty(1, device="cuda"), ssim=torch.empty(1, device="cuda"),
+                   g_rgb=torch.empty(3 * P, device="cuda"),
+                   g_depth=torch.empty(P, device="cuda"), g_alpha=torch.empty(P, device="cuda"))
+        buf = tuple(torch.empty(k * P, device="cuda") for k in (3, 1, 1))
+
+        def call():
+            r.forward(*[d[k] for k in ("means", "log_scales", "quats", "opacity", "sh", "poses")],
+                      sc.cams, 0, sc.background, key_capacity=20000, out=buf)
+            r.loss_render(*im, out=out)
+        return list(out.values()), call
+    r = Rasterizer(0)
+    fit(r, 118)[1]()
+    _check_capture(r, *fit(r, 119), *fit(Rasterizer(0), 119))
