@@ -266,17 +266,15 @@ constexpr uint64_t kNoCount = ~0ull;
 gsr_status await_count(gsr_context* ctx, hipStream_t st, uint64_t* out) {
   const hipError_t before = hipGetLastError();  // of the launches, or of an earlier call
   const uint64_t* box = ctx->h_count + kMailbox;
-  // (a stream in capture runs nothing: its synchronisation says so)
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
   uint64_t v;
   for (uint32_t i = 1; (v = __atomic_load_n(box, __ATOMIC_ACQUIRE)) == kNoCount; ++i) {
-    if (cap == hipStreamCaptureStatusNone) {
-      if (i % 4096 != 0) continue;
-      const hipError_t e = hipStreamQuery(st);
-      (void)hipGetLastError();  // ("not ready" is no error of this call)
-      if (e == hipErrorNotReady) continue;
-    }
+    if (i % 4096 != 0) continue;
+    // (a stream in capture runs nothing: its synchronisation says so)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(st, &cap);
+    if (e != hipSuccess || cap == hipStreamCaptureStatusNone) e = hipStreamQuery(st);
+    (void)hipGetLastError();  // ("not ready" is no error of this call)
+    if (e == hipErrorNotReady) continue;
     GSR_HIP(hipStreamSynchronize(st));
     v = __atomic_load_n(box, __ATOMIC_ACQUIRE);
     GSR_HIP(before);
