@@ -227,14 +227,13 @@ __global__ void __launch_bounds__(kScanFewThreads) scan_few_kernel(
 // A block of WAVES waves owns WAVES * 64 R consecutive keys, wave w the
 // contiguous 64 R keys from w * 64 R as R rounds of 64 (16, or 8 where there
 // are few keys).  Each lane loads its R keys and values straight into registers
-// (fully unrolled, so all the loads are in flight at once).  Per round a wave ranks its 64 keys by digit
-// with one ballot per digit bit, 8 or 10 whatever the width (lanes with
-// equal digits form one mask); the lowest lane of each group bumps the
-// wave's LDS counter.  No atomics there, so the
-// ranks are deterministic and the scatter is stable.  The keys then pass
-// through LDS in digit order so that each digit's run leaves the block as
-// consecutive stores.  BINS (256 or 1024) sizes the LDS counters; the pass
-// uses 2^width of them.
+// (fully unrolled, so all the loads are in flight at once).  Per round a wave
+// ranks its 64 keys by digit with one ballot per digit bit, 8 or 10 whatever
+// the width (lanes with equal digits form one mask); the lowest lane of each
+// group bumps the wave's LDS counter.  No atomics there, so the ranks are
+// deterministic and the scatter is stable.  The keys then pass through LDS in
+// digit order so that each digit's run leaves the block as consecutive stores.
+// BINS (256 or 1024) sizes the LDS counters; the pass uses 2^width of them.
 // ---------------------------------------------------------------------------
 
 // The lanes whose digits d agree with this lane's on the bits [0, NBITS).
@@ -1266,7 +1265,8 @@ void launch_offsets_scan(hipStream_t st, const uint32_t* skey, const uint32_t* p
                        cnt_sorted, trect_sorted, block_tmp);
   const unsigned nb = blocks_for(m, kScanTile);
   const bool spine = nb > kSpineBlocks;
-  if (spine) hipLaunchKernelGGL(scan_spine_kernel, dim3(1), dim3(kSpineThreads), 0, st, block_tmp, nb);
+  if (spine)
+    hipLaunchKernelGGL(scan_spine_kernel, dim3(1), dim3(kSpineThreads), 0, st, block_tmp, nb);
   hipLaunchKernelGGL(scan_down_kernel, dim3(nb), block, 0, st, cnt_sorted, m, block_tmp,
                      spine ? 0u : kScanItems / items, offsets, total, mailbox);
 }

@@ -348,8 +348,8 @@ struct alignas(16) FwdSurfel {
 // (one atomic add per block).
 template <int TW, int TH, bool COUNT>
 __global__ void __launch_bounds__(kWave) surfel_fwd_kernel(
-    int first, int n_tiles, int groups, const uint32_t* __restrict__ order, uint32_t* __restrict__ tile_nproc,
-    unsigned long long* __restrict__ pair_count,
+    int first, int n_tiles, int groups, const uint32_t* __restrict__ order,
+    uint32_t* __restrict__ tile_nproc, unsigned long long* __restrict__ pair_count,
     int n_frames, const FrameDesc* __restrict__ frames, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ vals, const Surfel* __restrict__ rec, float bg0, float bg1,
     float bg2, float* __restrict__ rgb, float* __restrict__ depth, float* __restrict__ alpha,

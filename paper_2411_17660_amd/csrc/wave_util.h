@@ -1,7 +1,8 @@
 // wave_util.h -- wave-level helpers shared by the kernels of the 3D Gaussian
 // and 2D surfel paths: the FP64 cross-lane swaps and DPP moves, the
-// transposing wave sum built on them, the XCD-grouped tile schedule, and the 8 x 8 pixel blocks the compositing kernels work over with
-// the test of an entry against a block.
+// transposing wave sum built on them, the XCD-grouped tile schedule, and the
+// 8 x 8 pixel blocks the compositing kernels work over with the test of an
+// entry against a block.
 #pragma once
 #include "gsr_device.h"
 
